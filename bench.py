@@ -2,10 +2,13 @@
 
 Workload: the 1.2M-cell synthetic netlist (150 macros, 1.3M nets, ~4.5M pins, grid
 1024 x 1024 x 4, seed 2403).  Two forms run from the same seed:
-  plain  -- float32 DCT contractions, the paper's field-gather density gradient
-  mixed  -- split-bf16 (hi/lo, three products, float32 accumulation) DCT contractions, same
-            field-gather gradient (the precision form of this workload)
-  autograd (optional, --forms) -- split-bf16 contractions with the exact-adjoint density gradient
+  plain  -- float32, the paper's field-gather density gradient
+  mixed  -- the precision form (PLACE3D_BF16X3): compensated exponential sums, same field-gather
+            gradient
+  autograd (optional, --forms) -- the precision form with the exact-adjoint density gradient
+The solve of a grid with power-of-two planar sides runs by float32 fast transforms in the plain and
+mixed forms; on other grids the plain form contracts in float32 and mixed in split bf16 (hi/lo,
+three products, float32 accumulation), as autograd does on every grid.
 A step is one full GP iteration (place3d_step): density map, spectral solve, density gradient,
 bistratal WA wirelength with the FDA z-gradient, preconditioned Nesterov move.  `value` is the
 mixed form's iterations/s over exactly --steps timed steps after --warmup warm-up and
@@ -63,6 +66,19 @@ def gemm_flops_per_step(nx, ny, nz, dgrad_field, bf16x3):
     if nx % 2 == 0 and ny % 2 == 0:
         total *= 0.5
     return total * (3.0 if bf16x3 else 1.0)
+
+
+def fast_solve(nx, ny, nz, dgrad_field):
+    """Whether the library solves this grid by fast transforms (float32 in both precisions)."""
+    side = lambda n: 64 <= n <= 2048 and n & (n - 1) == 0  # noqa: E731
+    return dgrad_field and side(nx) and side(ny) and nz in (2, 4)
+
+
+def fft_bytes_per_step(bins):
+    """Bytes the three fast-transform launches of one step have to move, 4 B per bin and map: x
+    forward (map in, spectra out), y (spectra in, two inverse-y results out), x inverse (those in,
+    three field maps out)."""
+    return 4.0 * bins * (2 + 3 + 5)
 
 
 def wl_bytes(n, P, m):
@@ -631,8 +647,10 @@ def main():
         prof = head["prof"]
         ps = args.profile_steps
         field_form = head_name != "autograd"
+        fast = fast_solve(case.nx, case.ny, case.nz, field_form)
         cands = {
-            "gemm": ("mfma", gemm_flops_per_step(case.nx, case.ny, case.nz, field_form, bf16x3) / 1e12,
+            "gemm": ("hbm", fft_bytes_per_step(bins) / 1e9, HBM_PEAK_GBS, "GB/s") if fast else (
+                "mfma", gemm_flops_per_step(case.nx, case.ny, case.nz, field_form, bf16x3) / 1e12,
                      PEAK_TFLOPS["bf16" if bf16x3 else "f32"], "TFLOP/s"),
             "wl_nets": ("hbm", wl_bytes(n, P, m) / 1e9, HBM_PEAK_GBS, "GB/s"),
             "density": ("hbm", density_bytes(n, bins) / 1e9, HBM_PEAK_GBS, "GB/s"),
@@ -664,7 +682,8 @@ def main():
         "repeats": args.repeats, "readback_every": args.readback_every,
         "runs_iters_per_s": [round(v, 1) for v in head["runs"]],
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "bf16x3/f32" if bf16x3 else "f32", "data": "synthetic",
+        "dtype": "bf16x3/f32" if bf16x3 and not fast_solve(case.nx, case.ny, case.nz, head_name != "autograd")
+        else "f32", "data": "synthetic",
         "config": {"workload": f"{args.config}: {n - case.meta['n_macros']} cells + {case.meta['n_macros']} macros, "
                                f"{m} nets, {P} pins, grid {case.nx}x{case.ny}x{case.nz}, seed {args.seed}",
                    "form": head_name, "parallelism": "single GPU"},

@@ -76,7 +76,11 @@ typedef enum place3d_status {
                                    with a pin                                                */
 } place3d_status;
 
-/* Arithmetic of the spectral contractions (a4, a5). */
+/* Arithmetic of the spectral solve (a4, a5) and of the wirelength's exponential sums.  Grids whose
+ * planar sides are powers of two in [64, 2048] with nz of 2 or 4 are solved by float32 fast
+ * transforms in both precisions (problems with PLACE3D_DGRAD_FIELD); on every other grid, and with
+ * PLACE3D_DGRAD_ADJOINT, the precision picks the dense contractions.
+ * BF16X3 also compensates the exponential sums, on every grid. */
 enum { PLACE3D_FP32 = 0,        /* float32 operands on float32 MFMA                          */
        PLACE3D_BF16X3 = 1 };    /* split hi/lo bfloat16 operands, three products, f32 accum  */
 
@@ -150,7 +154,8 @@ enum {
 /* Stages timed by the optional profiler (place3d_profile_enable / place3d_profile_read). */
 enum {
   PLACE3D_STAGE_DENSITY = 0,   /* density map by tiles: fixed-map copy, cell and macro deposits  */
-  PLACE3D_STAGE_GEMM = 1,      /* every DCT contraction launch (k_gemm_f32, k_gemm_bf16x3, k_sgemm) */
+  PLACE3D_STAGE_GEMM = 1,      /* every DCT launch: contractions (k_gemm_f32, k_gemm_bf16x3, k_sgemm)
+                                  or fast transforms (k_fft_x, k_fft_y, k_fft_ix)             */
   PLACE3D_STAGE_ZMIX = 2,      /* z mixing, spectral scaling, x fold / unfold between contractions */
   PLACE3D_STAGE_DGRAD = 3,     /* density gradient: field gather or exact adjoint                */
   PLACE3D_STAGE_WL_NETS = 4,   /* per-net WA / bistratal / FDA kernel                            */

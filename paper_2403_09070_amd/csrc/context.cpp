@@ -89,6 +89,23 @@ p3d::TileGeom tile_geom(const place3d_problem& p) {
   return t;
 }
 
+// Grids the fast transforms take: sides that are powers of two from 64 (below, a dense contraction
+// is as short as a launch) to 2048 (a workgroup's NZ groups of N / 16 lanes then reach 512 threads
+// and 70 KiB of LDS), and the two layer counts whose mixing a lane holds in registers.  They are
+// faster over the whole range in both precisions (Ex, Ey and Ez of a map, against the float32
+// contractions): 64 x 64 x 2 20 us against 42, 128 x 128 x 4 20 against 61, 512 x 512 x 4 26 against
+// 172, 1024 x 1024 x 4 53 against 418 (split bf16 154), 2048 x 2048 x 4 297 against 2569 (split bf16,
+// all four maps: 373 against 974).
+// The exact-adjoint form keeps the contractions: its gradient jumps where a cell's edge crosses a
+// bin face, so that after one step even the transforms' smaller rounding moves a few cells' whole
+// gradient (320k instances on 256 x 256 x 4: 6.5e-4 of the gradient's norm after two steps, where
+// the field form differs by 4e-6), and its iterates are kept as they are (386 us a step; 291 with
+// the transforms).
+bool fft_grid(const place3d_problem& p) {
+  auto side = [](int n) { return n >= 64 && n <= 2048 && (n & (n - 1)) == 0; };
+  return side(p.nx) && side(p.ny) && (p.nz == 2 || p.nz == 4) && p.dgrad == PLACE3D_DGRAD_FIELD;
+}
+
 int parts_bound(const place3d_problem& p, const p3d::TileGeom& t) {
   int b = std::max(p.n_nets / 4 + 16, p.n_inst / 256 + p.n_pins / 128 + 8);
   b = std::max(b, t.ntiles);
@@ -96,21 +113,16 @@ int parts_bound(const place3d_problem& p, const p3d::TileGeom& t) {
   return std::max(b, 1024);
 }
 
-size_t layout(place3d_ctx* c, const place3d_problem& p, char* base) {
-  Carver w{base};
-  c->tg = tile_geom(p);
-  c->part_stride = parts_bound(p, c->tg);
-  const size_t nx = p.nx, ny = p.ny, nz = p.nz, n = p.n_inst, P = p.n_pins, m = p.n_nets;
-  const size_t map = nx * ny * nz;
+// bases, split planes and intermediate maps of the dense contractions
+void layout_dense(place3d_ctx* c, const place3d_problem& p, Carver& w) {
+  const size_t nx = p.nx, ny = p.ny, nz = p.nz, map = nx * ny * nz;
   auto& d = c->dct;
   d.Fx = w.take<float>(nx * nx); d.Gx = w.take<float>(nx * nx); d.Hx = w.take<float>(nx * nx);
   d.FyT = w.take<float>(ny * ny); d.Gy = w.take<float>(ny * ny); d.Hy = w.take<float>(ny * ny);
   for (uint16_t** q : {&d.Fx_h, &d.Fx_l, &d.Gx_h, &d.Gx_l, &d.Hx_h, &d.Hx_l}) *q = w.take<uint16_t>(nx * nx);
   for (uint16_t** q : {&d.FyT_h, &d.FyT_l, &d.Gy_h, &d.Gy_l, &d.Hy_h, &d.Hy_l}) *q = w.take<uint16_t>(ny * ny);
-  d.zmat = w.take<float>(4 * p3d::kMaxNz * p3d::kMaxNz);
   {
     auto& q = c->sc;
-    q = p3d::SplitChain{};
     q.on = p.precision == PLACE3D_BF16X3 && nx % 2 == 0 && ny % 2 == 0 && (nz == 2 || nz == 4);
     if (q.on) {
       const size_t hx = nx / 2, hy = ny / 2, rx = (hx + 31) / 32 * 32, ry = (hy + 31) / 32 * 32;
@@ -124,9 +136,31 @@ size_t layout(place3d_ctx* c, const place3d_problem& p, char* base) {
     }
   }
   d.inv_w2 = w.take<float>(map);
-  c->map_t = w.take<float>(map); c->map_a = w.take<float>(map);
-  c->map_vg = w.take<float>(map); c->map_vh = w.take<float>(map);
+  c->map_a = w.take<float>(map);
   c->map_pc = w.take<float>(map); c->map_ps = w.take<float>(map); c->map_qc = w.take<float>(map);
+}
+
+size_t layout(place3d_ctx* c, const place3d_problem& p, char* base) {
+  Carver w{base};
+  c->tg = tile_geom(p);
+  c->part_stride = parts_bound(p, c->tg);
+  const size_t nx = p.nx, ny = p.ny, nz = p.nz, n = p.n_inst, P = p.n_pins, m = p.n_nets;
+  const size_t map = nx * ny * nz;
+  auto& d = c->dct;
+  d = p3d::DctBases{};
+  d.zmat = w.take<float>(4 * p3d::kMaxNz * p3d::kMaxNz);
+  c->fft = p3d::FftChain{};
+  c->fft.on = fft_grid(p);
+  c->sc = p3d::SplitChain{};
+  c->map_t = w.take<float>(map);
+  c->map_vg = w.take<float>(map); c->map_vh = w.take<float>(map);
+  if (c->fft.on) {
+    auto& q = c->fft;
+    q.tx = w.take<float2>(p3d::kFftTable * nx); q.wx = w.take<float2>(nx / 2 + 1);
+    q.ty = w.take<float2>(p3d::kFftTable * ny); q.wy = w.take<float2>(ny / 2 + 1);
+  } else {
+    layout_dense(c, p, w);
+  }
   c->rho = w.take<float>(map); c->phi = w.take<float>(map);
   c->ex = w.take<float>(map); c->ey = w.take<float>(map); c->ez = w.take<float>(map);
   c->fixed_map = w.take<float>(map);

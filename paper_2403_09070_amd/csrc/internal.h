@@ -85,6 +85,15 @@ struct SplitChain {
   HL vg, vh;             // inverse-y results (cosine, sine basis): [Nz Ny][2 rx], row = (z frequency, y)
 };
 
+// Fast transforms of the solve (fft_grid in context.cpp): tables per axis, the stages'
+// twiddles (at most kFftTable N entries) and e^{-i pi k / 2N} (k <= N / 2).  The dense bases and
+// the split chain are then not built.
+constexpr int kFftTable = 2;
+struct FftChain {
+  int on = 0;
+  float2 *tx = nullptr, *wx = nullptr, *ty = nullptr, *wy = nullptr;
+};
+
 }  // namespace p3d
 
 namespace p3d {
@@ -111,6 +120,7 @@ struct place3d_ctx {
   // spectral
   p3d::DctBases dct;
   p3d::SplitChain sc;
+  p3d::FftChain fft;
   float *map_t = nullptr, *map_a = nullptr, *map_vg = nullptr, *map_vh = nullptr;
   float *map_pc = nullptr, *map_ps = nullptr, *map_qc = nullptr;
   // step scratch maps (rho, phi, ex, ey, ez)
@@ -242,6 +252,10 @@ int spectral_field(place3d_ctx* c, const float* rho, float* phi, float* ex, floa
 // the split chain's bases (at creation) and its contractions; outputs in natural x order
 int build_split_chain(place3d_ctx* c, hipStream_t s);
 int field_split(place3d_ctx* c, const float* rho, float* phi, float* ex, float* ey, float* ez, hipStream_t s);
+
+// the fast transforms' tables (at creation) and their solve; outputs in natural x order
+int build_fft(place3d_ctx* c, hipStream_t s);
+int field_fft(place3d_ctx* c, const float* rho, float* phi, float* ex, float* ey, float* ez, hipStream_t s);
 
 // out[0..nq) = sums (max if is_max) of partial slots slot0.. over nparts blocks, fixed order
 int reduce_final(place3d_ctx* c, int slot0, int nq, int nparts, bool is_max, double* out, hipStream_t s);

@@ -23,7 +23,8 @@
 //   Pc, Ps, Qc = zmix_inv(Vg, Vh)    (cos / sin*omega_l along z)
 //   Ex = Pc . Hx, phi = Pc . Gx, Ey = Qc . Gx, Ez = Ps . Gx   (inverse x)
 // Every contraction is one launch of k_gemm: NN row-major, batched, with the float32 or the
-// split-bfloat16 (hi.hi + hi.lo + lo.hi, float32 accumulation) MFMA path.
+// split-bfloat16 (hi.hi + hi.lo + lo.hi, float32 accumulation) MFMA path.  Grids with power-of-two
+// planar sides (field form) take the fast transforms of spectral_fft.hip instead (fft_grid in context.cpp).
 #include <cmath>
 
 #include "internal.h"
@@ -759,6 +760,9 @@ int build_dct_bases(place3d_ctx* c, hipStream_t s) {
   const place3d_problem& p = c->prob;
   const double wb = p.die_x / p.nx, hb = p.die_y / p.ny, dz = p.nz * 0.5 * (wb + hb);
   c->dct.fold = (g.nx % 2 == 0 && g.ny % 2 == 0) ? 1 : 0;
+  hipLaunchKernelGGL(k_basis_z, dim3(1), dim3(kMaxNz * kMaxNz), 0, s, g.nz, dz, c->dct.zmat);
+  P3D_LAUNCH(c, "k_basis_z");
+  if (c->fft.on) return build_fft(c, s);
   hipLaunchKernelGGL(k_basis_x, dim3(blocks_for((long long)g.nx * g.nx, 256)), dim3(256), 0, s, g.nx, c->dct.fold,
                      p.die_x, c->dct.Fx, c->dct.Gx, c->dct.Hx);
   P3D_LAUNCH(c, "k_basis_x");
@@ -776,8 +780,6 @@ int build_dct_bases(place3d_ctx* c, hipStream_t s) {
     hipLaunchKernelGGL(k_split_bf16, dim3(by), dim3(256), 0, s, d.Hy, g.ny, g.ny, 0, d.Hy_h, d.Hy_l);
     P3D_LAUNCH(c, "k_split_bf16");
   }
-  hipLaunchKernelGGL(k_basis_z, dim3(1), dim3(kMaxNz * kMaxNz), 0, s, g.nz, dz, c->dct.zmat);
-  P3D_LAUNCH(c, "k_basis_z");
   const long long map = (long long)g.nx * g.ny * g.nz;
   hipLaunchKernelGGL(k_inv_w2, dim3(blocks_for(map, 256)), dim3(256), 0, s, g.nx, g.ny, g.nz, c->dct.fold, p.die_x,
                      p.die_y, dz, c->dct.inv_w2);
@@ -807,7 +809,10 @@ int spectral_field(place3d_ctx* c, const float* rho, float* phi, float* ex, floa
   if (ez) xo[nxo++] = {c->map_ps, Gx, ez, 1.f};
   if (phi) xo[nxo++] = {c->map_pc, Gx, phi, 1.f};
 
-  if (d.fold) {
+  if (c->fft.on) {
+    c->field_xfold = 0;
+    if ((rc = field_fft(c, rho, phi, ex, ey, ez, s))) return rc;
+  } else if (d.fold) {
     const int hx = nx / 2, hy = ny / 2;
     if (c->sc.on) {
       if ((rc = field_split(c, rho, phi, ex, ey, ez, s))) return rc;

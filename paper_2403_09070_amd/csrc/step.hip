@@ -331,9 +331,11 @@ int eval_parts(place3d_ctx* c, const float* xyz, float* gw, float* gd, double* r
   if ((rc = bucket_cells(c, xyz, s, 1))) return rc;  // the count pass packs xyz for the wirelength sweep
   // fork: the wirelength sweep (its own reduction slots, pin and instance scratch) runs on the
   // side stream while the bucketing, density, spectral and gather chain runs on s; joined below.
-  // With the float32 contractions (2.6 times as long as the split ones) the sweep forks after
-  // the scatter pass, which then runs alone, and overlaps the contractions; with the split ones
-  // it forks right after the count pass, so that it is mostly done before they start.
+  // With the fast transforms and the float32 contractions the sweep forks after the scatter pass,
+  // which then runs alone (1.2M-cell float32 step 358 us against 363 us with the fork after the
+  // count pass and 411 us with everything on one stream; the 200k-cell mixed one 142, 150 and 185 us);
+  // with the split contractions it forks right after the count pass, so that it is mostly done
+  // before they start.
   const bool fork_after_scatter = !c->sc.on;
   if (fork_after_scatter && (rc = bucket_cells(c, xyz, s, 2))) return rc;
   P3D_HIP(c, hipEventRecord(c->ev_fork, s));
