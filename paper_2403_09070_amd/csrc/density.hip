@@ -420,47 +420,49 @@ __global__ __launch_bounds__(kScanTiles * kScanParts) void k_bucket_scan_cols(in
   }
 }
 
-// Chunk plan of the current buckets, made by workgroup 0 of the scatter pass (every thread
-// takes the tiles [k0, k1) of the tile scan): a tile of more than kChunkEntries entries is heavy;
-// its chunks after the first are numbered after the tiles, in tile order, and it takes the next
-// accumulator slot.  Layout of plan: [0] extra chunks, [1] heavy tiles, [2 + k] slot of tile k
-// (-1 for a tile of one chunk), [2 + ntiles + e] tile of extra chunk e, [2 + ntiles + max_extra
-// + e] its index within the tile.
-__device__ void chunk_plan(const int32_t* __restrict__ totals, int k0, int k1, int ntiles, int max_extra,
-                           int32_t* __restrict__ plan) {
-  __shared__ int wx[kBucketThreads / kWave], wh[kBucketThreads / kWave];
+// A chunk plan of the current buckets, made by one workgroup of the scatter pass (every thread
+// takes the tiles [k0, k1) of the tile scan): a tile of more entries than `most` is heavy; its
+// chunks after the first are numbered after the tiles, in tile order.  Layout of plan: [0] extra
+// chunks, [1] most, [2 + k] first extra chunk of tile k (-1 for a tile of one chunk), [2 + ntiles
+// + e] tile of extra chunk e, [2 + ntiles + max_extra + e] its index within the tile.  most is the
+// split's bound for the entries at hand, which keeps the extra chunks below max_extra: a tile of v
+// entries has floor((v - 1) / most) of them.
+__device__ void chunk_plan(const int32_t* __restrict__ totals, int entries, SplitBound sb, int k0, int k1, int ntiles,
+                           int max_extra, int32_t* __restrict__ plan) {
+  __shared__ int wx[kBucketThreads / kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  int ox = 0, oh = 0;
+  const int most = max(sb.min, (entries + sb.count - 1) / sb.count);
+  int ox = 0;
   for (int k = k0; k < k1; ++k) {
     const int v = totals[k];
-    if (v > kChunkEntries) { ox += (v - 1) / kChunkEntries; ++oh; }
+    if (v > most) ox += (v - 1) / most;
   }
-  int ix = ox, ih = oh;                 // inclusive scans within the wavefront
+  int ix = ox;                          // inclusive scan within the wavefront
   for (int o = 1; o < kWave; o <<= 1) {
-    const int ux = __shfl_up(ix, o), uh = __shfl_up(ih, o);
-    if (lane >= o) { ix += ux; ih += uh; }
+    const int ux = __shfl_up(ix, o);
+    if (lane >= o) ix += ux;
   }
-  if (lane == kWave - 1) { wx[wave] = ix; wh[wave] = ih; }
+  if (lane == kWave - 1) wx[wave] = ix;
   __syncthreads();
-  int ex = ix - ox, eh = ih - oh;       // exclusive prefixes of this thread's tiles
-  for (int w = 0; w < wave; ++w) { ex += wx[w]; eh += wh[w]; }
+  int ex = ix - ox;                     // exclusive prefix of this thread's tiles
+  for (int w = 0; w < wave; ++w) ex += wx[w];
   int32_t* extra = plan + 2 + ntiles;
   for (int k = k0; k < k1; ++k) {
     const int v = totals[k];
-    if (v > kChunkEntries) {
-      const int nx = (v - 1) / kChunkEntries;
+    if (v > most) {
+      const int nx = (v - 1) / most;
       for (int j = 0; j < nx; ++j) {
         extra[ex + j] = k;
         extra[max_extra + ex + j] = j + 1;
       }
+      plan[2 + k] = ex;
       ex += nx;
-      plan[2 + k] = eh++;
     } else {
       plan[2 + k] = -1;
     }
   }
-  // the last thread's tile range ends at the last tile: its running counts are the totals
-  if (threadIdx.x == blockDim.x - 1) { plan[0] = ex; plan[1] = eh; }
+  // the last thread's tile range ends at the last tile: its running count is the total
+  if (threadIdx.x == blockDim.x - 1) { plan[0] = ex; plan[1] = most; }
 }
 
 __global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Geom g, TileGeom t, const float* __restrict__ xyz,
@@ -469,12 +471,14 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Geom g, TileG
                                                         const int32_t* __restrict__ totals,
                                                         int32_t* __restrict__ tile_start,
                                                         float4* __restrict__ entries, int32_t* __restrict__ cell_entry,
-                                                        int max_extra, int32_t* __restrict__ plan) {
+                                                        int max_extra_d, int32_t* __restrict__ plan_d,
+                                                        int max_extra_g, int32_t* __restrict__ plan_g) {
   // every workgroup scans the tile totals itself (exclusive prefix = tile_start) and workgroup 0
   // stores the result for the later passes; the cursor of tile k starts at tile_start[k] plus
   // this workgroup's offset within the tile
   extern __shared__ int cursor[];
   __shared__ int wsum[kBucketThreads / kWave];
+  __shared__ int total;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int per = (t.ntiles + blockDim.x - 1) / blockDim.x;
   const int k0 = min((int)threadIdx.x * per, t.ntiles), k1 = min(k0 + per, t.ntiles);
@@ -506,8 +510,14 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Geom g, TileG
     run += v;
   }
   if (blockIdx.x == 0 && k0 < k1 && k1 == t.ntiles) tile_start[t.ntiles] = run;
+  if (threadIdx.x == blockDim.x - 1) total = run;     // its tile range ends at the last tile
   __syncthreads();
-  if (blockIdx.x == 0) chunk_plan(totals, k0, k1, t.ntiles, max_extra, plan);
+  // the two chunk plans, by workgroups 0 and 1 where there are two
+  if (blockIdx.x == 0) chunk_plan(totals, total, kSplit[kSplitDensity], k0, k1, t.ntiles, max_extra_d, plan_d);
+  if (blockIdx.x == min(1u, gridDim.x - 1)) {
+    __syncthreads();            // a single workgroup makes both: the wavefront sums are free again
+    chunk_plan(totals, total, kSplit[kSplitGather], k0, k1, t.ntiles, max_extra_g, plan_g);
+  }
   const int n = g.n;
   const int base = blockIdx.x * t.cpb;
   for (int c0 = threadIdx.x; c0 < t.cpb; c0 += kCellsPerThread * blockDim.x) {
@@ -655,16 +665,17 @@ struct Chunks {
                                             // its layout is in the accessors below)
   int ntiles, max_extra;
   __device__ __forceinline__ int n_extra() const { return plan[0]; }
-  __device__ __forceinline__ int slot(int tile) const { return plan[2 + tile]; }
+  __device__ __forceinline__ int most() const { return plan[1]; }
+  __device__ __forceinline__ int first_extra(int tile) const { return plan[2 + tile]; }
   __device__ __forceinline__ int extra_tile(int e) const { return plan[2 + ntiles + e]; }
   __device__ __forceinline__ int extra_index(int e) const { return plan[2 + ntiles + max_extra + e]; }
-  __device__ __forceinline__ int32_t* done(int slot) const { return plan + 2 + ntiles + 2 * max_extra + slot; }
+  __device__ __forceinline__ int32_t* done(int e) const { return plan + 2 + ntiles + 2 * max_extra + e; }
+  __device__ __forceinline__ int32_t* groups_done(int e) const { return done(e) + max_extra; }
 };
 
 struct ChunkRef {
   int tile, first, last;    // entries [first, last) of the chunk
-  int nchunks;              // chunks of its tile
-  bool chunk0;
+  int nchunks, kc;          // chunks of its tile, index of this one
 };
 
 // (q is the same in every lane: the values are moved to scalar registers, which the compiler
@@ -680,10 +691,17 @@ __device__ __forceinline__ ChunkRef chunk_ref(const Chunks& ch, const TileGeom& 
   }
   const int ts = __builtin_amdgcn_readfirstlane(ch.tile_start[ck.tile]);
   const int te = __builtin_amdgcn_readfirstlane(ch.tile_start[ck.tile + 1]);
-  ck.nchunks = te - ts > kChunkEntries ? (te - ts - 1) / kChunkEntries + 1 : 1;
-  ck.chunk0 = kc == 0;
-  ck.first = ts + kc * kChunkEntries;
-  ck.last = min(ck.first + kChunkEntries, te);
+  ck.nchunks = 1;
+  ck.kc = kc;
+  ck.first = ts;
+  ck.last = te;
+  const int v = te - ts, most = __builtin_amdgcn_readfirstlane(ch.most());
+  if (v > most) {           // equal chunks, none above most
+    ck.nchunks = (v - 1) / most + 1;
+    const int per = (v + ck.nchunks - 1) / ck.nchunks;
+    ck.first = min(ts + kc * per, te);
+    ck.last = min(ck.first + per, te);
+  }
   return ck;
 }
 
@@ -726,15 +744,19 @@ __device__ __forceinline__ void write_tile(const Geom& g, const TileGeom& t, con
   block_partials<2>(ex, part, stride, R_EXCESS_BOT, tile);
 }
 
-// A chunk accumulates in LDS: its tile's fixed map and large-instance sweep with the first chunk,
-// then its entries.  A tile of one chunk is written from LDS.  The chunks of a heavy tile add
-// their LDS sums into the tile's accumulator slot (64-bit integer atomics, so the sum does not
-// depend on their order) and count themselves done; the last one reads the slot back, clearing
-// it, and writes the tile.
+// A chunk accumulates in LDS: its tile's fixed map with the first chunk, its share of the large
+// instances, its entries.  A tile of one chunk is written from LDS.  The chunks of a heavy tile
+// store their LDS sums (chunk 0 after all extra chunks, by the tile's first extra chunk) and count
+// themselves done in their group of kChunkGroup; the last of a group adds the group's sums, and
+// the last group of a tile the groups' sums, and writes the tile.  The sums are integers, so they
+// depend neither on the split nor on the order.  (Global atomics into one accumulator per tile
+// took 45 us per million adds; one level of sums 200 us where 1.2M cells share four tiles; a fence
+// by every thread of the workgroup, each of which writes the whole cache back, 45 us more where
+// 64 tiles have three chunks each.)
 // (eight wavefronts per SIMD: the scalar registers its heavy-tile path needs would otherwise cost
 // one; the excess goes to vector-register lanes)
 __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_density_tiles(Geom g, TileGeom t, const float4* __restrict__ entries,
-                                                       Chunks ch, unsigned long long* __restrict__ heavy_acc,
+                                                       Chunks ch, unsigned long long* __restrict__ sums,
                                                        const float* __restrict__ fixed_map,
                                                        const float4* __restrict__ lrec, int nlarge, float target,
                                                        int fillers, float* __restrict__ rho,
@@ -758,16 +780,18 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
     for (int k = threadIdx.x; k < tsz; k += blockDim.x) {
       const int lx = k & (t.T - 1), ly = (k >> t.lgT) & (t.T - 1), bz = k >> (2 * t.lgT);
       // fixed_map is null when the problem has no fixed instances (the map is then all zero)
-      S64[k] = (ck.chunk0 && fixed_map && lx < tb.wx && ly < tb.wy)
+      S64[k] = (ck.kc == 0 && fixed_map && lx < tb.wx && ly < tb.wy)
                    ? to_fix(fixed_map[bin_index(g, bz, tb.y0 + ly, tb.x0 + lx)])
                    : 0ull;
       if (fillers) SF[k] = 0ull;
     }
     __syncthreads();
-    // large instances: bin-parallel sweep of their part of this tile (first chunk)
-    for (int chunk = 0; ck.chunk0 && chunk < nlarge; chunk += blockDim.x) {
+    // large instances: bin-parallel sweep of their part of this tile, the tile's chunks sharing
+    // the instances (150 of them meet in four tiles at the start of a placement: swept by the
+    // first chunk alone they took 120 us of the gather's 169)
+    for (int chunk = 0; chunk < nlarge; chunk += blockDim.x) {
       const int nh = large_hits(lrec, nlarge, chunk, tb.x0, tb.x0 + tb.wx - 1, tb.y0, tb.y0 + tb.wy - 1, hits, wave_cnt);
-      for (int h_ = 0; h_ < nh; ++h_) {
+      for (int h_ = ck.kc; h_ < nh; h_ += ck.nchunks) {
         const Foot h = foot_record(g, lrec, hits[h_]);
         const int bx0 = max(h.bx0, tb.x0), bx1 = min(h.bx1, tb.x0 + tb.wx - 1);
         const int by0 = max(h.by0, tb.y0), by1 = min(h.by1, tb.y0 + tb.wy - 1);
@@ -833,30 +857,52 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
                  },
                  rho, part, stride);
     } else {
-      const int slot = ch.slot(ck.tile);
-      unsigned long long* acc = heavy_acc + (size_t)slot * 2 * tsz;
-      for (int k = threadIdx.x; k < tsz; k += blockDim.x) {
-        const unsigned long long a = S64[k];
-        if (a) atomicAdd(acc + k, a);
-        if (fillers) {
-          const unsigned long long b = SF[k];
-          if (b) atomicAdd(acc + tsz + k, b);
+      const int e0 = __builtin_amdgcn_readfirstlane(ch.first_extra(ck.tile));
+      const int used = fillers ? 2 * tsz : tsz;     // SF follows S64
+      auto sums_of = [&](int q) { return sums + (size_t)(q == 0 ? ch.max_extra + e0 : e0 + q - 1) * 2 * tsz; };
+      // stores the LDS sums as those of chunk q (past the cache, so that the fence finds little to
+      // write back) and counts them: true for the last of `of` workgroups to do so, which then sees
+      // the others' sums.  One thread fences for the workgroup.
+      auto hand_in = [&](int q, int32_t* count, int of) {
+        unsigned long long* to = sums_of(q);
+        for (int k = threadIdx.x; k < used; k += blockDim.x)
+          __hip_atomic_store(to + k, S64[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+          __threadfence();
+          last_chunk = atomicAdd(count, 1) == of - 1;
+          if (last_chunk) {
+            atomicExch(count, 0);     // zero again for the next call
+            __threadfence();
+          }
         }
+        __syncthreads();
+        return last_chunk != 0;
+      };
+      // the LDS sums become the sum over chunks q0, q0 + step, ... below q1
+      auto add_up = [&](int q0, int q1, int step) {
+        for (int k = threadIdx.x; k < used; k += blockDim.x) {
+          unsigned long long v = 0ull;
+#pragma unroll 4
+          for (int q = q0; q < q1; q += step) v += sums_of(q)[k];
+          S64[k] = v;
+        }
+        __syncthreads();
+      };
+      const int group = ck.kc / kChunkGroup, q0 = group * kChunkGroup, q1 = min(q0 + kChunkGroup, ck.nchunks);
+      const int ngroups = (ck.nchunks - 1) / kChunkGroup + 1;
+      if (!hand_in(ck.kc, ch.done(e0 + group), q1 - q0)) return;
+      add_up(q0, q1, 1);
+      if (ngroups > 1) {
+        if (!hand_in(q0, ch.groups_done(e0), ngroups)) return;
+        add_up(0, ck.nchunks, kChunkGroup);
       }
-      __threadfence();          // this chunk's sums are in place before it counts itself done
-      __syncthreads();
-      if (threadIdx.x == 0) last_chunk = atomicAdd(ch.done(slot), 1) == ck.nchunks - 1;
-      __syncthreads();
-      if (last_chunk) {
-        __threadfence();        // and the other chunks' sums before the last one reads them
-        write_tile(g, t, tb, ck.tile, target, fillers,
-                   [&](int k, unsigned long long& real, unsigned long long& fil) {
-                     real = atomicExch(acc + k, 0ull);
-                     fil = fillers ? atomicExch(acc + tsz + k, 0ull) : 0ull;
-                   },
-                   rho, part, stride);
-        if (threadIdx.x == 0) atomicExch(ch.done(slot), 0);
-      }
+      write_tile(g, t, tb, ck.tile, target, fillers,
+                 [&](int k, unsigned long long& real, unsigned long long& fil) {
+                   real = S64[k];
+                   fil = fillers ? SF[k] : 0ull;
+                 },
+                 rho, part, stride);
     }
   }
 }
@@ -1074,11 +1120,11 @@ __global__ __launch_bounds__(kTileThreads) void k_gather_tiles(Geom g, TileGeom 
       }
       out[oi] = make_float4(f.omega * sx, f.omega * sy, f.omega * sz, 0.f);
     }
-    // large instances' partial sums over the tile (first chunk)
-    if (lpart && ck.chunk0) {
+    // large instances' partial sums over the tile (the tile's chunks share the instances)
+    if (lpart) {
       for (int chunk = 0; chunk < nlarge; chunk += blockDim.x) {
         const int nh = large_hits(lrec, nlarge, chunk, tb.x0, tb.x0 + tb.wx - 1, tb.y0, tb.y0 + tb.wy - 1, hits, wave_cnt);
-        for (int r = 0; r < nh; ++r) {
+        for (int r = ck.kc; r < nh; r += ck.nchunks) {
           const int j = hits[r];
           const Foot h = foot_record(g, lrec, j);
           const int bx0 = max(h.bx0, tb.x0), bx1 = min(h.bx1, tb.x0 + tb.wx - 1);
@@ -1343,11 +1389,11 @@ __global__ __launch_bounds__(kTileThreads) void k_adjoint_tiles(Geom g, TileGeom
       }
       out[oi] = make_float4(r.x, r.y, r.z, 0.f);
     }
-    // large instances' partial sums over the tile (first chunk)
-    if (lpart && ck.chunk0) {
+    // large instances' partial sums over the tile (the tile's chunks share the instances)
+    if (lpart) {
       for (int chunk = 0; chunk < nlarge; chunk += blockDim.x) {
         const int nh = large_hits(lrec, nlarge, chunk, tb.x0, tb.x0 + tb.wx - 1, tb.y0, tb.y0 + tb.wy - 1, hits, wave_cnt);
-        for (int r = 0; r < nh; ++r) {
+        for (int r = ck.kc; r < nh; r += ck.nchunks) {
           const int j = hits[r];
           const Foot h = foot_record(g, lrec, j);
           const int bx0 = max(h.bx0, tb.x0), bx1 = min(h.bx1, tb.x0 + tb.wx - 1);
@@ -1451,7 +1497,9 @@ __global__ void k_cells_combine(int n, const uint8_t* __restrict__ cls, const in
 
 size_t tile_lds(const place3d_ctx* c, int maps) { return sizeof(float) * (size_t)maps * c->tg.T * c->tg.T * c->g.nz; }
 
-Chunks chunks_of(const place3d_ctx* c) { return Chunks{c->bk_tile_start, c->bk_plan, c->tg.ntiles, c->max_extra}; }
+Chunks chunks_of(const place3d_ctx* c, SplitKind k) {
+  return Chunks{c->bk_tile_start, c->bk_plan[k], c->tg.ntiles, c->max_extra[k]};
+}
 
 }  // namespace
 
@@ -1522,8 +1570,9 @@ int bucket_cells(place3d_ctx* c, const float* xyz, hipStream_t s, int part) {
                      t.ntiles, c->bk_counts, c->bk_totals);
   P3D_LAUNCH(c, "k_bucket_scan_cols");
   hipLaunchKernelGGL(k_bucket_scatter, dim3(t.nblk), dim3(kBucketThreads), hist, s, g, t, xyz, p.size, p.kind, c->cls,
-                     c->bk_counts, c->bk_totals, c->bk_tile_start, c->bk_entries, c->cell_entry, c->max_extra,
-                     c->bk_plan);
+                     c->bk_counts, c->bk_totals, c->bk_tile_start, c->bk_entries, c->cell_entry,
+                     c->max_extra[kSplitDensity], c->bk_plan[kSplitDensity], c->max_extra[kSplitGather],
+                     c->bk_plan[kSplitGather]);
   P3D_LAUNCH(c, "k_bucket_scatter");
   return PLACE3D_OK;
 }
@@ -1536,8 +1585,8 @@ int density_tiles(place3d_ctx* c, const float* xyz, float* rho, double* red, hip
     ProfScope prof_(c, PLACE3D_STAGE_DENSITY, s);
     const int fillers = c->n_fillers > 0 ? 1 : 0;
     const bool inst = (p.options & PLACE3D_OPT_MACRO_INSTANCE) != 0;
-    hipLaunchKernelGGL(k_density_tiles, dim3(t.ntiles + c->max_extra), dim3(kTileThreads), (2 + 2 * fillers) * tile_lds(c, 1), s, g,
-                       t, c->bk_entries, chunks_of(c), c->heavy_acc,
+    hipLaunchKernelGGL(k_density_tiles, dim3(t.ntiles + c->max_extra[kSplitDensity]), dim3(kTileThreads), (2 + 2 * fillers) * tile_lds(c, 1), s, g,
+                       t, c->bk_entries, chunks_of(c, kSplitDensity), c->chunk_sums,
                        c->n_fixed > 0 ? c->fixed_map : nullptr, c->large_rec,
                        inst ? 0 : c->n_large, (float)p.target_density, fillers, rho, c->part, c->part_stride);
     P3D_LAUNCH(c, "k_density_tiles");
@@ -1569,8 +1618,8 @@ int gather_bucketed(place3d_ctx* c, const float* xyz, const float* ex, const flo
   if (xfold && !tiled) return set_err(c, PLACE3D_ERR_ARG, "x-folded field maps need the tiled large-instance path");
   // Ex comes from the sine basis (unfold sign -1), Ey and Ez from the cosine basis (+1)
   const FoldX fx{xfold ? 1 : 0, g.nx / 2, -1.f, 1.f, 1.f};
-  hipLaunchKernelGGL(k_gather_tiles, dim3(t.ntiles + c->max_extra), dim3(kTileThreads), tile_lds(c, 3), s, g, t, c->bk_entries,
-                     chunks_of(c), ex, ey, ez, fx, c->entry_out, c->large_rec, c->n_large,
+  hipLaunchKernelGGL(k_gather_tiles, dim3(t.ntiles + c->max_extra[kSplitGather]), dim3(kTileThreads), tile_lds(c, 3), s, g, t, c->bk_entries,
+                     chunks_of(c, kSplitGather), ex, ey, ez, fx, c->entry_out, c->large_rec, c->n_large,
                      tiled && c->n_large > 0 ? c->lpart : nullptr);
   P3D_LAUNCH(c, "k_gather_tiles");
   if (c->n_large > 0 && tiled) {
@@ -1597,8 +1646,8 @@ int adjoint_bucketed(place3d_ctx* c, const float* xyz, const float* gmap, float 
   const place3d_problem& p = c->prob;
   const bool tiled = large_in_tiles(c);
   ProfScope prof_(c, PLACE3D_STAGE_DGRAD, s);
-  hipLaunchKernelGGL(k_adjoint_tiles, dim3(t.ntiles + c->max_extra), dim3(kTileThreads), tile_lds(c, 1), s, g, t, c->bk_entries,
-                     chunks_of(c), gmap, c->entry_out, c->large_rec, c->n_large,
+  hipLaunchKernelGGL(k_adjoint_tiles, dim3(t.ntiles + c->max_extra[kSplitGather]), dim3(kTileThreads), tile_lds(c, 1), s, g, t, c->bk_entries,
+                     chunks_of(c, kSplitGather), gmap, c->entry_out, c->large_rec, c->n_large,
                      tiled && c->n_large > 0 ? c->lpart : nullptr);
   P3D_LAUNCH(c, "k_adjoint_tiles");
   if (c->n_large > 0 && tiled) {

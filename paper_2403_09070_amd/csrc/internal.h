@@ -19,7 +19,19 @@ constexpr int kWaBlock = 256;           // threads per wirelength block
 constexpr int kPinsPerLane = 4;         // net pins a wirelength lane keeps in registers
 constexpr int kNumGroups = 7;           // nets by lane group: 1, 2, 4, ..., 64 lanes
 constexpr int kNumClasses = kNumGroups + 1;   // the groups, then two-pin nets (one lane each)
-constexpr int kChunkEntries = 16384;    // (cell, tile) entries one tile workgroup takes at a time
+constexpr int kChunkGroup = 16;         // chunks of a tile whose density sums one workgroup adds
+
+// Splits of heavy tiles: a tile is split where it holds more (cell, tile) entries than
+// max(min, entries / count), which leaves at most count chunks beside the tiles' first ones.  The
+// gathers' chunks are independent, so that they are split as far as a workgroup's staging of the
+// maps allows (min of 16384, 2048, 1024: adjoint of 320k cells on 64 tiles 62, 34, 23 us; gather of
+// 200k cells on 256 tiles 28.6, 19.8, 16.1; 1.2M cells on four tiles with count of 256, 512, 1024: 72,
+// 51, 46).  The density chunks' sums have to meet, 0.1 us of fence each beside their bytes: 320k
+// cells on 64 tiles 33 us whole, 36 in two, 54 in six chunks; 1.2M cells on four tiles 165 us
+// in 80 chunks, 94 in 256, 102 in 512.
+enum SplitKind { kSplitDensity = 0, kSplitGather = 1, kSplits = 2 };
+struct SplitBound { int min, count; };
+constexpr SplitBound kSplit[kSplits] = {{8192, 256}, {1024, 1024}};
 
 // Reduction slots (float64, device) inside the workspace.
 enum RedSlot {
@@ -142,16 +154,17 @@ struct place3d_ctx {
   int32_t* bk_totals = nullptr;        // [ntiles]
   int32_t* bk_tile_start = nullptr;    // [ntiles + 1]
   float4* bk_entries = nullptr;        // [2 * 4n] (cell, tile) entries
-  // tiles holding more than kChunkEntries entries are split into chunks of that many: chunk 0 is
-  // taken by the tile's own workgroup, the extra chunks by the workgroups that loop past the
-  // tile count; their density sums meet in a fixed-point accumulator per heavy tile
-  int32_t max_extra = 0, max_heavy = 0;   // bounds: 4n / kChunkEntries (+1)
-  // chunk plan, one array (the tile kernels take one pointer): [0] extra chunks and [1] heavy
-  // tiles of the current buckets, then per tile its accumulator slot (-1: one chunk), per extra
-  // chunk its tile and its index within the tile, and per slot the chunks finished (zero
+  // tiles holding more entries than the plan's bound are split into equal chunks: chunk 0 is
+  // taken by the tile's own workgroup, the extra chunks by the workgroups past the tile count;
+  // in the density pass each stores its fixed-point sums, and the last one of a tile adds them
+  int32_t max_extra[p3d::kSplits] = {};  // bounds: 4n / min (+1), at most count
+  // chunk plans, one array each (the tile kernels take one pointer): [0] extra chunks and [1] entries
+  // that a chunk may hold in the current buckets, then per tile its first extra chunk (-1: none),
+  // per extra chunk its tile and its index within the tile, and from a tile's first extra chunk on
+  // the chunks of its groups that are finished and, in a second array, its finished groups (zero
   // between calls)
-  int32_t* bk_plan = nullptr;          // [2 + ntiles + 2 max_extra + max_heavy]
-  unsigned long long* heavy_acc = nullptr;   // [max_heavy][2][T * T * nz] zero between calls
+  int32_t* bk_plan[p3d::kSplits] = {};   // [2 + ntiles + 4 max_extra]
+  unsigned long long* chunk_sums = nullptr;  // [2 max_extra][2][T * T * nz]
   int32_t* cell_entry = nullptr;       // [n] packed tile range of each bucketed cell, -1 if none
   float4* entry_out = nullptr;         // [4][n] per-(cell, tile) gather / adjoint results, cell-major
   // two-stage reductions: part[slot * part_stride + block]
