@@ -5,13 +5,21 @@
 // Work split: a net of degree d is taken by a group of G = 1, 2, 4, ..., 64 lanes, the smallest
 // with d <= kPinsPerLane * G (64 lanes for larger nets, whose lanes then loop); most nets have
 // few pins and are taken by a single lane.  Lane l of a group holds pins l, l + G, ... in
-// registers and the group walks them three times: (A) first and second largest and smallest pin
-// coordinate per die set and axis, z extremes, set sizes; (B) max-shifted exponential sums per
-// set and axis, and over the whole net in z; (C) per pin: its share of the gradient of the
-// chosen branch, its WA z-gradient and the FDA difference.  Group reductions after (A) and (B)
-// are xor butterflies, symmetric, so every lane of a group holds the same net values.  A static
-// schedule built at context creation lays out nets by class, widest groups first, so a workgroup
-// holds groups of one size.
+// registers and the group takes one axis after the other, x, y, z: first and second largest and
+// smallest pin coordinate per die set (in z the extremes of the whole net); max-shifted
+// exponential sums per set; per pin its share of the gradient of the chosen branch and its part
+// of the FDA difference.  Group reductions are xor butterflies, symmetric, so every lane of a
+// group holds the same net values.  A static schedule built at context creation lays out nets by
+// class, widest groups first, so a workgroup holds groups of one size.
+//
+// What bounds it: without index locality memory (600k instances, 2.3M pins, every pin's owner and
+// result in a line of its own: 360 MB in 71 us, 5 TB/s); with it the latency of the loads, three
+// deep (net, owner, coordinates), against the wavefronts that the registers allow.  So all loads of
+// a lane's pins are issued before any is used, and the axes follow one another, one axis's extremes,
+// sums and coefficients live at a time (125 registers, four wavefronts a SIMD, against 155 and three
+// with all axes at once; 1.2M instances, 4.5M pins: 85 us in float32 sums and 93 in compensated ones,
+// against 110 and 119).  Masking a lane's absent pins instead of branching round them makes 17 %
+// fewer instructions but holds 143 registers: no faster.
 //
 // Pin coordinates are taken relative to the x, y of the net's first pin's owner: the rounding of
 // each relative coordinate is then bounded by the net's span, not by the die size, and every
@@ -26,6 +34,7 @@
 // second extreme replaces it when it was the first) and joins the other set at its other-die
 // offset.
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -62,6 +71,14 @@ __device__ __forceinline__ int xchg(int v) {
   return __float_as_int(xchg<M>(__int_as_float(v)));
 }
 
+// base[i] by a 32-bit byte offset, which the load adds to the base by itself: instances, pins and
+// nets number at most 2^28, so that even a 16-byte element's offset fits
+template <class T>
+__device__ __forceinline__ T& at(T* base, int i) {
+  using Byte = std::conditional_t<std::is_const_v<T>, const char, char>;
+  return *reinterpret_cast<T*>(reinterpret_cast<Byte*>(base) + (uint32_t)i * (uint32_t)sizeof(T));
+}
+
 struct PinRel {        // one pin, relative to the net anchor
   float ux, uy;        // on its owner's current die
   float fx, fy;        // on the other die
@@ -69,10 +86,7 @@ struct PinRel {        // one pin, relative to the net anchor
   bool top;
 };
 
-__device__ __forceinline__ PinRel load_pin(const float4* __restrict__ xyzp, const int32_t* __restrict__ pin_node,
-                                           const float4* __restrict__ off, int slot, float half_dz, float xa, float ya) {
-  const float4 q = xyzp[pin_node[slot]];
-  const float4 o = off[slot];
+__device__ __forceinline__ PinRel pin_rel(const float4& q, const float4& o, float half_dz, float xa, float ya) {
   const float dx = q.x - xa, dy = q.y - ya;
   PinRel p;
   p.z = q.z;
@@ -82,6 +96,10 @@ __device__ __forceinline__ PinRel load_pin(const float4* __restrict__ xyzp, cons
   p.fx = dx + (p.top ? o.x : o.z);
   p.fy = dy + (p.top ? o.y : o.w);
   return p;
+}
+__device__ __forceinline__ PinRel load_pin(const float4* __restrict__ xyzp, const int32_t* __restrict__ pin_node,
+                                           const float4* __restrict__ off, int slot, float half_dz, float xa, float ya) {
+  return pin_rel(at(xyzp, at(pin_node, slot)), at(off, slot), half_dz, xa, ya);
 }
 
 // first and second largest and smallest of a multiset (duplicates kept)
@@ -99,27 +117,13 @@ __device__ __forceinline__ Ext2 ext_sel(bool c, const Ext2& a, const Ext2& b) {
   return {c ? a.max1 : b.max1, c ? a.max2 : b.max2, c ? a.min1 : b.min1, c ? a.min2 : b.min2};
 }
 
-struct NetExt {
-  Ext2 tx, ty, bx, by;        // top / bottom set, x / y
-  float zmax, zmin;
-  int ct, cb;
-};
-
-// every set is updated with values or sentinels (no branch on the die): a branch would let
-// the compiler select between the sets' addresses and move them to scratch memory
-__device__ __forceinline__ void ext_add(NetExt& a, const PinRel& p) {
-  const float tx_hi = p.top ? p.ux : kNegInf, tx_lo = p.top ? p.ux : kPosInf;
-  const float bx_hi = p.top ? kNegInf : p.ux, bx_lo = p.top ? kPosInf : p.ux;
-  const float ty_hi = p.top ? p.uy : kNegInf, ty_lo = p.top ? p.uy : kPosInf;
-  const float by_hi = p.top ? kNegInf : p.uy, by_lo = p.top ? kPosInf : p.uy;
-  ext_put(a.tx, tx_hi, tx_lo);
-  ext_put(a.bx, bx_hi, bx_lo);
-  ext_put(a.ty, ty_hi, ty_lo);
-  ext_put(a.by, by_hi, by_lo);
-  a.ct += p.top ? 1 : 0;
-  a.cb += p.top ? 0 : 1;
-  a.zmax = fmaxf(a.zmax, p.z);
-  a.zmin = fminf(a.zmin, p.z);
+// vmax / vmin of a pin in one of a net's two sets: every set is updated with values or sentinels
+// (no branch on the die): a branch would let the compiler select between the sets' addresses and
+// move them to scratch memory
+struct SetExt { Ext2 t, b; };          // top / bottom set along one axis
+__device__ __forceinline__ void ext_add(SetExt& a, bool top, float u) {
+  ext_put(a.t, top ? u : kNegInf, top ? u : kPosInf);
+  ext_put(a.b, top ? kNegInf : u, top ? kPosInf : u);
 }
 
 template <int M>
@@ -220,8 +224,8 @@ __device__ __forceinline__ void sums_axis(AxisSums<C>& S, bool top, float u, flo
   sums_add(S.b, !top, du, dl, ep, em);
 }
 template <bool C>
-__device__ __forceinline__ void sums_z(Sums4<C>& S, const NetExt& a, const PinRel& p, float ig) {
-  const float duz = p.z - a.zmax, dlz = p.z - a.zmin;
+__device__ __forceinline__ void sums_z(Sums4<C>& S, float zmax, float zmin, float z, float ig) {
+  const float duz = z - zmax, dlz = z - zmin;
   sums_add(S, true, duz, dlz, __expf(duz * ig), __expf(-dlz * ig));
 }
 
@@ -302,35 +306,30 @@ __device__ __forceinline__ float w_flip(Ext2 S, int cs, Ext2 O, int co, float u,
   return w_exact(smax, smin, cs - 1, fmaxf(O.max1, f), fminf(O.min1, f), co + 1);
 }
 
-struct NetCoef {
-  AxisCoef x, y;
-  float zmax, zmin, az_p, Az_p, az_m, Az_m;
-  float Wx, Wy;
-};
+struct ZCoef { float zmax, zmin, az_p, Az_p, az_m, Az_m; };
 
-// per pin: (dW^/dx, dW^/dy, alpha dW^z/dz, FDA difference)
-__device__ __forceinline__ float4 pin_result(const PinRel& p, const NetExt& a, const NetCoef& c, float ig, float alpha,
-                                             float four_over_dz) {
-  const float gx = axis_grad(c.x, p.top, p.ux, ig);
-  const float gy = axis_grad(c.y, p.top, p.uy, ig);
-  const float duz = p.z - c.zmax, dlz = p.z - c.zmin;
-  const float gz = alpha * (__expf(duz * ig) * c.az_p * (1.f + (duz - c.Az_p) * ig) -
-                            __expf(-dlz * ig) * c.az_m * (1.f - (dlz - c.Az_m) * ig));
-  const int cs = p.top ? a.ct : a.cb, co = p.top ? a.cb : a.ct;
-  const float wfx = w_flip(ext_sel(p.top, a.tx, a.bx), cs, ext_sel(p.top, a.bx, a.tx), co, p.ux, p.fx);
-  const float wfy = w_flip(ext_sel(p.top, a.ty, a.by), cs, ext_sel(p.top, a.by, a.ty), co, p.uy, p.fy);
-  // (4/d_z) (W with the owner on top - W with it on the bottom)
-  const float dw = (wfx - c.Wx) + (wfy - c.Wy);
-  return make_float4(gx, gy, gz, four_over_dz * (p.top ? -dw : dw));
+// alpha dW^z/dz of a pin
+__device__ __forceinline__ float z_grad(const ZCoef& c, float z, float ig, float alpha) {
+  const float duz = z - c.zmax, dlz = z - c.zmin;
+  return alpha * (__expf(duz * ig) * c.az_p * (1.f + (duz - c.Az_p) * ig) -
+                  __expf(-dlz * ig) * c.az_m * (1.f - (dlz - c.Az_m) * ig));
 }
 
 template <int M>
-__device__ __forceinline__ void merge_step(NetExt& a) {
-  ext_merge<M>(a.tx); ext_merge<M>(a.bx); ext_merge<M>(a.ty); ext_merge<M>(a.by);
-  a.zmax = fmaxf(a.zmax, xchg<M>(a.zmax));
-  a.zmin = fminf(a.zmin, xchg<M>(a.zmin));
-  a.ct += xchg<M>(a.ct);
-  a.cb += xchg<M>(a.cb);
+__device__ __forceinline__ void merge_step(SetExt& a) {
+  ext_merge<M>(a.t); ext_merge<M>(a.b);
+}
+struct Counts { int t, b; };           // pins of the top / bottom set
+template <int M>
+__device__ __forceinline__ void merge_step(Counts& a) {
+  a.t += xchg<M>(a.t);
+  a.b += xchg<M>(a.b);
+}
+struct Range { float max, min; };
+template <int M>
+__device__ __forceinline__ void merge_step(Range& a) {
+  a.max = fmaxf(a.max, xchg<M>(a.max));
+  a.min = fminf(a.min, xchg<M>(a.min));
 }
 template <int M, bool C>
 __device__ __forceinline__ void merge_step(AxisSums<C>& S) {
@@ -388,97 +387,160 @@ __device__ __forceinline__ double wave_sum(float v) {
   }
 }
 
+// What one planar axis of a net gives besides its pins' gradients: smoothed and exact bistratal
+// extent, whole-net extent.
+struct AxisOut { float W, We, span; };
+
+// One planar axis of a net: u[j] the lane's pins on their own die, replaced by their gradients;
+// f[j] on the other die, replaced by the exact extent with the pin moved there less the extent as
+// it is.  tail(fn) calls fn(k, u, f, top) for the lane's pins past the registers, put(k, g, dw)
+// takes their results.
+template <int G, bool kGrad, bool C, class Tail, class Put>
+__device__ __forceinline__ AxisOut wl_axis(int d, int lg, float (&u)[kPinsPerLane], float (&f)[kPinsPerLane],
+                                           const bool (&top)[kPinsPerLane], Counts n, float ig, float big, Tail tail,
+                                           Put put) {
+  SetExt e = {ext_empty(), ext_empty()};
+#pragma unroll
+  for (int j = 0; j < kPinsPerLane; ++j)
+    if (lg + G * j < d) ext_add(e, top[j], u[j]);
+  tail([&](int, float tu, float, bool tt) { ext_add(e, tt, tu); });
+  group_merge<G>(e);
+  AxisSums<C> S = {sums_start<C>(big), sums_start<C>(big)};
+#pragma unroll
+  for (int j = 0; j < kPinsPerLane; ++j)
+    if (lg + G * j < d) sums_axis(S, top[j], u[j], top[j] ? e.t.max1 : e.b.max1, top[j] ? e.t.min1 : e.b.min1, ig);
+  tail([&](int, float tu, float, bool tt) {
+    sums_axis(S, tt, tu, tt ? e.t.max1 : e.b.max1, tt ? e.t.min1 : e.b.min1, ig);
+  });
+  sums_settle(S.t, big); sums_settle(S.b, big);
+  group_merge<G>(S);
+  const AxisCoef c = axis_coef(e.t, val(S.t), n.t, e.b, val(S.b), n.b, ig);
+  const float We = w_exact(e.t.max1, e.t.min1, n.t, e.b.max1, e.b.min1, n.b);
+  if constexpr (kGrad) {
+    auto flip = [&](bool tt, float tu, float tf) {
+      return w_flip(ext_sel(tt, e.t, e.b), tt ? n.t : n.b, ext_sel(tt, e.b, e.t), tt ? n.b : n.t, tu, tf) - We;
+    };
+#pragma unroll
+    for (int j = 0; j < kPinsPerLane; ++j)
+      if (lg + G * j < d) {
+        f[j] = flip(top[j], u[j], f[j]);
+        u[j] = axis_grad(c, top[j], u[j], ig);
+      }
+    tail([&](int k, float tu, float tf, bool tt) { put(k, axis_grad(c, tt, tu, ig), flip(tt, tu, tf)); });
+  }
+  return {c.W, We, fmaxf(e.t.max1, e.b.max1) - fminf(e.t.min1, e.b.min1)};
+}
+
 // one net per group of G lanes; lane lg of the group holds pins lg + G j.  kGrad: also write the
-// per-pin results (phase C); else only the net totals.  C: compensated exponential sums.
+// per-pin results (dW^/dx, dW^/dy, alpha dW^z/dz, FDA difference) at the pin's node-ordered
+// position; else only the net totals.  C: compensated exponential sums.
 template <int G, bool kGrad, bool C>
 __device__ __forceinline__ NetTotals wl_group(int net, int lg, float half_dz, float four_over_dz, float ig, float big,
                                               float alpha, const float4* __restrict__ xyzp,
                                               const int32_t* __restrict__ s_net_start,
                                               const int32_t* __restrict__ pin_node, const float4* __restrict__ off,
                                               const int32_t* __restrict__ slot_pos, float4* __restrict__ pin_out) {
-  const int s = s_net_start[net], d = s_net_start[net + 1] - s;
-  const float4 q0 = xyzp[pin_node[s]];
-  const float xa = q0.x, ya = q0.y;
-  PinRel pc[kPinsPerLane];
-
-  // ---- phase A: extremes
-  NetExt a = {ext_empty(), ext_empty(), ext_empty(), ext_empty(), kNegInf, kPosInf, 0, 0};
+  const int s = at(s_net_start, net), d = at(s_net_start, net + 1) - s;
+  float ux[kPinsPerLane], uy[kPinsPerLane], fx[kPinsPerLane], fy[kPinsPerLane], z[kPinsPerLane], xa, ya;
+  bool top[kPinsPerLane];
+  int pos[kPinsPerLane];
+  Counts n = {0, 0};
+  Range rz = {kNegInf, kPosInf};
+  {
+    // all loads of the lane's pins before any use; a lane's absent pins repeat the net's last one
+    int node[kPinsPerLane];
+    float4 o[kPinsPerLane], q[kPinsPerLane];
+#pragma unroll
+    for (int j = 0; j < kPinsPerLane; ++j) {
+      const int k = s + min(lg + G * j, d - 1);
+      node[j] = at(pin_node, k);
+      o[j] = at(off, k);
+      if constexpr (kGrad) pos[j] = at(slot_pos, k);
+    }
+    int node0 = node[0];
+    if constexpr (G > 1) node0 = at(pin_node, s);
+#pragma unroll
+    for (int j = 0; j < kPinsPerLane; ++j) q[j] = at(xyzp, node[j]);
+    float4 q0 = q[0];
+    if constexpr (G > 1) q0 = at(xyzp, node0);
+    xa = q0.x;
+    ya = q0.y;
+#pragma unroll
+    for (int j = 0; j < kPinsPerLane; ++j) {
+      const PinRel p = pin_rel(q[j], o[j], half_dz, xa, ya);
+      ux[j] = p.ux; uy[j] = p.uy; fx[j] = p.fx; fy[j] = p.fy; z[j] = p.z; top[j] = p.top;
+      if (lg + G * j < d) {
+        n.t += p.top ? 1 : 0;
+        n.b += p.top ? 0 : 1;
+        rz.max = fmaxf(rz.max, p.z);
+        rz.min = fminf(rz.min, p.z);
+      }
+    }
+  }
+  // pins past the registers (nets of more than 64 kPinsPerLane pins) are read again by each pass
+  auto tail = [&](auto fn) {
+    if constexpr (G == kWave)
+      for (int k = lg + G * kPinsPerLane; k < d; k += G) fn(k, load_pin(xyzp, pin_node, off, s + k, half_dz, xa, ya));
+  };
+  tail([&](int, const PinRel& p) {
+    n.t += p.top ? 1 : 0;
+    n.b += p.top ? 0 : 1;
+    rz.max = fmaxf(rz.max, p.z);
+    rz.min = fminf(rz.min, p.z);
+  });
+  group_merge<G>(n);
+  group_merge<G>(rz);
+  const AxisOut ax = wl_axis<G, kGrad, C>(
+      d, lg, ux, fx, top, n, ig, big,
+      [&](auto fn) { tail([&](int k, const PinRel& p) { fn(k, p.ux, p.fx, p.top); }); },
+      [&](int k, float g, float dw) {
+        float4& r = at(pin_out, at(slot_pos, s + k));
+        r.x = g;
+        r.w = dw;
+      });
+  const AxisOut ay = wl_axis<G, kGrad, C>(
+      d, lg, uy, fy, top, n, ig, big,
+      [&](auto fn) { tail([&](int k, const PinRel& p) { fn(k, p.uy, p.fy, p.top); }); },
+      [&](int k, float g, float dw) {
+        float4& r = at(pin_out, at(slot_pos, s + k));
+        r.y = g;
+        r.w += dw;
+      });
+  Sums4<C> S = sums_start<C>(big);
 #pragma unroll
   for (int j = 0; j < kPinsPerLane; ++j)
-    if (lg + G * j < d) {
-      pc[j] = load_pin(xyzp, pin_node, off, s + lg + G * j, half_dz, xa, ya);
-      ext_add(a, pc[j]);
-    }
-  for (int k = lg + G * kPinsPerLane; k < d; k += G) ext_add(a, load_pin(xyzp, pin_node, off, s + k, half_dz, xa, ya));
-  group_merge<G>(a);
-
-  // ---- phase B: shifted exponential sums, one axis at a time, each reduced to its gradient
-  // coefficients before the next axis starts (one axis's sums live at a time: compensated sums
-  // hold two floats each)
-  NetCoef c;
-  {
-    AxisSums<C> S = {sums_start<C>(big), sums_start<C>(big)};
-#pragma unroll
-    for (int j = 0; j < kPinsPerLane; ++j)
-      if (lg + G * j < d)
-        sums_axis(S, pc[j].top, pc[j].ux, pc[j].top ? a.tx.max1 : a.bx.max1, pc[j].top ? a.tx.min1 : a.bx.min1, ig);
-    for (int k = lg + G * kPinsPerLane; k < d; k += G) {
-      const PinRel p = load_pin(xyzp, pin_node, off, s + k, half_dz, xa, ya);
-      sums_axis(S, p.top, p.ux, p.top ? a.tx.max1 : a.bx.max1, p.top ? a.tx.min1 : a.bx.min1, ig);
-    }
-    sums_settle(S.t, big); sums_settle(S.b, big);
-    group_merge<G>(S);
-    c.x = axis_coef(a.tx, val(S.t), a.ct, a.bx, val(S.b), a.cb, ig);
-  }
-  {
-    AxisSums<C> S = {sums_start<C>(big), sums_start<C>(big)};
-#pragma unroll
-    for (int j = 0; j < kPinsPerLane; ++j)
-      if (lg + G * j < d)
-        sums_axis(S, pc[j].top, pc[j].uy, pc[j].top ? a.ty.max1 : a.by.max1, pc[j].top ? a.ty.min1 : a.by.min1, ig);
-    for (int k = lg + G * kPinsPerLane; k < d; k += G) {
-      const PinRel p = load_pin(xyzp, pin_node, off, s + k, half_dz, xa, ya);
-      sums_axis(S, p.top, p.uy, p.top ? a.ty.max1 : a.by.max1, p.top ? a.ty.min1 : a.by.min1, ig);
-    }
-    sums_settle(S.t, big); sums_settle(S.b, big);
-    group_merge<G>(S);
-    c.y = axis_coef(a.ty, val(S.t), a.ct, a.by, val(S.b), a.cb, ig);
-  }
-  {
-    Sums4<C> S = sums_start<C>(big);
-#pragma unroll
-    for (int j = 0; j < kPinsPerLane; ++j)
-      if (lg + G * j < d) sums_z(S, a, pc[j], ig);
-    for (int k = lg + G * kPinsPerLane; k < d; k += G) sums_z(S, a, load_pin(xyzp, pin_node, off, s + k, half_dz, xa, ya), ig);
-    sums_settle(S, big);
-    group_merge<G>(S);
-    const Sums4v sz = val(S);
-    c.az_p = rcp(sz.sp); c.Az_p = sz.tp * c.az_p;
-    c.az_m = rcp(sz.sm); c.Az_m = sz.tm * c.az_m;
-  }
-  c.zmax = a.zmax; c.zmin = a.zmin;
-  c.Wx = w_exact(a.tx.max1, a.tx.min1, a.ct, a.bx.max1, a.bx.min1, a.cb);
-  c.Wy = w_exact(a.ty.max1, a.ty.min1, a.ct, a.by.max1, a.by.min1, a.cb);
-
-  // ---- phase C: per-pin results, written at the pin's node-ordered position
+    if (lg + G * j < d) sums_z(S, rz.max, rz.min, z[j], ig);
+  tail([&](int, const PinRel& p) { sums_z(S, rz.max, rz.min, p.z, ig); });
+  sums_settle(S, big);
+  group_merge<G>(S);
+  const Sums4v sz = val(S);
+  ZCoef c = {rz.max, rz.min, rcp(sz.sp), 0.f, rcp(sz.sm), 0.f};
+  c.Az_p = sz.tp * c.az_p;
+  c.Az_m = sz.tm * c.az_m;
   if constexpr (kGrad) {
+    // the FDA difference: (4/d_z) (W with the owner on top - W with it on the bottom)
 #pragma unroll
     for (int j = 0; j < kPinsPerLane; ++j)
-      if (lg + G * j < d) pin_out[slot_pos[s + lg + G * j]] = pin_result(pc[j], a, c, ig, alpha, four_over_dz);
-    for (int k = lg + G * kPinsPerLane; k < d; k += G)
-      pin_out[slot_pos[s + k]] =
-          pin_result(load_pin(xyzp, pin_node, off, s + k, half_dz, xa, ya), a, c, ig, alpha, four_over_dz);
+      if (lg + G * j < d) {
+        const float dw = fx[j] + fy[j];
+        at(pin_out, pos[j]) = make_float4(ux[j], uy[j], z_grad(c, z[j], ig, alpha), four_over_dz * (top[j] ? -dw : dw));
+      }
+    tail([&](int k, const PinRel& p) {
+      float4& r = at(pin_out, at(slot_pos, s + k));
+      const float dw = r.w;
+      r.z = z_grad(c, p.z, ig, alpha);
+      r.w = four_over_dz * (p.top ? -dw : dw);
+    });
   }
 
   // ---- net totals, from the group's first lane
   NetTotals t = {0.f, 0.f, 0.f, 0.f, 0.f};
   if (lg == 0) {
-    t.wa_bi = c.x.W + c.y.W;
-    t.wa_z = alpha * ((a.zmax - a.zmin) + (c.Az_p - c.Az_m));
-    t.hpwl = c.Wx + c.Wy;
-    t.hpwl3d = (fmaxf(a.tx.max1, a.bx.max1) - fminf(a.tx.min1, a.bx.min1)) +
-               (fmaxf(a.ty.max1, a.by.max1) - fminf(a.ty.min1, a.by.min1)) + alpha * (a.zmax - a.zmin);
-    t.ncut = (a.ct > 0 && a.cb > 0) ? 1.f : 0.f;
+    t.wa_bi = ax.W + ay.W;
+    t.wa_z = alpha * ((rz.max - rz.min) + (c.Az_p - c.Az_m));
+    t.hpwl = ax.We + ay.We;
+    t.hpwl3d = ax.span + ay.span + alpha * (rz.max - rz.min);
+    t.ncut = (n.t > 0 && n.b > 0) ? 1.f : 0.f;
   }
   return t;
 }
@@ -510,7 +572,7 @@ __device__ __forceinline__ NetTotals wl_pair(int s, float half_dz, float four_ov
                                              const float4* __restrict__ xyzp, const int32_t* __restrict__ pin_node,
                                              const float4* __restrict__ off, const int32_t* __restrict__ slot_pos,
                                              float4* __restrict__ pin_out) {
-  const float4 q0 = xyzp[pin_node[s]];
+  const float4 q0 = at(xyzp, at(pin_node, s));
   const PinRel p = load_pin(xyzp, pin_node, off, s, half_dz, q0.x, q0.y);
   const PinRel q = load_pin(xyzp, pin_node, off, s + 1, half_dz, q0.x, q0.y);
   const float dx = p.ux - q.ux, dy = p.uy - q.uy, dz = p.z - q.z;
@@ -519,8 +581,8 @@ __device__ __forceinline__ NetTotals wl_pair(int s, float half_dz, float four_ov
   if constexpr (kGrad) {
     const float dwp = (fabsf(p.fx - q.ux) - hx) + (fabsf(p.fy - q.uy) - hy);
     const float dwq = (fabsf(q.fx - p.ux) - hx) + (fabsf(q.fy - p.uy) - hy);
-    pin_out[slot_pos[s]] = make_float4(ax.g, ay.g, alpha * az.g, four_over_dz * (p.top ? -dwp : dwp));
-    pin_out[slot_pos[s + 1]] = make_float4(-ax.g, -ay.g, -(alpha * az.g), four_over_dz * (q.top ? -dwq : dwq));
+    at(pin_out, at(slot_pos, s)) = make_float4(ax.g, ay.g, alpha * az.g, four_over_dz * (p.top ? -dwp : dwp));
+    at(pin_out, at(slot_pos, s + 1)) = make_float4(-ax.g, -ay.g, -(alpha * az.g), four_over_dz * (q.top ? -dwq : dwq));
   }
   NetTotals t;
   t.wa_bi = ax.W + ay.W;
