@@ -140,28 +140,34 @@ struct GemmArgs {
   GemmProb p[kMaxProb];
 };
 
-constexpr int BM = 128, BN = 128;
-
-__device__ __forceinline__ bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
 // Output tile of a workgroup.  The launch is one-dimensional over (n tile, m tile, problem x
 // batch), n fastest, and the XCD-aware order gives each die a contiguous run of tiles: the n
 // tiles of one m block (which share its rows of the data operand) then stay on one die's L2.
 struct TileIdx { int n, m, z; };
-template <int BMT = BM>
+template <int BMT, int BNT>
 __device__ __forceinline__ TileIdx tile_of(int M, int N) {
-  const int ntn = (N + BN - 1) / BN, ntm = (M + BMT - 1) / BMT;
+  const int ntn = (N + BNT - 1) / BNT, ntm = (M + BMT - 1) / BMT;
   const int w = xcd_swizzle((int)blockIdx.x, (int)gridDim.x);
   return {w % ntn, (w / ntn) % ntm, w / (ntn * ntm)};
 }
 
-// C[M][N] = A[M][K] . B[K][N] on float32 MFMA (32x32x2): 4 waves, each a 64 x 64 sub-tile.
+// C[M][N] = A[M][K] . B[K][N] on float32 MFMA (32x32x2): 4 waves, each a 32 x 32 sub-tile.
+// What bounds it: on small grids a wavefront's chain of stages and K / 2 matrix instructions, with
+// few workgroups on the chip: then FT = 64, a 32 x 32 sub-tile each and 32 of k a stage; on large
+// ones the matrix cores: FT = 128, 64 x 64 each and 16 of k.  Operands are loaded by dwords, along k
+// for A and along n for B, which is coalesced for every size and alignment (half of 420 is no
+// multiple of 4).  The sums run over k in ascending order, whatever the tile.  Ex, Ey and Ez of a
+// map, the four launches and the passes between them: 75 x 61 x 6 38 us (71 with 128-wide tiles
+// loaded by 16 bytes where aligned), 256 x 256 x 4 48 (94), 420 x 380 x 4 79 (177), 1024 x 1024 x 4
+// 372 (419), 2048 x 2048 x 4 2454 (2566; 98 TFLOP/s).
+template <int FT>
 __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs args) {
-  constexpr int BK = 16, PAD = 4;
-  __shared__ float As[2][BK][BM + PAD];
-  __shared__ float Bs[2][BK][BN + PAD];
+  constexpr int BK = 2048 / FT, NL = FT * BK / 256;   // loads of each operand a thread makes per stage
+  constexpr int W = FT / 64;                          // 32 x 32 outputs a wavefront holds along each side
+  __shared__ float As[2][BK][FT + 1];
+  __shared__ float Bs[2][BK][FT + 1];
   const int M = args.M, N = args.N, K = args.K, lda = args.lda, ldb = args.ldb, ldc = args.ldc, fn = args.fold_n;
-  const TileIdx ti = tile_of(M, N);
+  const TileIdx ti = tile_of<FT, FT>(M, N);
   const int prob = ti.z / args.nbatch, bat = ti.z % args.nbatch;
   const GemmProb P = args.p[prob];
   const float* __restrict__ A = P.A + bat * P.sA;
@@ -170,117 +176,89 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs args) {
   const float fa = args.fold_a ? P.fold : 0.f, fb = args.fold_a ? 0.f : P.fold;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-  const int m0 = ti.m * BM, n0 = ti.n * BN;
-  const bool vec = ((K & 3) == 0) && ((N & 3) == 0) && ((lda & 3) == 0) && ((ldb & 3) == 0) && ((fn & 3) == 0) &&
-                   al16(A) && al16(B);
+  const int m0 = ti.m * FT, n0 = ti.n * FT;
 
-  // staged operands; wa / wb hold the scaled mirrored values of a fold (zero otherwise)
-  float ra[8], rb[8], wa[8], wb[8];
+  // a thread's elements of a stage: A row ar + RA q at k ak, B row bk + RB q at column bn; rows and
+  // columns past the edge repeat the last one (their outputs are not stored)
+  constexpr int RA = 256 / BK, RB = 256 / FT;
+  const int ak = tid & (BK - 1), ar = tid / BK, bn = tid & (FT - 1), bk = tid / FT;
+  const float* arow[NL];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) wa[e] = wb[e] = 0.f;
+  for (int q = 0; q < NL; ++q) arow[q] = A + (size_t)min(m0 + ar + RA * q, M - 1) * lda;
+  const float* bcol = B + min(n0 + bn, N - 1);
+  float ra[NL], rb[NL], wa[NL], wb[NL];         // wa / wb: the mirrored values of a fold
+#pragma unroll
+  for (int q = 0; q < NL; ++q) wa[q] = wb[q] = 0.f;
   auto load = [&](int k0) {
+    const int k = min(k0 + ak, K - 1);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int f = tid + 256 * q;
-      const int ar = f >> 2, ak = (f & 3) * 4;          // A: 128 rows x 4 float4
-      const int gm = m0 + ar, gk = k0 + ak;
-      if (vec && gm < M && gk + 3 < K) {
-        const float4 v = *reinterpret_cast<const float4*>(A + (size_t)gm * lda + gk);
-        ra[4 * q] = v.x; ra[4 * q + 1] = v.y; ra[4 * q + 2] = v.z; ra[4 * q + 3] = v.w;
-        if (fa != 0.f) {   // mirrored group, added when the stage is stored
-          const float4 w = *reinterpret_cast<const float4*>(A + (size_t)gm * lda + fn - 4 - gk);
-          wa[4 * q] = fa * w.w; wa[4 * q + 1] = fa * w.z; wa[4 * q + 2] = fa * w.y; wa[4 * q + 3] = fa * w.x;
-        }
-      } else {
+    for (int q = 0; q < NL; ++q) ra[q] = arow[q][k];
+    if (fa != 0.f) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float v = 0.f, w = 0.f;
-          if (gm < M && gk + e < K) {
-            v = A[(size_t)gm * lda + gk + e];
-            if (fa != 0.f) w = fa * A[(size_t)gm * lda + fn - 1 - gk - e];
-          }
-          ra[4 * q + e] = v;
-          wa[4 * q + e] = w;
-        }
-      }
-      const int br = f >> 5, bn = (f & 31) * 4;         // B: 16 rows x 32 float4
-      const int gkb = k0 + br, gn = n0 + bn;
-      if (vec && gkb < K && gn + 3 < N) {
-        const float4 v = *reinterpret_cast<const float4*>(B + (size_t)gkb * ldb + gn);
-        rb[4 * q] = v.x; rb[4 * q + 1] = v.y; rb[4 * q + 2] = v.z; rb[4 * q + 3] = v.w;
-        if (fb != 0.f) {
-          const float4 w = *reinterpret_cast<const float4*>(B + (size_t)(fn - 1 - gkb) * ldb + gn);
-          wb[4 * q] = fb * w.x; wb[4 * q + 1] = fb * w.y; wb[4 * q + 2] = fb * w.z; wb[4 * q + 3] = fb * w.w;
-        }
-      } else {
+      for (int q = 0; q < NL; ++q) wa[q] = arow[q][fn - 1 - k];
+    }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float v = 0.f, w = 0.f;
-          if (gkb < K && gn + e < N) {
-            v = B[(size_t)gkb * ldb + gn + e];
-            if (fb != 0.f) w = fb * B[(size_t)(fn - 1 - gkb) * ldb + gn + e];
-          }
-          rb[4 * q + e] = v;
-          wb[4 * q + e] = w;
-        }
-      }
+    for (int q = 0; q < NL; ++q) rb[q] = bcol[(size_t)min(k0 + bk + RB * q, K - 1) * ldb];
+    if (fb != 0.f) {
+#pragma unroll
+      for (int q = 0; q < NL; ++q) wb[q] = bcol[(size_t)(fn - 1 - min(k0 + bk + RB * q, K - 1)) * ldb];
     }
   };
-  auto store = [&](int buf) {
+  // a stage past the end of k holds zeros
+  auto store = [&](int buf, int k0) {
+    const bool ain = k0 + ak < K;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int f = tid + 256 * q;
-      const int ar = f >> 2, ak = (f & 3) * 4;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) As[buf][ak + e][ar] = ra[4 * q + e] + wa[4 * q + e];
-      const int br = f >> 5, bn = (f & 31) * 4;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) Bs[buf][br][bn + e] = rb[4 * q + e] + wb[4 * q + e];
+    for (int q = 0; q < NL; ++q) {
+      As[buf][ak][ar + RA * q] = ain ? ra[q] + fa * wa[q] : 0.f;
+      Bs[buf][bk + RB * q][bn] = k0 + bk + RB * q < K ? rb[q] + fb * wb[q] : 0.f;
     }
   };
 
-  f32x16 acc[2][2];
+  f32x16 acc[W][W];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < W; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < W; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-
-  const int KT = (K + BK - 1) / BK;
   load(0);
-  store(0);
+  store(0, 0);
   __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < KT) load((kt + 1) * BK);
+  for (int k0 = 0, cur = 0; k0 < K; k0 += BK, cur ^= 1) {
+    if (k0 + BK < K) load(k0 + BK);
+    const float* as = &As[cur][lane >> 5][wm * 32 * W + (lane & 31)];
+    const float* bs = &Bs[cur][lane >> 5][wn * 32 * W + (lane & 31)];
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      const int kr = kk + (lane >> 5);
-      const float a0 = As[cur][kr][wm * 64 + (lane & 31)];
-      const float a1 = As[cur][kr][wm * 64 + 32 + (lane & 31)];
-      const float b0 = Bs[cur][kr][wn * 64 + (lane & 31)];
-      const float b1 = Bs[cur][kr][wn * 64 + 32 + (lane & 31)];
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-    }
-    if (kt + 1 < KT) store(cur ^ 1);
+    for (int kk = 0; kk < BK; kk += 2)
+#pragma unroll
+      for (int a = 0; a < W; ++a)
+#pragma unroll
+        for (int b = 0; b < W; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(as[kk * (FT + 1) + 32 * a], bs[kk * (FT + 1) + 32 * b],
+                                                           acc[a][b], 0, 0, 0);
+    if (k0 + BK < K) store(cur ^ 1, k0 + BK);
     __syncthreads();
   }
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < W; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int col = n0 + wn * 64 + b * 32 + (lane & 31);
+    for (int b = 0; b < W; ++b) {
+      const int col = n0 + (wn * W + b) * 32 + (lane & 31);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm * 64 + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const int row = m0 + (wm * W + a) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
         if (row < M && col < N) C[(size_t)row * ldc + col] = acc[a][b][r];
       }
     }
 }
+
+// Wide tiles of the float32 contraction from two per compute unit on: below, the narrow ones fill
+// the chip better (512 x 512 x 4: 88 us against 142), from there on they wait for their operands
+// (2048 x 2048 x 4: 2803 us against 2454; even at 700 to 1400).
+constexpr long long kF32Wide = 512;
+constexpr int BM = 128, BN = 128;      // largest output tile of the split contraction
+
+__device__ __forceinline__ bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 __device__ __forceinline__ unsigned short bf16_rne(float x) {
   unsigned u = __float_as_uint(x);
@@ -325,7 +303,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16x3(GemmSplitArgs args) {
   __shared__ unsigned short Bh[2][BN][LDK], Bl[2][BN][LDK];
   auto sw = [](int r, int unit) { return 8 * (unit ^ ((r >> 1) & 3)); };
   const int M = args.M, N = args.N, K = args.K, ldd = args.ldd, ldb = args.ldb, ldc = args.ldc, fn = args.fold_n;
-  const TileIdx ti = tile_of<BMT>(M, N);
+  const TileIdx ti = tile_of<BMT, BN>(M, N);
   const int prob = ti.z / args.nbatch, bat = ti.z % args.nbatch;
   const GemmSplitProb P = args.p[prob];
   const float* __restrict__ D = P.data + bat * P.s_data;
@@ -713,15 +691,15 @@ int gemm(place3d_ctx* c, int M, int N, int K, int nbatch, bool left_basis, int l
          int fold_n, long long s_data, long long s_out, const GemmJob* jobs, int njobs, hipStream_t s) {
   if (njobs <= 0) return PLACE3D_OK;
   if (njobs > kMaxProb) return set_err(c, PLACE3D_ERR_ARG, "too many contractions in one launch");
-  const long long tiles = (long long)((N + BN - 1) / BN) * ((M + BM - 1) / BM) * nbatch * njobs;
-  if (tiles > 0x7fffffffLL) return set_err(c, PLACE3D_ERR_SIZE, "contraction grid too large");
-  const dim3 grid((unsigned)tiles);
+  auto tiles_of = [&](int bm, int bn) {
+    return (long long)((N + bn - 1) / bn) * ((M + bm - 1) / bm) * nbatch * njobs;
+  };
+  if (tiles_of(64, 64) > 0x7fffffffLL) return set_err(c, PLACE3D_ERR_SIZE, "contraction grid too large");
   ProfScope prof_(c, PLACE3D_STAGE_GEMM, s);
   if (c->prob.precision == PLACE3D_BF16X3) {
     // 64-row blocks when 128-row ones would leave the chip with fewer than two per compute unit
-    const bool half = tiles < 512 && M > 64;
-    const long long tiles64 = (long long)((N + BN - 1) / BN) * ((M + 63) / 64) * nbatch * njobs;
-    const dim3 grid_s(half ? (unsigned)tiles64 : (unsigned)tiles);
+    const bool half = tiles_of(BM, BN) < 512 && M > 64;
+    const dim3 grid_s((unsigned)tiles_of(half ? 64 : BM, BN));
     GemmSplitArgs a;
     a.M = M; a.N = N; a.K = K; a.nbatch = nbatch;
     a.ldd = ld_data; a.ldb = ld_basis; a.ldc = ldc; a.fold_n = fold_n;
@@ -747,7 +725,10 @@ int gemm(place3d_ctx* c, int M, int N, int K, int nbatch, bool left_basis, int l
       a.p[i] = left_basis ? GemmProb{jb.basis.f32, jb.data, jb.out, 0, s_data, s_out, jb.fold}
                           : GemmProb{jb.data, jb.basis.f32, jb.out, s_data, 0, s_out, jb.fold};
     }
-    hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, s, a);
+    if (tiles_of(128, 128) < kF32Wide)
+      hipLaunchKernelGGL(k_gemm_f32<64>, dim3((unsigned)tiles_of(64, 64)), dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL(k_gemm_f32<128>, dim3((unsigned)tiles_of(128, 128)), dim3(256), 0, s, a);
   }
   P3D_LAUNCH(c, "k_gemm");
   return PLACE3D_OK;
