@@ -609,8 +609,9 @@ int32_t place3d_wl_vjp(place3d_ctx* ctx, const float* xyz, const double* d_scale
   if (bad_ptr(xyz) || bad_ptr(grad_xyz)) return set_err(ctx, PLACE3D_ERR_ARG, "NULL or misaligned array");
   if (d_scale && (reinterpret_cast<uintptr_t>(d_scale) & 7)) return set_err(ctx, PLACE3D_ERR_ARG, "misaligned d_scale");
   if (z_mode != PLACE3D_WLZ_FDA && z_mode != PLACE3D_WLZ_VALUE) return set_err(ctx, PLACE3D_ERR_ARG, "bad z_mode");
-  return p3d::wirelength_eval(ctx, xyz, grad_xyz, accumulate != 0, ctx->red, nullptr,
-                              reinterpret_cast<hipStream_t>(stream), false, d_scale, z_mode == PLACE3D_WLZ_FDA);
+  const bool fda = z_mode == PLACE3D_WLZ_FDA;
+  return p3d::wirelength_eval(ctx, xyz, grad_xyz, accumulate != 0, fda ? ctx->red : nullptr, nullptr,
+                              reinterpret_cast<hipStream_t>(stream), false, d_scale, fda);
 }
 
 int32_t place3d_read_scalars(place3d_ctx* ctx, const place3d_state* state, double* host_scalars, void* stream) {

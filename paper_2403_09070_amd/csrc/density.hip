@@ -283,6 +283,8 @@ __device__ __forceinline__ float block_sum(float v, float* sh) {
 // threads of a bucketing workgroup: its 2048 instances take two rounds, and 16 wavefronts per
 // workgroup keep enough loads in flight at a few workgroups per compute unit
 constexpr int kBucketThreads = 1024;
+constexpr long long kOwnScanCounts = 32768;
+constexpr int kOwnScanTiles = 4096;     // two LDS counts each
 constexpr int kCellsPerThread = 2;      // cells a bucketing thread loads together per round
 
 // number of entries (tiles) of a bucketed cell from its packed tile range, 0 for -1 (not bucketed)
@@ -309,12 +311,7 @@ __device__ __forceinline__ void large_record(const Geom& g, const float* __restr
                                              const int32_t* __restrict__ large, int j, float4* __restrict__ rec);
 
 // Blocks [0, nblk) count; the blocks after them write the large-instance records.
-__global__ __launch_bounds__(kBucketThreads) void k_bucket_count(Geom g, TileGeom t, const float* __restrict__ xyz,
-                                                      const float* __restrict__ size, const uint8_t* __restrict__ kind,
-                                                      const uint8_t* __restrict__ cls, int32_t* __restrict__ counts,
-                                                      int32_t* __restrict__ tiles_of, float4* __restrict__ xyzp,
-                                                      const int32_t* __restrict__ large, int nlarge,
-                                                      float4* __restrict__ lrec) {
+__device__ __forceinline__ void bucket_count(Geom g, TileGeom t, const float* __restrict__ xyz, const float* __restrict__ size, const uint8_t* __restrict__ kind, const uint8_t* __restrict__ cls, int32_t* __restrict__ counts, int32_t* __restrict__ tiles_of, float4* __restrict__ xyzp, const int32_t* __restrict__ large, int nlarge, float4* __restrict__ lrec) {
   extern __shared__ int hist[];
   if ((int)blockIdx.x >= t.nblk) {
     const int j = ((int)blockIdx.x - t.nblk) * blockDim.x + threadIdx.x;
@@ -353,6 +350,26 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_count(Geom g, TileGeo
   __syncthreads();
   // block-major: this block's counts are one contiguous row
   for (int k = threadIdx.x; k < t.ntiles; k += blockDim.x) counts[(size_t)blockIdx.x * t.ntiles + k] = hist[k];
+}
+
+struct CountArgs {
+  Geom g;
+  TileGeom t;
+  const float* xyz;
+  const float* size;
+  const uint8_t* kind;
+  const uint8_t* cls;
+  int32_t* counts;
+  int32_t* tiles_of;
+  float4* xyzp;
+  const int32_t* large;
+  int nlarge;
+  float4* lrec;
+};
+template <int B>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_count(Many<CountArgs, B> m) {
+  const CountArgs& a = m.mine();
+  bucket_count(a.g, a.t, a.xyz, a.size, a.kind, a.cls, a.counts, a.tiles_of, a.xyzp, a.large, a.nlarge, a.lrec);
 }
 
 // Exclusive scan of every tile's counts over the bucket blocks (in place, counts block-major
@@ -427,7 +444,7 @@ __global__ __launch_bounds__(kScanTiles * kScanParts) void k_bucket_scan_cols(in
 // + e] tile of extra chunk e, [2 + ntiles + max_extra + e] its index within the tile.  most is the
 // split's bound for the entries at hand, which keeps the extra chunks below max_extra: a tile of v
 // entries has floor((v - 1) / most) of them.
-__device__ void chunk_plan(const int32_t* __restrict__ totals, int entries, SplitBound sb, int k0, int k1, int ntiles,
+__device__ void chunk_plan(const int32_t* totals, int entries, SplitBound sb, int k0, int k1, int ntiles,
                            int max_extra, int32_t* __restrict__ plan) {
   __shared__ int wx[kBucketThreads / kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -465,25 +482,46 @@ __device__ void chunk_plan(const int32_t* __restrict__ totals, int entries, Spli
   if (threadIdx.x == blockDim.x - 1) { plan[0] = ex; plan[1] = most; }
 }
 
-__global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Geom g, TileGeom t, const float* __restrict__ xyz,
-                                                        const float* __restrict__ size, const uint8_t* __restrict__ kind,
-                                                        const uint8_t* __restrict__ cls, const int32_t* __restrict__ counts,
-                                                        const int32_t* __restrict__ totals,
-                                                        int32_t* __restrict__ tile_start,
-                                                        float4* __restrict__ entries, int32_t* __restrict__ cell_entry,
-                                                        int max_extra_d, int32_t* __restrict__ plan_d,
-                                                        int max_extra_g, int32_t* __restrict__ plan_g) {
+// kScan: the workgroup also adds up its column offsets and the tile totals from all blocks' counts,
+// which the scan pass leaves ready otherwise.
+template <bool kScan>
+__device__ __forceinline__ void bucket_scatter(Geom g, TileGeom t, const float* __restrict__ xyz, const float* __restrict__ size, const uint8_t* __restrict__ kind, const uint8_t* __restrict__ cls, const int32_t* __restrict__ counts, const int32_t* totals, int32_t* __restrict__ tile_start, float4* __restrict__ entries, int32_t* __restrict__ cell_entry, int max_extra_d, int32_t* __restrict__ plan_d, int max_extra_g, int32_t* __restrict__ plan_g) {
   // every workgroup scans the tile totals itself (exclusive prefix = tile_start) and workgroup 0
   // stores the result for the later passes; the cursor of tile k starts at tile_start[k] plus
   // this workgroup's offset within the tile
+  if ((int)blockIdx.x >= t.nblk) return;      // a launch over several contexts takes the most blocks of any
   extern __shared__ int cursor[];
   __shared__ int wsum[kBucketThreads / kWave];
   __shared__ int total;
+  if constexpr (kScan) {
+    // counts of the blocks before this one into cursor, of all blocks into tot
+    int* tot = cursor + t.ntiles;
+    for (int k = threadIdx.x; k < 2 * t.ntiles; k += blockDim.x) cursor[k] = 0;
+    __syncthreads();
+    const int parts = max(1, (int)blockDim.x / t.ntiles), q = threadIdx.x / t.ntiles;
+    for (int k = parts > 1 ? (int)threadIdx.x - q * t.ntiles : (int)threadIdx.x; k < t.ntiles && q < parts; k += blockDim.x) {
+      int before = 0, all = 0;
+#pragma unroll 8
+      for (int b = parts > 1 ? q : 0; b < t.nblk; b += parts) {
+        const int v = counts[(size_t)b * t.ntiles + k];
+        all += v;
+        before += b < (int)blockIdx.x ? v : 0;
+      }
+      atomicAdd(&cursor[k], before);
+      atomicAdd(&tot[k], all);
+    }
+    __syncthreads();
+    totals = tot;
+  }
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int per = (t.ntiles + blockDim.x - 1) / blockDim.x;
   const int k0 = min((int)threadIdx.x * per, t.ntiles), k1 = min(k0 + per, t.ntiles);
   int own = 0;
-  for (int k = k0; k < k1; ++k) { const int v = totals[k]; cursor[k] = v; own += v; }
+  for (int k = k0; k < k1; ++k) {
+    const int v = totals[k];
+    if constexpr (!kScan) cursor[k] = v;
+    own += v;
+  }
   int incl = own;
   for (int o = 1; o < kWave; o <<= 1) {
     const int u = __shfl_up(incl, o);
@@ -504,9 +542,9 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Geom g, TileG
   __syncthreads();
   int run = wsum[wave] + incl - own;
   for (int k = k0; k < k1; ++k) {
-    const int v = cursor[k];
+    const int v = kScan ? totals[k] : cursor[k];
     if (blockIdx.x == 0) tile_start[k] = run;
-    cursor[k] = run + counts[(size_t)blockIdx.x * t.ntiles + k];
+    cursor[k] = run + (kScan ? cursor[k] : counts[(size_t)blockIdx.x * t.ntiles + k]);
     run += v;
   }
   if (blockIdx.x == 0 && k0 < k1 && k1 == t.ntiles) tile_start[t.ntiles] = run;
@@ -514,7 +552,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Geom g, TileG
   __syncthreads();
   // the two chunk plans, by workgroups 0 and 1 where there are two
   if (blockIdx.x == 0) chunk_plan(totals, total, kSplit[kSplitDensity], k0, k1, t.ntiles, max_extra_d, plan_d);
-  if (blockIdx.x == min(1u, gridDim.x - 1)) {
+  if ((int)blockIdx.x == min(1, t.nblk - 1)) {
     __syncthreads();            // a single workgroup makes both: the wavefront sums are free again
     chunk_plan(totals, total, kSplit[kSplitGather], k0, k1, t.ntiles, max_extra_g, plan_g);
   }
@@ -548,6 +586,29 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Geom g, TileG
         }
     }
   }
+}
+
+struct ScatterArgs {
+  Geom g;
+  TileGeom t;
+  const float* xyz;
+  const float* size;
+  const uint8_t* kind;
+  const uint8_t* cls;
+  const int32_t* counts;
+  const int32_t* totals;
+  int32_t* tile_start;
+  float4* entries;
+  int32_t* cell_entry;
+  int max_extra_d;
+  int32_t* plan_d;
+  int max_extra_g;
+  int32_t* plan_g;
+};
+template <bool kScan, int B>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_scatter(Many<ScatterArgs, B> m) {
+  const ScatterArgs& a = m.mine();
+  bucket_scatter<kScan>(a.g, a.t, a.xyz, a.size, a.kind, a.cls, a.counts, a.totals, a.tile_start, a.entries, a.cell_entry, a.max_extra_d, a.plan_d, a.max_extra_g, a.plan_g);
 }
 
 __device__ __forceinline__ void large_record(const Geom& g, const float* __restrict__ xyz,
@@ -755,12 +816,7 @@ __device__ __forceinline__ void write_tile(const Geom& g, const TileGeom& t, con
 // 64 tiles have three chunks each.)
 // (eight wavefronts per SIMD: the scalar registers its heavy-tile path needs would otherwise cost
 // one; the excess goes to vector-register lanes)
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_density_tiles(Geom g, TileGeom t, const float4* __restrict__ entries,
-                                                       Chunks ch, unsigned long long* __restrict__ sums,
-                                                       const float* __restrict__ fixed_map,
-                                                       const float4* __restrict__ lrec, int nlarge, float target,
-                                                       int fillers, float* __restrict__ rho,
-                                                       double* __restrict__ part, int stride) {
+__device__ __forceinline__ void density_of_tiles(Geom g, TileGeom t, const float4* __restrict__ entries, Chunks ch, unsigned long long* __restrict__ sums, const float* __restrict__ fixed_map, const float4* __restrict__ lrec, int nlarge, float target, int fillers, float* __restrict__ rho, double* __restrict__ part, int stride) {
   extern __shared__ unsigned long long S64[];
   __shared__ int hits[kTileThreads];
   __shared__ int wave_cnt[kTileThreads / kWave];
@@ -907,6 +963,27 @@ __global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)
   }
 }
 
+struct DensityArgs {
+  Geom g;
+  TileGeom t;
+  const float4* entries;
+  Chunks ch;
+  unsigned long long* sums;
+  const float* fixed_map;
+  const float4* lrec;
+  int nlarge;
+  float target;
+  int fillers;
+  float* rho;
+  double* part;
+  int stride;
+};
+template <int B>
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_density_tiles(Many<DensityArgs, B> m) {
+  const DensityArgs& a = m.mine();
+  density_of_tiles(a.g, a.t, a.entries, a.ch, a.sums, a.fixed_map, a.lrec, a.nlarge, a.target, a.fillers, a.rho, a.part, a.stride);
+}
+
 // fixed map: one workgroup per fixed instance, global atomics (built once)
 __global__ void k_density_large(Geom g, const float* __restrict__ xyz, const float* __restrict__ size,
                                 const uint8_t* __restrict__ kind, const int32_t* __restrict__ list,
@@ -982,30 +1059,13 @@ __global__ void k_zero_f64(double* __restrict__ p, int n) {
 __global__ __launch_bounds__(256) void k_red_final(const double* __restrict__ part, int stride, int slot0, int nq0,
                                                    int nparts0, int is_max, double* __restrict__ out0, int slot1,
                                                    int nparts1, double* __restrict__ out1) {
-  __shared__ double sh[256];
+  __shared__ double sh[1][256];
   const bool second = (int)blockIdx.x >= nq0;
   const int qi = second ? (int)blockIdx.x - nq0 : (int)blockIdx.x;
-  const int q = (second ? slot1 : slot0) + qi;
-  const int nparts = second ? nparts1 : nparts0;
-  double* out = second ? out1 : out0;
-  const double* row = part + (size_t)q * stride;
-  // four independent accumulators keep four loads in flight per thread
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-  int b = threadIdx.x;
-  for (; b + 768 < nparts; b += 1024) {
-    const double v0 = row[b], v1 = row[b + 256], v2 = row[b + 512], v3 = row[b + 768];
-    if (is_max) { a0 = fmax(a0, v0); a1 = fmax(a1, v1); a2 = fmax(a2, v2); a3 = fmax(a3, v3); }
-    else { a0 += v0; a1 += v1; a2 += v2; a3 += v3; }
-  }
-  for (; b < nparts; b += 256) a0 = is_max ? fmax(a0, row[b]) : a0 + row[b];
-  sh[threadIdx.x] = is_max ? fmax(fmax(a0, a1), fmax(a2, a3)) : (a0 + a1) + (a2 + a3);
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o)
-      sh[threadIdx.x] = is_max ? fmax(sh[threadIdx.x], sh[threadIdx.x + o]) : sh[threadIdx.x] + sh[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[qi] = sh[0];
+  const double* const row[1] = {part + (size_t)((second ? slot1 : slot0) + qi) * stride};
+  double v[1];
+  row_sums<1>(row, second ? nparts1 : nparts0, is_max != 0, sh, v);
+  if (threadIdx.x == 0) (second ? out1 : out0)[qi] = v[0];
 }
 
 // ------------------------------------------------------------------ field gather
@@ -1016,12 +1076,7 @@ __global__ __launch_bounds__(256) void k_red_final(const double* __restrict__ pa
 // sign (E - O), with E at column x and O at column hx + x of the stored map.
 struct FoldX { int on, hx; float sx, sy, sz; };
 
-__global__ __launch_bounds__(kTileThreads) void k_gather_tiles(Geom g, TileGeom t, const float4* __restrict__ entries,
-                                                      Chunks ch,
-                                                      const float* __restrict__ mx, const float* __restrict__ my,
-                                                      const float* __restrict__ mz, FoldX fx, float4* __restrict__ out,
-                                                      const float4* __restrict__ lrec, int nlarge,
-                                                      float4* __restrict__ lpart) {
+__device__ __forceinline__ void gather_of_tiles(Geom g, TileGeom t, const float4* __restrict__ entries, Chunks ch, const float* __restrict__ mx, const float* __restrict__ my, const float* __restrict__ mz, FoldX fx, float4* __restrict__ out, const float4* __restrict__ lrec, int nlarge, float4* __restrict__ lpart) {
   extern __shared__ __align__(16) float S[];
   __shared__ int hits[kTileThreads];
   __shared__ int wave_cnt[kTileThreads / kWave];
@@ -1159,10 +1214,28 @@ __global__ __launch_bounds__(kTileThreads) void k_gather_tiles(Geom g, TileGeom 
   }
 }
 
+struct GatherArgs {
+  Geom g;
+  TileGeom t;
+  const float4* entries;
+  Chunks ch;
+  const float* mx;
+  const float* my;
+  const float* mz;
+  FoldX fx;
+  float4* out;
+  const float4* lrec;
+  int nlarge;
+  float4* lpart;
+};
+template <int B>
+__global__ __launch_bounds__(kTileThreads) void k_gather_tiles(Many<GatherArgs, B> m) {
+  const GatherArgs& a = m.mine();
+  gather_of_tiles(a.g, a.t, a.entries, a.ch, a.mx, a.my, a.mz, a.fx, a.out, a.lrec, a.nlarge, a.lpart);
+}
+
 // per large instance (one wavefront each): sum the partials of the tiles its record overlaps
-__global__ void k_large_gather_finish(Geom g, TileGeom t, const int32_t* __restrict__ large, int nlarge,
-                                      const float4* __restrict__ lrec, const float4* __restrict__ lpart, float scale,
-                                      float* __restrict__ grad, int accumulate) {
+__device__ __forceinline__ void large_gather_finish(Geom g, TileGeom t, const int32_t* __restrict__ large, int nlarge, const float4* __restrict__ lrec, const float4* __restrict__ lpart, float scale, float* __restrict__ grad, int accumulate) {
   const int j = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   const int lane = threadIdx.x & (kWave - 1);
   if (j >= nlarge) return;
@@ -1181,6 +1254,23 @@ __global__ void k_large_gather_finish(Geom g, TileGeom t, const int32_t* __restr
     if (accumulate) { grad[i] += scale * sx; grad[n + i] += scale * sy; grad[2 * n + i] += scale * sz; }
     else { grad[i] = scale * sx; grad[n + i] = scale * sy; grad[2 * n + i] = scale * sz; }
   }
+}
+
+struct FinishArgs {
+  Geom g;
+  TileGeom t;
+  const int32_t* large;
+  int nlarge;
+  const float4* lrec;
+  const float4* lpart;
+  float scale;
+  float* grad;
+  int accumulate;
+};
+template <int B>
+__global__ void k_large_gather_finish(Many<FinishArgs, B> m) {
+  const FinishArgs& a = m.mine();
+  large_gather_finish(a.g, a.t, a.large, a.nlarge, a.lrec, a.lpart, a.scale, a.grad, a.accumulate);
 }
 
 __device__ __forceinline__ void gather3(const Geom& g, const float* __restrict__ mx, const float* __restrict__ my,
@@ -1532,10 +1622,10 @@ int reduce_final_in(place3d_ctx* c, const double* part, int stride, int slot0, i
   return PLACE3D_OK;
 }
 
-int reduce_final2(place3d_ctx* c, int slot0, int nq0, int nparts0, double* out0, int slot1, int nq1, int nparts1,
-                  double* out1, hipStream_t s) {
+int reduce_final2(place3d_ctx* c, const double* part, int stride, int slot0, int nq0, int nparts0, double* out0, int slot1,
+                  int nq1, int nparts1, double* out1, hipStream_t s) {
   ProfScope prof_(c, PLACE3D_STAGE_UPDATE, s);
-  hipLaunchKernelGGL(k_red_final, dim3(nq0 + nq1), dim3(256), 0, s, c->part, c->part_stride, slot0, nq0, nparts0, 0,
+  hipLaunchKernelGGL(k_red_final, dim3(nq0 + nq1), dim3(256), 0, s, part, stride, slot0, nq0, nparts0, 0,
                      out0, slot1, nparts1, out1);
   P3D_LAUNCH(c, "k_red_final");
   return PLACE3D_OK;
@@ -1553,54 +1643,105 @@ int build_fixed_map(place3d_ctx* c, hipStream_t s) {
   return PLACE3D_OK;
 }
 
+// launches kern<B> for nb contexts, B their number or the most there are; args(i) makes context i's
+// arguments
+template <class A, class Args, class K1, class KN>
+void launch_many(K1 one, KN many, int nb, unsigned blocks, unsigned threads, size_t lds, hipStream_t s, Args args) {
+  if (nb == 1) {
+    hipLaunchKernelGGL(one, dim3(blocks), dim3(threads), lds, s, Many<A, 1>{{args(0)}});
+  } else {
+    Many<A, kMaxMany> m;
+    for (int i = 0; i < kMaxMany; ++i) m.v[i] = args(i < nb ? i : 0);
+    hipLaunchKernelGGL(many, dim3(blocks, nb), dim3(threads), lds, s, m);
+  }
+}
+template <class Get>
+int most_of(int nb, Get get) {
+  int m = get(0);
+  for (int i = 1; i < nb; ++i) m = std::max(m, get(i));
+  return m;
+}
+
 int bucket_cells(place3d_ctx* c, const float* xyz, hipStream_t s, int part) {
-  const Geom& g = c->g;
-  const TileGeom& t = c->tg;
-  const place3d_problem& p = c->prob;
-  ProfScope prof_(c, PLACE3D_STAGE_BUCKET, s);
-  const size_t hist = sizeof(int) * t.ntiles;
-  const int nrec = (c->n_large + kBucketThreads - 1) / kBucketThreads;
+  return bucket_cells_many(&c, &xyz, 1, s, part);
+}
+
+int bucket_cells_many(place3d_ctx* const* c, const float* const* xyz, int nb, hipStream_t s, int part) {
+  const int ntiles = c[0]->tg.ntiles;
+  ProfScope prof_(c[0], PLACE3D_STAGE_BUCKET, s);
+  const size_t hist = sizeof(int) * ntiles;
   if (part != 2) {
-    hipLaunchKernelGGL(k_bucket_count, dim3(t.nblk + nrec), dim3(kBucketThreads), hist, s, g, t, xyz, p.size, p.kind,
-                       c->cls, c->bk_counts, c->cell_entry, c->xyzp, c->large_list, c->n_large, c->large_rec);
-    P3D_LAUNCH(c, "k_bucket_count");
+    const int blocks = most_of(nb, [&](int i) {
+      return c[i]->tg.nblk + (c[i]->n_large + kBucketThreads - 1) / kBucketThreads;
+    });
+    launch_many<CountArgs>(k_bucket_count<1>, k_bucket_count<kMaxMany>, nb, blocks, kBucketThreads, hist, s, [&](int i) {
+      place3d_ctx* q = c[i];
+      return CountArgs{q->g, q->tg, xyz[i], q->prob.size, q->prob.kind, q->cls, q->bk_counts, q->cell_entry, q->xyzp,
+                       q->large_list, q->n_large, q->large_rec};
+    });
+    P3D_LAUNCH(c[0], "k_bucket_count");
   }
   if (part == 1) return PLACE3D_OK;
-  hipLaunchKernelGGL(k_bucket_scan_cols, dim3((t.ntiles + kScanTiles - 1) / kScanTiles), dim3(kScanTiles * kScanParts), 0, s, t.nblk,
-                     t.ntiles, c->bk_counts, c->bk_totals);
-  P3D_LAUNCH(c, "k_bucket_scan_cols");
-  hipLaunchKernelGGL(k_bucket_scatter, dim3(t.nblk), dim3(kBucketThreads), hist, s, g, t, xyz, p.size, p.kind, c->cls,
-                     c->bk_counts, c->bk_totals, c->bk_tile_start, c->bk_entries, c->cell_entry,
-                     c->max_extra[kSplitDensity], c->bk_plan[kSplitDensity], c->max_extra[kSplitGather],
-                     c->bk_plan[kSplitGather]);
-  P3D_LAUNCH(c, "k_bucket_scatter");
+  // Up to this many counts every scatter workgroup adds them up itself: 25k of them (200k instances on
+  // 256 tiles) cost it 3 us, the scan pass 5 and a launch (step 130 -> 126 us; multi-die 300k nodes
+  // 197 -> 181; even at 40k).
+  const int nblk = most_of(nb, [&](int i) { return c[i]->tg.nblk; });
+  const bool own_scan = (long long)nblk * ntiles <= kOwnScanCounts && ntiles <= kOwnScanTiles;
+  for (int i = 0; i < nb && !own_scan; ++i) {
+    hipLaunchKernelGGL(k_bucket_scan_cols, dim3((ntiles + kScanTiles - 1) / kScanTiles), dim3(kScanTiles * kScanParts), 0, s,
+                       c[i]->tg.nblk, ntiles, c[i]->bk_counts, c[i]->bk_totals);
+    P3D_LAUNCH(c[0], "k_bucket_scan_cols");
+  }
+  auto args = [&](int i) {
+    place3d_ctx* q = c[i];
+    return ScatterArgs{q->g, q->tg, xyz[i], q->prob.size, q->prob.kind, q->cls, q->bk_counts, q->bk_totals,
+                       q->bk_tile_start, q->bk_entries, q->cell_entry, q->max_extra[kSplitDensity],
+                       q->bk_plan[kSplitDensity], q->max_extra[kSplitGather], q->bk_plan[kSplitGather]};
+  };
+  if (own_scan)
+    launch_many<ScatterArgs>(k_bucket_scatter<true, 1>, k_bucket_scatter<true, kMaxMany>, nb, nblk, kBucketThreads,
+                             2 * hist, s, args);
+  else
+    launch_many<ScatterArgs>(k_bucket_scatter<false, 1>, k_bucket_scatter<false, kMaxMany>, nb, nblk, kBucketThreads, hist,
+                             s, args);
+  P3D_LAUNCH(c[0], "k_bucket_scatter");
   return PLACE3D_OK;
 }
 
 int density_tiles(place3d_ctx* c, const float* xyz, float* rho, double* red, hipStream_t s, bool reduce) {
-  const Geom& g = c->g;
-  const TileGeom& t = c->tg;
-  const place3d_problem& p = c->prob;
+  return density_tiles_many(&c, &xyz, &rho, &red, 1, s, reduce);
+}
+
+int density_tiles_many(place3d_ctx* const* c, const float* const* xyz, float* const* rho, double* const* red, int nb,
+                       hipStream_t s, bool reduce) {
+  const int ntiles = c[0]->tg.ntiles;
   {
-    ProfScope prof_(c, PLACE3D_STAGE_DENSITY, s);
-    const int fillers = c->n_fillers > 0 ? 1 : 0;
-    const bool inst = (p.options & PLACE3D_OPT_MACRO_INSTANCE) != 0;
-    hipLaunchKernelGGL(k_density_tiles, dim3(t.ntiles + c->max_extra[kSplitDensity]), dim3(kTileThreads), (2 + 2 * fillers) * tile_lds(c, 1), s, g,
-                       t, c->bk_entries, chunks_of(c, kSplitDensity), c->chunk_sums,
-                       c->n_fixed > 0 ? c->fixed_map : nullptr, c->large_rec,
-                       inst ? 0 : c->n_large, (float)p.target_density, fillers, rho, c->part, c->part_stride);
-    P3D_LAUNCH(c, "k_density_tiles");
-    if (inst && c->n_large > 0) {
-      hipLaunchKernelGGL(k_density_large_thread, dim3(blocks_for(c->n_large, 64)), dim3(64), 0, s, g, xyz, p.size,
-                         p.kind, c->large_list, c->n_large, rho);
-      P3D_LAUNCH(c, "k_density_large_thread");
-      hipLaunchKernelGGL(k_map_excess, dim3(t.ntiles), dim3(256), 0, s, g, rho, (float)p.target_density, c->part,
-                         c->part_stride);
-      P3D_LAUNCH(c, "k_map_excess");
+    ProfScope prof_(c[0], PLACE3D_STAGE_DENSITY, s);
+    const int fillers = most_of(nb, [&](int i) { return c[i]->n_fillers > 0 ? 1 : 0; });
+    const int extra = most_of(nb, [&](int i) { return c[i]->max_extra[kSplitDensity]; });
+    auto inst = [&](int i) { return (c[i]->prob.options & PLACE3D_OPT_MACRO_INSTANCE) != 0; };
+    launch_many<DensityArgs>(k_density_tiles<1>, k_density_tiles<kMaxMany>, nb, ntiles + extra, kTileThreads,
+                             (2 + 2 * fillers) * tile_lds(c[0], 1), s, [&](int i) {
+      place3d_ctx* q = c[i];
+      return DensityArgs{q->g, q->tg, q->bk_entries, chunks_of(q, kSplitDensity), q->chunk_sums,
+                         q->n_fixed > 0 ? q->fixed_map : nullptr, q->large_rec, inst(i) ? 0 : q->n_large,
+                         (float)q->prob.target_density, q->n_fillers > 0 ? 1 : 0, rho[i], q->part, q->part_stride};
+    });
+    P3D_LAUNCH(c[0], "k_density_tiles");
+    for (int i = 0; i < nb; ++i) {
+      place3d_ctx* q = c[i];
+      if (!inst(i) || q->n_large == 0) continue;
+      hipLaunchKernelGGL(k_density_large_thread, dim3(blocks_for(q->n_large, 64)), dim3(64), 0, s, q->g, xyz[i],
+                         q->prob.size, q->prob.kind, q->large_list, q->n_large, rho[i]);
+      P3D_LAUNCH(c[0], "k_density_large_thread");
+      hipLaunchKernelGGL(k_map_excess, dim3(ntiles), dim3(256), 0, s, q->g, rho[i], (float)q->prob.target_density, q->part,
+                         q->part_stride);
+      P3D_LAUNCH(c[0], "k_map_excess");
     }
   }
-  if (!reduce) return PLACE3D_OK;
-  return reduce_final(c, R_EXCESS_BOT, 2, t.ntiles, false, red + R_EXCESS_BOT, s);
+  for (int i = 0; i < nb && reduce; ++i)
+    if (int rc = reduce_final(c[i], R_EXCESS_BOT, 2, ntiles, false, red[i] + R_EXCESS_BOT, s)) return rc;
+  return PLACE3D_OK;
 }
 
 int density_forward(place3d_ctx* c, const float* xyz, float* rho, hipStream_t s) {
@@ -1610,32 +1751,50 @@ int density_forward(place3d_ctx* c, const float* xyz, float* rho, hipStream_t s)
 
 int gather_bucketed(place3d_ctx* c, const float* xyz, const float* ex, const float* ey, const float* ez, float scale,
                     float* grad, int accumulate, hipStream_t s, bool cells, bool xfold) {
-  const Geom& g = c->g;
-  const TileGeom& t = c->tg;
-  const place3d_problem& p = c->prob;
-  const bool tiled = large_in_tiles(c);
-  ProfScope prof_(c, PLACE3D_STAGE_DGRAD, s);
-  if (xfold && !tiled) return set_err(c, PLACE3D_ERR_ARG, "x-folded field maps need the tiled large-instance path");
+  return gather_bucketed_many(&c, &xyz, &ex, &ey, &ez, scale, &grad, accumulate, 1, s, cells, xfold);
+}
+
+int gather_bucketed_many(place3d_ctx* const* c, const float* const* xyz, const float* const* ex, const float* const* ey,
+                         const float* const* ez, float scale, float* const* grad, int accumulate, int nb, hipStream_t s,
+                         bool cells, bool xfold) {
+  const int ntiles = c[0]->tg.ntiles;
+  ProfScope prof_(c[0], PLACE3D_STAGE_DGRAD, s);
+  for (int i = 0; i < nb; ++i)
+    if (xfold && !large_in_tiles(c[i]))
+      return set_err(c[0], PLACE3D_ERR_ARG, "x-folded field maps need the tiled large-instance path");
   // Ex comes from the sine basis (unfold sign -1), Ey and Ez from the cosine basis (+1)
-  const FoldX fx{xfold ? 1 : 0, g.nx / 2, -1.f, 1.f, 1.f};
-  hipLaunchKernelGGL(k_gather_tiles, dim3(t.ntiles + c->max_extra[kSplitGather]), dim3(kTileThreads), tile_lds(c, 3), s, g, t, c->bk_entries,
-                     chunks_of(c, kSplitGather), ex, ey, ez, fx, c->entry_out, c->large_rec, c->n_large,
-                     tiled && c->n_large > 0 ? c->lpart : nullptr);
-  P3D_LAUNCH(c, "k_gather_tiles");
-  if (c->n_large > 0 && tiled) {
-    hipLaunchKernelGGL(k_large_gather_finish, dim3(blocks_for(c->n_large, 256 / kWave)), dim3(256), 0, s, g, t,
-                       c->large_list, c->n_large, c->large_rec, c->lpart, scale, grad, accumulate);
-    P3D_LAUNCH(c, "k_large_gather_finish");
-  } else if (c->n_large > 0) {
-    hipLaunchKernelGGL(k_gather_large, dim3(c->n_large), dim3(256), 0, s, g, xyz, p.size, p.kind, c->large_list, ex,
-                       ey, ez, scale, grad, accumulate);
-    P3D_LAUNCH(c, "k_gather_large");
+  const FoldX fx{xfold ? 1 : 0, c[0]->g.nx / 2, -1.f, 1.f, 1.f};
+  const int extra = most_of(nb, [&](int i) { return c[i]->max_extra[kSplitGather]; });
+  launch_many<GatherArgs>(k_gather_tiles<1>, k_gather_tiles<kMaxMany>, nb, ntiles + extra, kTileThreads,
+                          tile_lds(c[0], 3), s, [&](int i) {
+    place3d_ctx* q = c[i];
+    return GatherArgs{q->g, q->tg, q->bk_entries, chunks_of(q, kSplitGather), ex[i], ey[i], ez[i], fx, q->entry_out,
+                      q->large_rec, q->n_large, large_in_tiles(q) && q->n_large > 0 ? q->lpart : nullptr};
+  });
+  P3D_LAUNCH(c[0], "k_gather_tiles");
+  // (a context whose large instances do not go through the tiles takes none here)
+  auto nlarge = [&](int i) { return large_in_tiles(c[i]) ? c[i]->n_large : 0; };
+  if (most_of(nb, nlarge) > 0) {
+    launch_many<FinishArgs>(k_large_gather_finish<1>, k_large_gather_finish<kMaxMany>, nb,
+                            blocks_for(most_of(nb, nlarge), 256 / kWave), 256, 0, s, [&](int i) {
+      place3d_ctx* q = c[i];
+      return FinishArgs{q->g, q->tg, q->large_list, nlarge(i), q->large_rec, q->lpart, scale, grad[i], accumulate};
+    });
+    P3D_LAUNCH(c[0], "k_large_gather_finish");
   }
-  c->cell_scale = scale;
-  if (!cells) return PLACE3D_OK;
-  hipLaunchKernelGGL(k_cells_combine, dim3(blocks_for(g.n, 256)), dim3(256), 0, s, g.n, c->cls, c->cell_entry,
-                     c->entry_out, scale, (const double*)nullptr, grad, accumulate);
-  P3D_LAUNCH(c, "k_cells_combine");
+  for (int i = 0; i < nb; ++i) {
+    place3d_ctx* q = c[i];
+    if (q->n_large > 0 && !large_in_tiles(q)) {
+      hipLaunchKernelGGL(k_gather_large, dim3(q->n_large), dim3(256), 0, s, q->g, xyz[i], q->prob.size, q->prob.kind,
+                         q->large_list, ex[i], ey[i], ez[i], scale, grad[i], accumulate);
+      P3D_LAUNCH(c[0], "k_gather_large");
+    }
+    q->cell_scale = scale;
+    if (!cells) continue;
+    hipLaunchKernelGGL(k_cells_combine, dim3(blocks_for(q->g.n, 256)), dim3(256), 0, s, q->g.n, q->cls, q->cell_entry,
+                       q->entry_out, scale, (const double*)nullptr, grad[i], accumulate);
+    P3D_LAUNCH(c[0], "k_cells_combine");
+  }
   return PLACE3D_OK;
 }
 

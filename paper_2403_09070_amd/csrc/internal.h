@@ -252,6 +252,95 @@ struct ProfScope {
   ~ProfScope() { if (on) prof_end(c, s, launches); }
 };
 
+// Sums (or maxima) of NQ rows of nparts float64 partials by a workgroup of 256 threads, in the fixed
+// order of every final reduction here; all threads get the results.  The rows' loads are in flight
+// together, four per thread and row.
+template <int NQ>
+__device__ __forceinline__ void row_sums(const double* const (&row)[NQ], int nparts, bool is_max, double (&sh)[NQ][256],
+                                         double (&out)[NQ]) {
+  double a[NQ][4] = {};
+  int b = threadIdx.x;
+  for (; b + 768 < nparts; b += 1024) {
+    double v[NQ][4];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[q][u] = row[q][b + 256 * u];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a[q][u] = is_max ? fmax(a[q][u], v[q][u]) : a[q][u] + v[q][u];
+  }
+  for (; b < nparts; b += 256)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) a[q][0] = is_max ? fmax(a[q][0], row[q][b]) : a[q][0] + row[q][b];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+    sh[q][threadIdx.x] = is_max ? fmax(fmax(a[q][0], a[q][1]), fmax(a[q][2], a[q][3])) : (a[q][0] + a[q][1]) + (a[q][2] + a[q][3]);
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (threadIdx.x < o)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+        sh[q][threadIdx.x] = is_max ? fmax(sh[q][threadIdx.x], sh[q][threadIdx.x + o]) : sh[q][threadIdx.x] + sh[q][threadIdx.x + o];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) out[q] = sh[q][0];
+}
+
+// Partials up to which the move sums a step's norms itself, every workgroup the same two rows, instead
+// of reading what a reduction launched before it left: it saves a launch (2k instances 88 -> 84 us a
+// step, the host's time) and costs a round of loads per 1024 partials (200k instances, 785 partials:
+// 125.5 -> 126.3 us).
+constexpr int kOwnSumParts = 512;
+
+// scale of the FDA z-gradient (Eq. fda-normalize) from the evaluation's norms
+__device__ __forceinline__ double fda_scale(const double* red) {
+  const double nf = red[R_NORM_FDA];
+  return nf > 0.0 ? (red[R_NORM_X] + red[R_NORM_Y]) / (2.0 * nf) : 0.0;
+}
+
+// Cell density gradients held as per-(cell, tile) shares (entry != nullptr, cell-major [q][n], q < the
+// cell's entry count read from its packed tile range), summed in the order the separate combine pass
+// uses.
+struct CellShares {
+  const uint8_t* cls;
+  const int32_t* cell_entry;
+  const float4* entry;
+  float scale;
+};
+
+// cls and packed: the instance's density class and packed tile range (loaded by the caller with
+// its other operands); a cell's up to four shares are loaded together and summed in q order
+__device__ __forceinline__ void density_grad_of(const CellShares& cs, const float* __restrict__ gd, int n, int i,
+                                                uint8_t cls, int packed, float (&d)[3]) {
+  if (!cs.entry || cls == kClsLarge) {
+    for (int a = 0; a < 3; ++a) d[a] = gd[a * n + i];
+    return;
+  }
+  float sx = 0.f, sy = 0.f, sz = 0.f;
+  if (cls == kClsCell) {
+    // the cell's entry count from its packed tile range; its shares are cell-major [q][n]
+    // (a bucketed cell has 1, 2 or 4 entries: its tile range is 1 or 2 tiles per axis)
+    const int cnt = packed < 0 ? 0 : (1 + ((packed >> 24) & 1)) * (1 + ((packed >> 25) & 1));
+    // All four loads are issued together: an absent share's load re-reads share 0 (the same
+    // cache line) and counts as zero, which leaves the sum in q order unchanged.
+    const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    const size_t i1 = cnt > 1 ? (size_t)n + i : (size_t)i;
+    const size_t i2 = cnt > 2 ? 2 * (size_t)n + i : (size_t)i, i3 = cnt > 2 ? 3 * (size_t)n + i : (size_t)i;
+    const float4 r0 = cs.entry[i], r1 = cs.entry[i1], r2 = cs.entry[i2], r3 = cs.entry[i3];
+    const float4 v0 = r0, v1 = cnt > 1 ? r1 : z4, v2 = cnt > 2 ? r2 : z4, v3 = cnt > 2 ? r3 : z4;
+    if (cnt > 0) {
+      sx = ((v0.x + v1.x) + v2.x) + v3.x;
+      sy = ((v0.y + v1.y) + v2.y) + v3.y;
+      sz = ((v0.z + v1.z) + v2.z) + v3.z;
+    }
+    sx *= cs.scale; sy *= cs.scale; sz *= cs.scale;
+  }
+  d[0] = sx; d[1] = sy; d[2] = sz;
+}
+
 // ---- launchers implemented in the .hip sources (all enqueue only) ----
 int launch_zero_f64(place3d_ctx* c, double* p, int n, hipStream_t s);
 int launch_fill_f32(place3d_ctx* c, float* p, long long n, float v, hipStream_t s);
@@ -277,11 +366,27 @@ int reduce_final_in(place3d_ctx* c, const double* part, int stride, int slot0, i
                     double* out, hipStream_t s);
 // two sum reductions in one launch: slots slot0.. (nq0 of them, nparts0 partials) into out0[] and
 // slots slot1.. (nq1, nparts1) into out1[]
-int reduce_final2(place3d_ctx* c, int slot0, int nq0, int nparts0, double* out0, int slot1, int nq1, int nparts1,
+int reduce_final2(place3d_ctx* c, const double* part, int stride, int slot0, int nq0, int nparts0, double* out0, int slot1, int nq1, int nparts1,
                   double* out1, hipStream_t s);
 
 int build_fixed_map(place3d_ctx* c, hipStream_t s);
 // part 0: the whole bucketing; 1: only the count pass (which also packs xyzp); 2: the rest
+// The same launch over up to kMaxMany contexts (blockIdx.y picks one), for the layers of a multi-die
+// problem: their grids and options are the same, their instances are not.
+constexpr int kMaxMany = 3;
+template <class A, int B>
+struct Many {
+  A v[B];
+  __device__ __forceinline__ const A& mine() const { return v[B == 1 ? 0 : blockIdx.y]; }
+};
+int bucket_cells_many(place3d_ctx* const* c, const float* const* xyz, int nb, hipStream_t s, int part = 0);
+int density_tiles_many(place3d_ctx* const* c, const float* const* xyz, float* const* rho, double* const* red, int nb,
+                       hipStream_t s, bool reduce);
+int gather_bucketed_many(place3d_ctx* const* c, const float* const* xyz, const float* const* ex, const float* const* ey,
+                         const float* const* ez, float scale, float* const* grad, int accumulate, int nb, hipStream_t s,
+                         bool cells, bool xfold);
+int field_fft_many(place3d_ctx* const* c, const float* const* rho, float* const* phi, float* const* ex, float* const* ey,
+                   float* const* ez, int nb, hipStream_t s);
 int bucket_cells(place3d_ctx* c, const float* xyz, hipStream_t s, int part = 0);
 // reduce: finish the overflow reduction here (else the caller reduces the R_EXCESS slots later)
 int density_tiles(place3d_ctx* c, const float* xyz, float* rho, double* red, hipStream_t s, bool reduce = true);
@@ -300,9 +405,11 @@ int density_adjoint(place3d_ctx* c, const float* xyz, const float* gmap, float s
 // packed: c->xyzp already holds xyz (the bucket pass of the same positions wrote it); dscale: a
 // device float64 factor of the gradient (NULL: 1); with_fda: the z-gradient carries the normalised
 // FDA term, else only the derivative of alpha p^(z)
+// red: receives the totals and norms (null without with_fda: none are made).  finish_z: write the
+// z gradient and the metrics (else the caller's kernel takes wl_gzwa, wl_fda and the norms).
 int wirelength_eval(place3d_ctx* c, const float* xyz, float* grad, int accumulate, double* red,
                     double* metrics, hipStream_t s, bool packed = false, const double* dscale = nullptr,
-                    bool with_fda = true);
+                    bool with_fda = true, bool finish_z = true);
 // the model's net totals only (no gradient, nothing per pin) into metrics[PLACE3D_NMETRICS]; the
 // packed positions and the per-workgroup partials go to xyzp / part (stride per slot) when given,
 // else to the workspace's

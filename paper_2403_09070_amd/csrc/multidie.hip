@@ -22,8 +22,10 @@ using namespace p3d;
 
 namespace {
 
+constexpr int kOwnNorms = 2048;   // partials up to which the move sums the step's norms itself
+
 enum MdSlot {   // float64 reduction slots of the multi-die context
-  M_DV2 = 0, M_DG2, M_GMAX, M_L1W, M_L1D = M_L1W + 3, M_COUNT = M_L1D + 3
+  M_DV2 = 0, M_DG2, M_GMAX, M_A_PREV, M_L1W, M_L1D = M_L1W + 3, M_COUNT = M_L1D + 3
 };
 
 }  // namespace
@@ -44,7 +46,6 @@ struct place3d_md2d_ctx {
   uint8_t* l_kind[3] = {};
   int32_t* l_start[3] = {};
   int32_t* node_local = nullptr;     // [n] index of a node in its layer's sub-problem
-  float* xyz_wl = nullptr;           // [3][n]
   float* g_wl = nullptr;             // [3][n]
   float* xyz_l[3] = {};              // [3][n_L]
   float* g_l[3] = {};                // [3][n_L]
@@ -53,8 +54,9 @@ struct place3d_md2d_ctx {
   int part_stride = 0;
   char* sub_ws[4] = {};
   size_t sub_bytes[4] = {};
-  // an evaluation forks the wirelength and the three layers onto the sub-contexts' side streams
-  hipEvent_t ev_fork = nullptr, ev_done[4] = {};
+  // an evaluation forks the wirelength (and where the layers' solves do not share launches, two of
+  // them) onto the sub-contexts' side streams
+  hipEvent_t ev_fork = nullptr, ev_done[3] = {};
   ~place3d_md2d_ctx() {
     place3d_destroy(wl);
     for (auto* c : lay) place3d_destroy(c);
@@ -75,24 +77,27 @@ int md_err(place3d_md2d_ctx* c, int code, const std::string& msg) {
 
 // ------------------------------------------------------------------ kernels
 
-// positions of the sub-problems: every node at (x, y, zmid) in the wirelength context and in its
-// layer's context
+// positions of the sub-problems: every node at (x, y, zmid) in the wirelength context (packed, as
+// its sweep reads them) and in its layer's context
 __global__ void k_md_pack(int n, const float* __restrict__ xy, const uint8_t* __restrict__ layer,
-                          const int32_t* __restrict__ local, float zmid, float* __restrict__ xyz_wl, float* l0,
+                          const int32_t* __restrict__ local, float zmid, float4* __restrict__ xyzp, float* l0,
                           float* l1, float* l2, int n0, int n1, int n2) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const float x = xy[i], y = xy[n + i];
-  xyz_wl[i] = x; xyz_wl[n + i] = y; xyz_wl[2 * n + i] = zmid;
+  xyzp[i] = make_float4(x, y, zmid, 0.f);
   const int L = layer[i], j = local[i];
   float* d = L == 0 ? l0 : (L == 1 ? l1 : l2);
   const int m = L == 0 ? n0 : (L == 1 ? n1 : n2);
   d[j] = x; d[m + j] = y; d[2 * m + j] = zmid;
 }
 
+// The layers' density gradients: g (every node's, or the large nodes' where cs holds the cells'
+// shares).
 struct LayerGrads {
   const float* g[3];
   int n[3];
+  CellShares cs[3];
 };
 
 __device__ __forceinline__ void den_grad(const LayerGrads& lg, const uint8_t* __restrict__ layer,
@@ -100,6 +105,14 @@ __device__ __forceinline__ void den_grad(const LayerGrads& lg, const uint8_t* __
   const int L = layer[i], j = local[i];
   const float* g = L == 0 ? lg.g[0] : (L == 1 ? lg.g[1] : lg.g[2]);
   const int m = L == 0 ? lg.n[0] : (L == 1 ? lg.n[1] : lg.n[2]);
+  const CellShares cs = L == 0 ? lg.cs[0] : (L == 1 ? lg.cs[1] : lg.cs[2]);
+  if (cs.entry) {
+    float d[3];
+    density_grad_of(cs, g, m, j, cs.cls[j], cs.cell_entry[j], d);
+    gx = d[0];
+    gy = d[1];
+    return;
+  }
   gx = g[j];
   gy = g[m + j];
 }
@@ -180,14 +193,15 @@ __global__ void k_md_l1(int n, const uint8_t* __restrict__ kind, const uint8_t* 
 
 // g = (grad W + lambda_L grad U_L) / H, H of Eq. improved-precond with q = w h and the node's layer
 // weight.  Mode 0: g to gout and max|g| partials; mode 1: |v - v_prev|^2 and |g - g_prev|^2
-// partials, g over g_prev.
+// partials, g over g_prev, and a_k where the move reads it (the move updates the scalars).
 __global__ void k_md_combine(int n, const float* __restrict__ size, const uint8_t* __restrict__ kind,
                              const uint8_t* __restrict__ layer, const int32_t* __restrict__ local,
                              const float* __restrict__ npins, const float* __restrict__ v,
                              const float* __restrict__ v_prev, const float* __restrict__ g_wl, LayerGrads lg,
                              const double* __restrict__ sc, int mode, float* __restrict__ gout,
-                             double* __restrict__ part, int stride) {
+                             double* __restrict__ part, int stride, double* __restrict__ a_copy) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (mode == 1 && i == 0) *a_copy = sc[PLACE3D_MS_A];
   double acc[2] = {0.0, 0.0};
   if (i < n) {
     const uint8_t k = kind[i];
@@ -261,15 +275,71 @@ __global__ void k_md_bootstrap(int n, const float* __restrict__ size, const uint
   v_prev[n + i] = y;
 }
 
-__global__ void k_md_nesterov(int n, const float* __restrict__ size, const uint8_t* __restrict__ kind, float dx,
-                              float dy, const double* __restrict__ sc, const double* __restrict__ red,
-                              float* __restrict__ u, float* __restrict__ v, float* __restrict__ v_prev,
-                              const float* __restrict__ gk) {
+struct LayerRed { double* r[3]; double scale[3]; };   // excess slots and (2/d_z)/area per layer
+
+// wirelength totals and the layers' overflow at the evaluation point (slots 0..4 of out)
+__device__ __forceinline__ void md_metrics(const double* __restrict__ wl_red, const LayerRed& lr, double* out) {
+  out[PLACE3D_MD_WA] = wl_red[R_WA_BI];
+  out[PLACE3D_MD_HPWL] = wl_red[R_HPWL];
+  for (int L = 0; L < 3; ++L)
+    out[PLACE3D_MD_OVFL + L] = (lr.r[L][R_EXCESS_BOT] + lr.r[L][R_EXCESS_TOP]) * lr.scale[L];
+}
+
+// The step's scalars, by one thread of the move: a = a_k, the layers' overflow excess in lr.
+__device__ void md_step_finish(double* __restrict__ sc, double dv2, double dg2, const double* __restrict__ wl_red,
+                               const LayerRed& lr, double ramp, double a) {
+  sc[PLACE3D_MS_STEP] = dg2 > 0.0 ? sqrt(dv2 / dg2) : 0.0;
+  sc[PLACE3D_MS_A] = 0.5 * (1.0 + sqrt(4.0 * a * a + 1.0));
+  for (int L = 0; L < 3; ++L) sc[PLACE3D_MS_LAMBDA + L] *= ramp;
+  sc[PLACE3D_MS_ITER] += 1.0;
+  md_metrics(wl_red, lr, sc + PLACE3D_MS_METRICS);
+  bool finite = isfinite(dv2) && isfinite(dg2);
+  for (int q = 0; q < 5; ++q) finite = finite && isfinite(sc[PLACE3D_MS_METRICS + q]);
+  for (int L = 0; L < 3; ++L) finite = finite && isfinite(sc[PLACE3D_MS_LAMBDA + L]);
+  if (!finite && sc[PLACE3D_MS_NONFINITE] == 0.0) sc[PLACE3D_MS_NONFINITE] = sc[PLACE3D_MS_ITER];
+}
+
+// the layers' overflow partials
+struct LayerParts {
+  const double* part[3];
+  int stride[3], ntiles[3];
+};
+
+// The move; the first workgroup also sums the layers' overflow and writes the step's scalars.  kSum:
+// every workgroup sums the combine's norms from its partials (else a launch before has).
+template <bool kSum>
+__global__ __launch_bounds__(256) void k_md_nesterov(
+    int n, const float* __restrict__ size, const uint8_t* __restrict__ kind, float dx, float dy, double* __restrict__ sc,
+    const double* __restrict__ red, float* __restrict__ u, float* __restrict__ v, float* __restrict__ v_prev,
+    const float* __restrict__ gk, const double* __restrict__ part, int stride, const double* __restrict__ wl_red,
+    LayerRed lr, LayerParts lp, double ramp) {
+  __shared__ double sh[2][256];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  const double a = red[M_A_PREV];
+  double dv2, dg2;
+  if constexpr (kSum) {
+    const double* const row[2] = {part + (size_t)M_DV2 * stride, part + (size_t)M_DG2 * stride};
+    double s[2];
+    row_sums<2>(row, gridDim.x, false, sh, s);
+    dv2 = s[0];
+    dg2 = s[1];
+  } else {
+    dv2 = red[M_DV2];
+    dg2 = red[M_DG2];
+  }
+  if (blockIdx.x == 0) {
+    for (int L = 0; L < 3; ++L) {
+      const double* const row[2] = {lp.part[L] + (size_t)R_EXCESS_BOT * lp.stride[L],
+                                    lp.part[L] + (size_t)R_EXCESS_TOP * lp.stride[L]};
+      double s[2];
+      __syncthreads();
+      row_sums<2>(row, lp.ntiles[L], false, sh, s);
+      if (threadIdx.x == 0) { lr.r[L][R_EXCESS_BOT] = s[0]; lr.r[L][R_EXCESS_TOP] = s[1]; }
+    }
+    if (i == 0) md_step_finish(sc, dv2, dg2, wl_red, lr, ramp, a);
+  }
   if (i >= n) return;
-  const double dv2 = red[M_DV2], dg2 = red[M_DG2];
   const float st = (float)(dg2 > 0.0 ? sqrt(dv2 / dg2) : 0.0);
-  const double a = sc[PLACE3D_MS_A];
   const double a1 = 0.5 * (1.0 + sqrt(4.0 * a * a + 1.0));
   const float coef = (float)((a - 1.0) / a1);
   const float vx = v[i], vy = v[n + i];
@@ -282,32 +352,6 @@ __global__ void k_md_nesterov(int n, const float* __restrict__ size, const uint8
   clamp2(size, n, i, nx, ny, dx, dy);
   u[i] = ux; u[n + i] = uy;
   v[i] = nx; v[n + i] = ny;
-}
-
-struct LayerRed { const double* r[3]; double scale[3]; };   // excess slots and (2/d_z)/area per layer
-
-// wirelength totals and the layers' overflow at the evaluation point (slots 0..4 of out)
-__device__ __forceinline__ void md_metrics(const double* __restrict__ wl_red, const LayerRed& lr, double* out) {
-  out[PLACE3D_MD_WA] = wl_red[R_WA_BI];
-  out[PLACE3D_MD_HPWL] = wl_red[R_HPWL];
-  for (int L = 0; L < 3; ++L)
-    out[PLACE3D_MD_OVFL + L] = (lr.r[L][R_EXCESS_BOT] + lr.r[L][R_EXCESS_TOP]) * lr.scale[L];
-}
-
-__global__ void k_md_step_finish(double* __restrict__ sc, const double* __restrict__ red,
-                                 const double* __restrict__ wl_red, LayerRed lr, double ramp) {
-  if (threadIdx.x != 0) return;
-  const double dv2 = red[M_DV2], dg2 = red[M_DG2];
-  const double a = sc[PLACE3D_MS_A];
-  sc[PLACE3D_MS_STEP] = dg2 > 0.0 ? sqrt(dv2 / dg2) : 0.0;
-  sc[PLACE3D_MS_A] = 0.5 * (1.0 + sqrt(4.0 * a * a + 1.0));
-  for (int L = 0; L < 3; ++L) sc[PLACE3D_MS_LAMBDA + L] *= ramp;
-  sc[PLACE3D_MS_ITER] += 1.0;
-  md_metrics(wl_red, lr, sc + PLACE3D_MS_METRICS);
-  bool finite = isfinite(dv2) && isfinite(dg2);
-  for (int q = 0; q < 5; ++q) finite = finite && isfinite(sc[PLACE3D_MS_METRICS + q]);
-  for (int L = 0; L < 3; ++L) finite = finite && isfinite(sc[PLACE3D_MS_LAMBDA + L]);
-  if (!finite && sc[PLACE3D_MS_NONFINITE] == 0.0) sc[PLACE3D_MS_NONFINITE] = sc[PLACE3D_MS_ITER];
 }
 
 __global__ void k_md_eval_metrics(const double* __restrict__ wl_red, LayerRed lr, const double* __restrict__ en,
@@ -400,7 +444,6 @@ int md_layout(place3d_md2d_ctx* c, const place3d_md2d_problem& p, char* base, si
   c->wl_off = w.take<float>(4 * P + 1);
   c->wl_fixed = w.take<float>(3 * n);
   c->node_local = w.take<int32_t>(n);
-  c->xyz_wl = w.take<float>(3 * n);
   c->g_wl = w.take<float>(3 * n);
   for (int L = 0; L < 3; ++L) {
     const size_t m = p.n_layer[L];
@@ -418,9 +461,14 @@ int md_layout(place3d_md2d_ctx* c, const place3d_md2d_problem& p, char* base, si
   return PLACE3D_OK;
 }
 
-LayerGrads layer_grads(const place3d_md2d_ctx* c) {
-  LayerGrads lg;
-  for (int L = 0; L < 3; ++L) { lg.g[L] = c->g_l[L]; lg.n[L] = c->n_of[L]; }
+LayerGrads layer_grads(const place3d_md2d_ctx* c, bool shares = false) {
+  LayerGrads lg = {};
+  for (int L = 0; L < 3; ++L) {
+    lg.g[L] = c->g_l[L];
+    lg.n[L] = c->n_of[L];
+    const place3d_ctx* lc = c->lay[L];
+    if (shares) lg.cs[L] = CellShares{lc->cls, lc->cell_entry, lc->entry_out, lc->cell_scale};
+  }
   return lg;
 }
 
@@ -447,32 +495,62 @@ LayerRed layer_red(const place3d_md2d_ctx* c) {
   } while (0)
 
 // both objective parts at xy: the wirelength context's gradient into g_wl, each layer's 2D
-// field-gather gradient into g_l; with energy, also phi and U_3 of each layer into en[3]
-// The partial nets' wirelength and the three layers' density chains share nothing but the packed
-// positions: after the pack on s they run concurrently, each on its sub-context's side stream
-// (default priority), and s waits for all four before anything reads their results.
-int md_evaluate(place3d_md2d_ctx* c, const float* xy, hipStream_t s, double* en = nullptr) {
+// field-gather gradient into g_l; with energy, also phi and U_3 of each layer into en[3].
+// in_combine: the cells' density-gradient shares and the overflow partials are left to the step's
+// combine and move.
+// The partial nets' wirelength and the layers' density chains share nothing but the packed positions:
+// the wirelength runs on its sub-context's side stream (default priority) meanwhile, and s waits for
+// it before anything reads its results.  The three layers, each too small to fill the chip, share
+// their launches: 300k nodes on 512 x 512 181 us a step, against 199 to 253 with a stream for each
+// (as its streams share the hardware queues; the host then issues 30 launches and 10 event
+// operations in 160 to 230 us, here 14 and 4 in 85 to 105), 8k nodes on 64 x 64 78 against 160.
+int md_evaluate(place3d_md2d_ctx* c, const float* xy, hipStream_t s, double* en = nullptr, bool in_combine = false) {
   const place3d_md2d_problem& p = c->prob;
   const int n = p.n_nodes;
   hipLaunchKernelGGL(k_md_pack, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, xy, p.layer, c->node_local, c->zmid,
-                     c->xyz_wl, c->xyz_l[0], c->xyz_l[1], c->xyz_l[2], c->n_of[0], c->n_of[1], c->n_of[2]);
+                     c->wl->xyzp, c->xyz_l[0], c->xyz_l[1], c->xyz_l[2], c->n_of[0], c->n_of[1], c->n_of[2]);
   MD_HIP(c, hipGetLastError());
   MD_HIP(c, hipEventRecord(c->ev_fork, s));
   hipStream_t ws = c->wl->side;
   MD_HIP(c, hipStreamWaitEvent(ws, c->ev_fork, 0));
-  MD_SUB(c, c->wl, wirelength_eval(c->wl, c->xyz_wl, c->g_wl, 0, c->wl->red, nullptr, ws, false, nullptr, false));
+  MD_SUB(c, c->wl, wirelength_eval(c->wl, nullptr, c->g_wl, 0, c->wl->red, nullptr, ws, true, nullptr, false, false));
   MD_HIP(c, hipEventRecord(c->ev_done[0], ws));
+  const float *xyz[3], *cex[3], *cey[3], *cez[3];
+  const float* crho[3];
+  float *rho[3], *phi[3], *ex[3], *ey[3], *ez[3], *g[3];
+  double* red2[3];
   for (int L = 0; L < 3; ++L) {
     place3d_ctx* lc = c->lay[L];
-    hipStream_t ls = lc->side;
-    MD_HIP(c, hipStreamWaitEvent(ls, c->ev_fork, 0));
-    MD_SUB(c, lc, density_forward(lc, c->xyz_l[L], lc->rho, ls));
-    MD_SUB(c, lc, spectral_field(lc, lc->rho, en ? lc->phi : nullptr, lc->ex, lc->ey, nullptr, en ? en + L : nullptr, ls));
-    // grad = (4/d_z) grad_3: the layer's 2D field-gather gradient; E_z is read from a zero map
-    MD_SUB(c, lc, gather_bucketed(lc, c->xyz_l[L], lc->ex, lc->ey, lc->ez, -4.f / c->dz, c->g_l[L], 0, ls));
-    MD_HIP(c, hipEventRecord(c->ev_done[1 + L], ls));
+    xyz[L] = c->xyz_l[L];
+    crho[L] = rho[L] = lc->rho;
+    phi[L] = en ? lc->phi : nullptr;
+    cex[L] = ex[L] = lc->ex;
+    cey[L] = ey[L] = lc->ey;
+    ez[L] = nullptr;
+    cez[L] = lc->ez;                  // E_z is read from a zero map
+    g[L] = c->g_l[L];
+    red2[L] = lc->red2;
   }
-  for (auto& ev : c->ev_done) MD_HIP(c, hipStreamWaitEvent(s, ev, 0));
+  MD_SUB(c, c->lay[0], bucket_cells_many(c->lay, xyz, 3, s));
+  MD_SUB(c, c->lay[0], density_tiles_many(c->lay, xyz, rho, red2, 3, s, !in_combine));
+  if (c->lay[0]->fft.on && !en) {
+    for (auto* lc : c->lay) lc->field_xfold = 0;
+    MD_SUB(c, c->lay[0], field_fft_many(c->lay, crho, phi, ex, ey, ez, 3, s));
+  } else {
+    // the other solves are many small launches: two of them on the layers' side streams
+    MD_HIP(c, hipEventRecord(c->ev_fork, s));
+    for (int L = 0; L < 3; ++L) {
+      place3d_ctx* lc = c->lay[L];
+      hipStream_t ls = L < 2 ? lc->side : s;
+      if (L < 2) MD_HIP(c, hipStreamWaitEvent(ls, c->ev_fork, 0));
+      MD_SUB(c, lc, spectral_field(lc, rho[L], phi[L], ex[L], ey[L], nullptr, en ? en + L : nullptr, ls));
+      if (L < 2) MD_HIP(c, hipEventRecord(c->ev_done[1 + L], ls));
+    }
+    for (int L = 0; L < 2; ++L) MD_HIP(c, hipStreamWaitEvent(s, c->ev_done[1 + L], 0));
+  }
+  // grad = (4/d_z) grad_3: the layer's 2D field-gather gradient
+  MD_SUB(c, c->lay[0], gather_bucketed_many(c->lay, xyz, cex, cey, cez, -4.f / c->dz, g, 0, 3, s, !in_combine, false));
+  MD_HIP(c, hipStreamWaitEvent(s, c->ev_done[0], 0));
   return PLACE3D_OK;
 }
 
@@ -680,7 +758,7 @@ int32_t place3d_md2d_gp_init(place3d_md2d_ctx* c, place3d_md2d_state* st, const 
   MD_HIP(c, hipGetLastError());
   hipLaunchKernelGGL(k_md_combine, dim3(nb), dim3(256), 0, s, n, p.size, p.kind, p.layer, c->node_local,
                      c->wl->npins, st->v, st->v_prev, c->g_wl, layer_grads(c), st->scalars, 0, st->g_prev, c->part,
-                     c->part_stride);
+                     c->part_stride, nullptr);
   MD_HIP(c, hipGetLastError());
   if (int rc = md_reduce(c, M_GMAX, 1, true, s)) return rc;
   hipLaunchKernelGGL(k_md_bootstrap, dim3(nb), dim3(256), 0, s, n, p.size, p.kind, dx, dy, wb, st->v, st->g_prev,
@@ -689,7 +767,7 @@ int32_t place3d_md2d_gp_init(place3d_md2d_ctx* c, place3d_md2d_state* st, const 
   if (int rc = md_evaluate(c, st->v_prev, s)) return rc;
   hipLaunchKernelGGL(k_md_combine, dim3(nb), dim3(256), 0, s, n, p.size, p.kind, p.layer, c->node_local,
                      c->wl->npins, st->v_prev, st->v_prev, c->g_wl, layer_grads(c), st->scalars, 0, st->g_prev,
-                     c->part, c->part_stride);
+                     c->part, c->part_stride, nullptr);
   MD_HIP(c, hipGetLastError());
   return PLACE3D_OK;
 }
@@ -702,17 +780,25 @@ int32_t place3d_md2d_step(place3d_md2d_ctx* c, place3d_md2d_state* st, void* str
   const int n = p.n_nodes;
   const unsigned nb = blocks_for(n, 256);
   const float dx = (float)p.die_x, dy = (float)p.die_y;
-  if (int rc = md_evaluate(c, st->v, s)) return rc;
+  if (int rc = md_evaluate(c, st->v, s, nullptr, true)) return rc;
   hipLaunchKernelGGL(k_md_combine, dim3(nb), dim3(256), 0, s, n, p.size, p.kind, p.layer, c->node_local,
-                     c->wl->npins, st->v, st->v_prev, c->g_wl, layer_grads(c), st->scalars, 1, st->g_prev, c->part,
-                     c->part_stride);
+                     c->wl->npins, st->v, st->v_prev, c->g_wl, layer_grads(c, true), st->scalars, 1, st->g_prev, c->part,
+                     c->part_stride, c->red + M_A_PREV);
   MD_HIP(c, hipGetLastError());
-  if (int rc = md_reduce(c, M_DV2, 2, false, s)) return rc;
-  hipLaunchKernelGGL(k_md_nesterov, dim3(nb), dim3(256), 0, s, n, p.size, p.kind, dx, dy, st->scalars, c->red, st->u,
-                     st->v, st->v_prev, st->g_prev);
-  MD_HIP(c, hipGetLastError());
-  hipLaunchKernelGGL(k_md_step_finish, dim3(1), dim3(64), 0, s, st->scalars, c->red, c->wl->red, layer_red(c),
-                     p.lambda_ramp);
+  // the move sums the norms itself (300k nodes, 1172 partials: 183.6 -> 181.3 us a step) until that
+  // is several rounds of loads
+  const bool own = (int)nb <= kOwnNorms;
+  if (!own)
+    if (int rc = md_reduce(c, M_DV2, 2, false, s)) return rc;
+  LayerParts lp;
+  for (int L = 0; L < 3; ++L) {
+    lp.part[L] = c->lay[L]->part;
+    lp.stride[L] = c->lay[L]->part_stride;
+    lp.ntiles[L] = c->lay[L]->tg.ntiles;
+  }
+  hipLaunchKernelGGL(own ? k_md_nesterov<true> : k_md_nesterov<false>, dim3(nb), dim3(256), 0, s, n, p.size, p.kind, dx,
+                     dy, st->scalars, c->red, st->u, st->v, st->v_prev, st->g_prev, c->part, c->part_stride, c->wl->red,
+                     layer_red(c), lp, p.lambda_ramp);
   MD_HIP(c, hipGetLastError());
   return PLACE3D_OK;
 }

@@ -276,10 +276,15 @@ __device__ __forceinline__ float layer_ref(const float* __restrict__ plane, int 
   return v * (1.f / 64.f);
 }
 
+// the maps of a launch (of one problem, or of the layers of a multi-die one)
+struct FftMapIn { const float* p[kMaxMany]; };
+struct FftMapOut { float* p[kMaxMany]; };
+
 // x forward: rows (z, y), two per FFT, to t[x frequency][z][y], with the x normalisation
 template <int N>
-__global__ __launch_bounds__(x_threads<N>()) void k_fft_x(const float* __restrict__ rho, int ny, int nz,
-                                                               FftTabs tb, float* __restrict__ out) {
+__global__ __launch_bounds__(x_threads<N>()) void k_fft_x(FftMapIn maps, int ny, int nz, FftTabs tb, FftMapOut outs) {
+  const float* __restrict__ rho = maps.p[blockIdx.y];
+  float* __restrict__ out = outs.p[blockIdx.y];
   constexpr int E = Plan<N>::E, T = lanes_of<N>(), G = x_groups<N>(), RW = 2 * G;
   constexpr int kBuf = G * buf_of<N>() * 2, kTileF = N * (RW + 1);      // floats
   __shared__ __attribute__((aligned(16))) float L[kBuf > kTileF ? kBuf : kTileF];
@@ -342,11 +347,11 @@ __global__ __launch_bounds__(x_threads<N>()) void k_fft_x(const float* __restric
 
 struct FftYArgs {
   int nx;
-  const float* rho;              // the map, for its layers' references
+  FftMapIn rho;                  // the map, for its layers' references
   float px2, py, py2, pz2;       // (pi / length)^2, pi / d_y
   const float* zmat;
-  const float* t;                // [nx][nz][N]
-  float *vg, *vh;                // [nx / 2][N][nz][2], either may be null
+  FftMapIn t;                    // [nx][nz][N]
+  FftMapOut vg, vh;              // [nx / 2][N][nz][2], either may be null
 };
 
 // 1 / w2 to half an ulp: the hardware reciprocal and one Newton step
@@ -375,7 +380,7 @@ __global__ __launch_bounds__((y_threads<N, NZ>()), 2) void k_fft_y(FftYArgs g, F
   cf* buf = L + f * B;
   {
     cf x[E];
-    const float* r0 = g.t + ((size_t)kx * NZ + 2 * r) * N;
+    const float* r0 = g.t.p[blockIdx.y] + ((size_t)kx * NZ + 2 * r) * N;
     const float* r1 = r0 + N;
 #pragma unroll
     for (int s = 0; s < E; ++s) {
@@ -419,7 +424,7 @@ __global__ __launch_bounds__((y_threads<N, NZ>()), 2) void k_fft_y(FftYArgs g, F
     }
     cf z0 = zb[0];
     if (kx2 == pr) {                                     // the workgroup of x frequency 0
-      const float* plane = g.rho + (size_t)(2 * p) * g.nx * N;
+      const float* plane = g.rho.p[blockIdx.y] + (size_t)(2 * p) * g.nx * N;
       const float c0 = layer_ref(plane, g.nx, N), c1 = layer_ref(plane + (size_t)g.nx * N, g.nx, N);
       if (kx == 0) z0 = {z0.x + (float)N * c0, z0.y + (float)N * c1};
     }
@@ -465,7 +470,7 @@ __global__ __launch_bounds__((y_threads<N, NZ>()), 2) void k_fft_y(FftYArgs g, F
   const float d0 = buf[N].x, d1 = buf[N + 1].x;
 #pragma unroll 1
   for (int sine = 0; sine < 2; ++sine) {
-    float* v = sine ? g.vh : g.vg;
+    float* v = sine ? g.vh.p[blockIdx.y] : g.vg.p[blockIdx.y];
     if (!v) continue;
     // rows kx and kx + 1 as g0 + i g1, real and imaginary parts swapped (an inverse FFT)
     const PairW<N> pw(tb.wy, t);
@@ -506,7 +511,7 @@ __global__ __launch_bounds__((y_threads<N, NZ>()), 2) void k_fft_y(FftYArgs g, F
 
 // one output map of the x inverse: its inverse-y source, z matrix, x series and destination
 struct FftXJob { const float* v; const float* zm; int sine; float* out; };
-struct FftXArgs { int ny; float px; int vec; FftXJob job[4]; };
+struct FftXArgs { int ny; float px; int vec; FftXJob job[4 * kMaxMany]; };
 
 // z mixing and x inverse of four rows y of a map (blockIdx.y), one group of lanes each, two layers
 // per FFT.  The rows' coefficients are read as the y pass wrote them, one run of 128 bytes (NZ = 4)
@@ -669,40 +674,55 @@ int build_fft(place3d_ctx* c, hipStream_t s) {
 }
 
 int field_fft(place3d_ctx* c, const float* rho, float* phi, float* ex, float* ey, float* ez, hipStream_t s) {
-  const Geom& g = c->g;
-  const place3d_problem& p = c->prob;
+  return field_fft_many(&c, &rho, &phi, &ex, &ey, &ez, 1, s);
+}
+
+int field_fft_many(place3d_ctx* const* c, const float* const* rho, float* const* phi, float* const* ex, float* const* ey,
+                   float* const* ez, int nb, hipStream_t s) {
+  const Geom& g = c[0]->g;
+  const place3d_problem& p = c[0]->prob;
   const int nx = g.nx, ny = g.ny, nz = g.nz;
-  const FftTabs tb = tabs_of(c);
+  const FftTabs tb = tabs_of(c[0]);
   const double dz = p.nz * 0.5 * (p.die_x / p.nx + p.die_y / p.ny);
   const double px = M_PI / p.die_x, py = M_PI / p.die_y, pz = M_PI / dz;
-  ProfScope prof_(c, PLACE3D_STAGE_GEMM, s);
+  ProfScope prof_(c[0], PLACE3D_STAGE_GEMM, s);
   prof_.launches = 3;
+  // every context asks for the same outputs
+  const bool need_g = phi[0] || ex[0] || ez[0], need_h = ey[0] != nullptr;
+  FftMapIn in{}, t_in{};
+  FftMapOut t_out{}, vg{}, vh{};
+  for (int i = 0; i < nb; ++i) {
+    in.p[i] = rho[i];
+    t_in.p[i] = t_out.p[i] = c[i]->map_t;
+    vg.p[i] = need_g ? c[i]->map_vg : nullptr;
+    vh.p[i] = need_h ? c[i]->map_vh : nullptr;
+  }
   with_side(nx, [&](auto side) {
     constexpr int N = decltype(side)::value;
-    hipLaunchKernelGGL((k_fft_x<N>), dim3(nz * ny / (2 * x_groups<N>())), dim3(x_threads<N>()), 0, s, rho, ny, nz, tb,
-                       c->map_t);
+    hipLaunchKernelGGL((k_fft_x<N>), dim3(nz * ny / (2 * x_groups<N>()), nb), dim3(x_threads<N>()), 0, s, in, ny, nz, tb,
+                       t_out);
   });
-  P3D_LAUNCH(c, "k_fft_x");
-  const bool need_g = phi || ex || ez, need_h = ey != nullptr;
+  P3D_LAUNCH(c[0], "k_fft_x");
   if (!need_g && !need_h) return PLACE3D_OK;
-  const FftYArgs ya{nx, rho, (float)(px * px), (float)py, (float)(py * py), (float)(pz * pz), c->dct.zmat, c->map_t,
-                    need_g ? c->map_vg : nullptr, need_h ? c->map_vh : nullptr};
+  const FftYArgs ya{nx, in, (float)(px * px), (float)py, (float)(py * py), (float)(pz * pz), c[0]->dct.zmat, t_in, vg, vh};
   with_side(ny, [&](auto side) {
     constexpr int N = decltype(side)::value;
     const int pairs = nx / 2;
-    if (nz == 2) hipLaunchKernelGGL((k_fft_y<N, 2>), dim3(pairs / y_pairs<N, 2>()), dim3(y_threads<N, 2>()), 0, s, ya, tb);
-    else hipLaunchKernelGGL((k_fft_y<N, 4>), dim3(pairs / y_pairs<N, 4>()), dim3(y_threads<N, 4>()), 0, s, ya, tb);
+    if (nz == 2) hipLaunchKernelGGL((k_fft_y<N, 2>), dim3(pairs / y_pairs<N, 2>(), nb), dim3(y_threads<N, 2>()), 0, s, ya, tb);
+    else hipLaunchKernelGGL((k_fft_y<N, 4>), dim3(pairs / y_pairs<N, 4>(), nb), dim3(y_threads<N, 4>()), 0, s, ya, tb);
   });
-  P3D_LAUNCH(c, "k_fft_y");
-  const float* Gz = c->dct.zmat + kMaxNz * kMaxNz;
-  const float* Hz = c->dct.zmat + 2 * kMaxNz * kMaxNz;
+  P3D_LAUNCH(c[0], "k_fft_y");
+  const float* Gz = c[0]->dct.zmat + kMaxNz * kMaxNz;
+  const float* Hz = c[0]->dct.zmat + 2 * kMaxNz * kMaxNz;
   FftXArgs xa{};
   xa.ny = ny; xa.px = (float)px;
   int nj = 0;
-  if (ex) xa.job[nj++] = {c->map_vg, Gz, 1, ex};
-  if (ez) xa.job[nj++] = {c->map_vg, Hz, 0, ez};
-  if (phi) xa.job[nj++] = {c->map_vg, Gz, 0, phi};
-  if (ey) xa.job[nj++] = {c->map_vh, Gz, 0, ey};
+  for (int i = 0; i < nb; ++i) {
+    if (ex[i]) xa.job[nj++] = {vg.p[i], Gz, 1, ex[i]};
+    if (ez[i]) xa.job[nj++] = {vg.p[i], Hz, 0, ez[i]};
+    if (phi[i]) xa.job[nj++] = {vg.p[i], Gz, 0, phi[i]};
+    if (ey[i]) xa.job[nj++] = {vh.p[i], Gz, 0, ey[i]};
+  }
   uintptr_t at = 0;
   for (int i = 0; i < nj; ++i) at |= reinterpret_cast<uintptr_t>(xa.job[i].out);
   xa.vec = (at & 15) == 0;
@@ -712,7 +732,7 @@ int field_fft(place3d_ctx* c, const float* rho, float* phi, float* ex, float* ey
     if (nz == 2) hipLaunchKernelGGL((k_fft_ix<N, 2>), grid, dim3(ix_threads<N>()), 0, s, xa, tb);
     else hipLaunchKernelGGL((k_fft_ix<N, 4>), grid, dim3(ix_threads<N>()), 0, s, xa, tb);
   });
-  P3D_LAUNCH(c, "k_fft_ix");
+  P3D_LAUNCH(c[0], "k_fft_ix");
   return PLACE3D_OK;
 }
 

@@ -118,50 +118,17 @@ __global__ void k_l1_parts(Geom g, const uint8_t* __restrict__ kind, const float
 // g = (gw + lambda gd) / H.  Mode 0 (init): write g to `gout` and track max|g|.  Mode 1 (step):
 // accumulate |v - v_prev|^2 and |g - g_prev|^2, store g over g_prev, and the movable charge
 // per die without fillers (overflow denominators).  A z-held instance's z-gradient is zero.
-// Cell density gradients held as per-(cell, tile) shares (CellShares.entry != nullptr, cell-major
-// [q][n], q < the cell's entry count read from its packed tile range) are summed here, in the
-// order the separate combine pass uses, instead of being materialised first.
-struct CellShares {
-  const uint8_t* cls;
-  const int32_t* cell_entry;
-  const float4* entry;
-  float scale;
+// The cells' density-gradient shares are summed here instead of being materialised first.
+// The wirelength z-gradient not yet scaled (gz != nullptr; as k_wl_finish_z makes it): scale * fda + gz
+struct WlZ {
+  const float *gz, *fda;
+  const double* red;
 };
-
-// cls and packed: the instance's density class and packed tile range (loaded by the caller with
-// its other operands); a cell's up to four shares are loaded together and summed in q order
-__device__ __forceinline__ void density_grad_of(const CellShares& cs, const float* __restrict__ gd, int n, int i,
-                                                uint8_t cls, int packed, float (&d)[3]) {
-  if (!cs.entry || cls == kClsLarge) {
-    for (int a = 0; a < 3; ++a) d[a] = gd[a * n + i];
-    return;
-  }
-  float sx = 0.f, sy = 0.f, sz = 0.f;
-  if (cls == kClsCell) {
-    // the cell's entry count from its packed tile range; its shares are cell-major [q][n]
-    // (a bucketed cell has 1, 2 or 4 entries: its tile range is 1 or 2 tiles per axis)
-    const int cnt = packed < 0 ? 0 : (1 + ((packed >> 24) & 1)) * (1 + ((packed >> 25) & 1));
-    // All four loads are issued together: an absent share's load re-reads share 0 (the same
-    // cache line) and counts as zero, which leaves the sum in q order unchanged.
-    const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    const size_t i1 = cnt > 1 ? (size_t)n + i : (size_t)i;
-    const size_t i2 = cnt > 2 ? 2 * (size_t)n + i : (size_t)i, i3 = cnt > 2 ? 3 * (size_t)n + i : (size_t)i;
-    const float4 r0 = cs.entry[i], r1 = cs.entry[i1], r2 = cs.entry[i2], r3 = cs.entry[i3];
-    const float4 v0 = r0, v1 = cnt > 1 ? r1 : z4, v2 = cnt > 2 ? r2 : z4, v3 = cnt > 2 ? r3 : z4;
-    if (cnt > 0) {
-      sx = ((v0.x + v1.x) + v2.x) + v3.x;
-      sy = ((v0.y + v1.y) + v2.y) + v3.y;
-      sz = ((v0.z + v1.z) + v2.z) + v3.z;
-    }
-    sx *= cs.scale; sy *= cs.scale; sz *= cs.scale;
-  }
-  d[0] = sx; d[1] = sy; d[2] = sz;
-}
 
 __global__ void k_combine(Geom g, const float* __restrict__ size, const uint8_t* __restrict__ kind,
                           const float* __restrict__ npins, const float* __restrict__ v,
                           const float* __restrict__ v_prev, const float* __restrict__ gw,
-                          const float* __restrict__ gd, CellShares cs, const double* __restrict__ lam_ptr, int lam_slot,
+                          WlZ wz, const float* __restrict__ gd, CellShares cs, const double* __restrict__ lam_ptr, int lam_slot,
                           int mode_pre, int mode, float* __restrict__ gout, double* __restrict__ part, int stride,
                           const double* __restrict__ a_src, double* __restrict__ a_copy) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -179,9 +146,10 @@ __global__ void k_combine(Geom g, const float* __restrict__ size, const uint8_t*
     float wv[3], vv[3], vp[3] = {0.f, 0.f, 0.f}, go[3] = {0.f, 0.f, 0.f};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      wv[a] = gw[a * n + i];
+      if (a < 2 || !wz.gz) wv[a] = gw[a * n + i];
       vv[a] = v[a * n + i];
     }
+    if (wz.gz) wv[2] = (float)fda_scale(wz.red) * wz.fda[i] + wz.gz[i];
     if (mode == 1) {
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
@@ -284,18 +252,45 @@ __device__ void finish_scalars(double* __restrict__ sc, const double* __restrict
   if (!finite && sc[PLACE3D_S_NONFINITE] == 0.0) sc[PLACE3D_S_NONFINITE] = sc[PLACE3D_S_ITER];
 }
 
-// the Nesterov move; g (the new preconditioned gradient) sits in g_prev
-__global__ void k_nesterov(Geom g, const float* __restrict__ size, const uint8_t* __restrict__ kind,
-                           double* __restrict__ sc, const double* __restrict__ red, double ramp,
-                           float* __restrict__ u, float* __restrict__ v, float* __restrict__ v_prev,
-                           const float* __restrict__ gk) {
+// the Nesterov move; g (the new preconditioned gradient) sits in g_prev.  kSum: every workgroup
+// sums the combine's norms from its partials, and the first one also the overflow's (reductions
+// that a launch between the combine and the move has made otherwise).
+template <bool kSum>
+__global__ __launch_bounds__(256) void k_nesterov(Geom g, const float* __restrict__ size,
+                                                  const uint8_t* __restrict__ kind, double* __restrict__ sc, double* red,
+                                                  double ramp, float* __restrict__ u, float* __restrict__ v,
+                                                  float* __restrict__ v_prev, const float* __restrict__ gk,
+                                                  const double* __restrict__ part, int stride, int ntiles) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   // a_k from the combine's copy: thread 0 writes a_{k+1} (and the other scalars) meanwhile
   const double a = red[R_A_PREV];
+  double dv2, dg2;
+  if constexpr (kSum) {
+    __shared__ double sh[2][256];
+    double s[2];
+    auto rows = [&](int slot, int nparts) {
+      const double* const row[2] = {part + (size_t)slot * stride, part + (size_t)(slot + 1) * stride};
+      row_sums<2>(row, nparts, false, sh, s);
+    };
+    if (blockIdx.x == 0) {
+      rows(R_Q_BOT, gridDim.x);
+      if (threadIdx.x == 0) { red[R_Q_BOT] = s[0]; red[R_Q_TOP] = s[1]; }
+      __syncthreads();
+      rows(R_EXCESS_BOT, ntiles);
+      if (threadIdx.x == 0) { red[R_EXCESS_BOT] = s[0]; red[R_EXCESS_TOP] = s[1]; }
+      __syncthreads();
+    }
+    rows(R_DV2, gridDim.x);
+    dv2 = s[0];
+    dg2 = s[1];
+    if (i == 0) { red[R_DV2] = dv2; red[R_DG2] = dg2; }
+  } else {
+    dv2 = red[R_DV2];
+    dg2 = red[R_DG2];
+  }
   if (i == 0) finish_scalars(sc, red, ramp, a);
   if (i >= g.n) return;
   const int n = g.n;
-  const double dv2 = red[R_DV2], dg2 = red[R_DG2];
   const double step = dg2 > 0.0 ? sqrt(dv2 / dg2) : 0.0;
   const double a1 = 0.5 * (1.0 + sqrt(4.0 * a * a + 1.0));
   const float coef = (float)((a - 1.0) / a1);
@@ -321,10 +316,10 @@ __global__ void k_nesterov(Geom g, const float* __restrict__ size, const uint8_t
 
 // wirelength and density gradients at xyz into gw and gd (both [3][n]); reductions into red.
 // The cells are bucketed once and the buckets serve the density map and its gradient.
-// cells_in_combine: leave the cells' density-gradient shares for k_combine to sum
-// defer_excess: leave the overflow slots' partials for the caller's final reduction
+// in_combine: leave the cells' density-gradient shares for k_combine to sum, the wirelength
+// z-gradient for it to scale, and the overflow slots' partials for the caller's final reduction
 int eval_parts(place3d_ctx* c, const float* xyz, float* gw, float* gd, double* red, hipStream_t s,
-               bool cells_in_combine = false, bool defer_excess = false) {
+               bool in_combine = false) {
   int rc;
   // every reduction slot read after an evaluation is written by it (the energy slot, read only
   // for the scalars, stays as gp_init zeroed it in the field-gather form)
@@ -340,19 +335,19 @@ int eval_parts(place3d_ctx* c, const float* xyz, float* gw, float* gd, double* r
   if (fork_after_scatter && (rc = bucket_cells(c, xyz, s, 2))) return rc;
   P3D_HIP(c, hipEventRecord(c->ev_fork, s));
   P3D_HIP(c, hipStreamWaitEvent(c->side, c->ev_fork, 0));
-  if ((rc = wirelength_eval(c, xyz, gw, 0, red, nullptr, c->side, true))) return rc;
+  if ((rc = wirelength_eval(c, xyz, gw, 0, red, nullptr, c->side, true, nullptr, true, !in_combine))) return rc;
   P3D_HIP(c, hipEventRecord(c->ev_join, c->side));
   if (!fork_after_scatter && (rc = bucket_cells(c, xyz, s, 2))) return rc;
-  if ((rc = density_tiles(c, xyz, c->rho, red, s, !defer_excess))) return rc;
+  if ((rc = density_tiles(c, xyz, c->rho, red, s, !in_combine))) return rc;
   if (c->prob.dgrad == PLACE3D_DGRAD_FIELD) {
     // the float32 form's field stays x-folded for the gather, which unfolds it while staging its
     // tiles (the split-bf16 chain returns it unfolded)
     if ((rc = spectral_field(c, c->rho, nullptr, c->ex, c->ey, c->ez, nullptr, s, large_in_tiles(c)))) return rc;
-    if ((rc = gather_bucketed(c, xyz, c->ex, c->ey, c->ez, -1.f, gd, 0, s, !cells_in_combine, c->field_xfold != 0)))
+    if ((rc = gather_bucketed(c, xyz, c->ex, c->ey, c->ez, -1.f, gd, 0, s, !in_combine, c->field_xfold != 0)))
       return rc;
   } else {
     if ((rc = spectral_field(c, c->rho, c->phi, nullptr, nullptr, nullptr, red + R_ENERGY, s))) return rc;
-    if ((rc = adjoint_bucketed(c, xyz, c->phi, c->g.vol_bin, gd, 0, s, !cells_in_combine))) return rc;
+    if ((rc = adjoint_bucketed(c, xyz, c->phi, c->g.vol_bin, gd, 0, s, !in_combine))) return rc;
   }
   P3D_HIP(c, hipStreamWaitEvent(s, c->ev_join, 0));
   return PLACE3D_OK;
@@ -405,7 +400,7 @@ extern "C" int32_t place3d_gp_init(place3d_ctx* c, place3d_state* st, const floa
   {
     ProfScope prof_(c, PLACE3D_STAGE_UPDATE, s);
     hipLaunchKernelGGL(k_combine, dim3(nb), dim3(256), 0, s, g, p.size, p.kind, c->npins, st->v, st->v_prev,
-                     c->gw, c->den_grad, CellShares{}, st->scalars, (int)PLACE3D_S_LAMBDA, p.precond, 0, st->g_prev,
+                     c->gw, WlZ{}, c->den_grad, CellShares{}, st->scalars, (int)PLACE3D_S_LAMBDA, p.precond, 0, st->g_prev,
                      c->part, c->part_stride, nullptr, nullptr);
     P3D_LAUNCH(c, "k_combine(init)");
   }
@@ -421,7 +416,7 @@ extern "C" int32_t place3d_gp_init(place3d_ctx* c, place3d_state* st, const floa
   {
     ProfScope prof_(c, PLACE3D_STAGE_UPDATE, s);
     hipLaunchKernelGGL(k_combine, dim3(nb), dim3(256), 0, s, g, p.size, p.kind, c->npins, st->v_prev, st->v_prev,
-                     c->gw, c->den_grad, CellShares{}, st->scalars, (int)PLACE3D_S_LAMBDA, p.precond, 0, st->g_prev,
+                     c->gw, WlZ{}, c->den_grad, CellShares{}, st->scalars, (int)PLACE3D_S_LAMBDA, p.precond, 0, st->g_prev,
                      c->part, c->part_stride, nullptr, nullptr);
     P3D_LAUNCH(c, "k_combine(init2)");
   }
@@ -436,24 +431,26 @@ extern "C" int32_t place3d_step(place3d_ctx* c, place3d_state* st, void* stream)
   const place3d_problem& p = c->prob;
   const unsigned nb = blocks_for(g.n, 256);
   int rc;
-  if ((rc = eval_parts(c, st->v, c->gw, c->den_grad, c->red, s, true, true))) return rc;
+  if ((rc = eval_parts(c, st->v, c->gw, c->den_grad, c->red, s, true))) return rc;
   {
     ProfScope prof_(c, PLACE3D_STAGE_UPDATE, s);
     const CellShares cs{c->cls, c->cell_entry, c->entry_out, c->cell_scale};
     hipLaunchKernelGGL(k_combine, dim3(nb), dim3(256), 0, s, g, p.size, p.kind, c->npins, st->v, st->v_prev,
-                     c->gw, c->den_grad, cs, st->scalars, (int)PLACE3D_S_LAMBDA, p.precond, 1, st->g_prev,
+                     c->gw, WlZ{c->wl_gzwa, c->wl_fda, c->red}, c->den_grad, cs, st->scalars, (int)PLACE3D_S_LAMBDA, p.precond, 1, st->g_prev,
                      c->part, c->part_stride, st->scalars + PLACE3D_S_A, c->red + R_A_PREV);
     P3D_LAUNCH(c, "k_combine");
   }
-  // the step's partials and the density pass's overflow partials, in one launch
-  if ((rc = reduce_final2(c, R_DV2, 4, (int)nb, c->red + R_DV2, R_EXCESS_BOT, 2, c->tg.ntiles, c->red + R_EXCESS_BOT,
-                          s)))
+  // the step's partials and the density pass's overflow partials: by the move, or in one launch
+  const bool own = (int)nb <= kOwnSumParts;
+  if (!own && (rc = reduce_final2(c, c->part, c->part_stride, R_DV2, 4, (int)nb, c->red + R_DV2, R_EXCESS_BOT, 2,
+                                  c->tg.ntiles, c->red + R_EXCESS_BOT, s)))
     return rc;
   {
     // the move, and the step's scalars from its first thread
     ProfScope prof_(c, PLACE3D_STAGE_UPDATE, s);
-    hipLaunchKernelGGL(k_nesterov, dim3(nb), dim3(256), 0, s, g, p.size, p.kind, st->scalars, c->red, p.lambda_ramp,
-                     st->u, st->v, st->v_prev, st->g_prev);
+    hipLaunchKernelGGL(own ? k_nesterov<true> : k_nesterov<false>, dim3(nb), dim3(256), 0, s, g, p.size, p.kind,
+                       st->scalars, c->red, p.lambda_ramp, st->u, st->v, st->v_prev, st->g_prev, c->part, c->part_stride,
+                       c->tg.ntiles);
     P3D_LAUNCH(c, "k_nesterov");
   }
   return PLACE3D_OK;

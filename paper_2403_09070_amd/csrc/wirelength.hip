@@ -724,18 +724,13 @@ __global__ void k_wl_gather(int n, int nlight, const int32_t* __restrict__ heavy
   }
 }
 
-__device__ __forceinline__ double fda_scale(const double* red) {
-  const double nf = red[R_NORM_FDA];
-  return nf > 0.0 ? (red[R_NORM_X] + red[R_NORM_Y]) / (2.0 * nf) : 0.0;
-}
-
 // grad_z (+)= sc (scale * fda + gz_wa), scale = (|g_x|_1 + |g_y|_1) / (2 |fda|_1); without the FDA
 // term (with_fda == 0) grad_z (+)= sc gz_wa, the derivative of the model's value
 __global__ void k_wl_finish_z(int n, const float* __restrict__ gz_wa, const float* __restrict__ fda,
                               const double* __restrict__ red, int with_fda, const double* __restrict__ dscale,
                               float* __restrict__ grad, int accumulate, double* __restrict__ metrics) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const float scale = (float)fda_scale(red);
+  const float scale = with_fda ? (float)fda_scale(red) : 0.f;
   if (i < n) {
     const float sc = dscale ? (float)dscale[0] : 1.f;
     const float v = sc * (with_fda ? scale * fda[i] + gz_wa[i] : gz_wa[i]);
@@ -831,7 +826,7 @@ __global__ __launch_bounds__(256) void k_fda_shared(const int32_t* __restrict__ 
 }  // namespace
 
 int wirelength_eval(place3d_ctx* c, const float* xyz, float* grad, int accumulate, double* red,
-                    double* metrics, hipStream_t s, bool packed, const double* dscale, bool with_fda) {
+                    double* metrics, hipStream_t s, bool packed, const double* dscale, bool with_fda, bool finish_z) {
   const Geom& g = c->g;
   const place3d_problem& p = c->prob;
   const bool comp = p.precision == PLACE3D_BF16X3;      // the precision form compensates the sums
@@ -848,7 +843,9 @@ int wirelength_eval(place3d_ctx* c, const float* xyz, float* grad, int accumulat
                        (float)p.alpha, c->xyzp, c->s_net_start, c->s_pin_node, c->s_off, c->slot_pos, c->pin_out,
                        c->classes, c->wa_block_order, c->part, c->part_stride);
     P3D_LAUNCH(c, "k_wl_nets");
-    if (p.options & PLACE3D_OPT_FDA_VANILLA) {
+    if (!with_fda) {
+      // the FDA values are not read
+    } else if (p.options & PLACE3D_OPT_FDA_VANILLA) {
       const int nslots = p.n_pins, nnets = c->classes.net_begin[kNumClasses];
       hipLaunchKernelGGL(k_fda_vanilla, dim3(blocks_for(nslots, 256)), dim3(256), 0, s, nslots, nnets, g.half_dz,
                          4.f / g.dz, c->xyzp, c->s_net_start, c->s_pin_node, c->s_off, c->slot_pos, c->pin_out);
@@ -860,7 +857,6 @@ int wirelength_eval(place3d_ctx* c, const float* xyz, float* grad, int accumulat
       P3D_LAUNCH(c, "k_fda_shared");
     }
   }
-  if ((rc = reduce_final(c, R_WA_BI, 5, c->n_wa_blocks, false, red + R_WA_BI, s))) return rc;
   const unsigned nlight = blocks_for(g.n, 256);
   const unsigned nb = nlight + (unsigned)((c->n_heavy + 3) / 4);
   {
@@ -870,8 +866,11 @@ int wirelength_eval(place3d_ctx* c, const float* xyz, float* grad, int accumulat
                        c->part_stride);
     P3D_LAUNCH(c, "k_wl_gather");
   }
-  if ((rc = reduce_final(c, R_NORM_X, 3, (int)nb, false, red + R_NORM_X, s))) return rc;
-  {
+  // the net totals and, where the FDA is scaled by them, the gradient norms, in one launch
+  if (red && (rc = reduce_final2(c, c->part, c->part_stride, R_WA_BI, 5, c->n_wa_blocks, red + R_WA_BI, R_NORM_X,
+                                 with_fda ? 3 : 0, (int)nb, red + R_NORM_X, s)))
+    return rc;
+  if (finish_z) {
     ProfScope prof_(c, PLACE3D_STAGE_WL_NODES, s);
     hipLaunchKernelGGL(k_wl_finish_z, dim3(blocks_for(std::max(g.n, (int)PLACE3D_NMETRICS), 256)), dim3(256), 0, s,
                        g.n, c->wl_gzwa, c->wl_fda, red, with_fda ? 1 : 0, dscale, grad, accumulate, metrics);
@@ -900,9 +899,11 @@ int wirelength_value(place3d_ctx* c, const float* xyz, double* metrics, hipStrea
                        c->classes, c->wa_block_order, part, stride);
     P3D_LAUNCH(c, "k_wl_nets(value)");
   }
-  // the five net totals straight into the metrics; the gradient norms are not computed here
-  if ((rc = launch_zero_f64(c, metrics, PLACE3D_NMETRICS, s))) return rc;
-  return reduce_final_in(c, part, stride, R_WA_BI, 5, c->n_wa_blocks, false, metrics + PLACE3D_M_WA_BI, s);
+  // the five net totals straight into the metrics, the others 0 (sums of no partials): the gradient
+  // norms are not computed here
+  static_assert(PLACE3D_M_WA_BI == 0 && PLACE3D_M_NORM_X == 5, "totals come first");
+  return reduce_final2(c, part, stride, R_WA_BI, 5, c->n_wa_blocks, metrics, R_WA_BI, PLACE3D_NMETRICS - 5, 0,
+                       metrics + 5, s);
 }
 
 // ---- the value call without workspace scratch (place3d_wl_value_static)
