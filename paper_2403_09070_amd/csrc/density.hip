@@ -311,7 +311,12 @@ __device__ __forceinline__ void large_record(const Geom& g, const float* __restr
                                              const int32_t* __restrict__ large, int j, float4* __restrict__ rec);
 
 // Blocks [0, nblk) count; the blocks after them write the large-instance records.
-__device__ __forceinline__ void bucket_count(Geom g, TileGeom t, const float* __restrict__ xyz, const float* __restrict__ size, const uint8_t* __restrict__ kind, const uint8_t* __restrict__ cls, int32_t* __restrict__ counts, int32_t* __restrict__ tiles_of, float4* __restrict__ xyzp, const int32_t* __restrict__ large, int nlarge, float4* __restrict__ lrec) {
+__device__ __forceinline__ void bucket_count(Geom g, TileGeom t, const float* __restrict__ xyz,
+                                             const float* __restrict__ size, const uint8_t* __restrict__ kind,
+                                             const uint8_t* __restrict__ cls, int32_t* __restrict__ counts,
+                                             int32_t* __restrict__ tiles_of, float4* __restrict__ xyzp,
+                                             const int32_t* __restrict__ large, int nlarge,
+                                             float4* __restrict__ lrec) {
   extern __shared__ int hist[];
   if ((int)blockIdx.x >= t.nblk) {
     const int j = ((int)blockIdx.x - t.nblk) * blockDim.x + threadIdx.x;
@@ -485,7 +490,13 @@ __device__ void chunk_plan(const int32_t* totals, int entries, SplitBound sb, in
 // kScan: the workgroup also adds up its column offsets and the tile totals from all blocks' counts,
 // which the scan pass leaves ready otherwise.
 template <bool kScan>
-__device__ __forceinline__ void bucket_scatter(Geom g, TileGeom t, const float* __restrict__ xyz, const float* __restrict__ size, const uint8_t* __restrict__ kind, const uint8_t* __restrict__ cls, const int32_t* __restrict__ counts, const int32_t* totals, int32_t* __restrict__ tile_start, float4* __restrict__ entries, int32_t* __restrict__ cell_entry, int max_extra_d, int32_t* __restrict__ plan_d, int max_extra_g, int32_t* __restrict__ plan_g) {
+__device__ __forceinline__ void bucket_scatter(Geom g, TileGeom t, const float* __restrict__ xyz,
+                                               const float* __restrict__ size, const uint8_t* __restrict__ kind,
+                                               const uint8_t* __restrict__ cls, const int32_t* __restrict__ counts,
+                                               const int32_t* totals, int32_t* __restrict__ tile_start,
+                                               float4* __restrict__ entries, int32_t* __restrict__ cell_entry,
+                                               int max_extra_d, int32_t* __restrict__ plan_d, int max_extra_g,
+                                               int32_t* __restrict__ plan_g) {
   // every workgroup scans the tile totals itself (exclusive prefix = tile_start) and workgroup 0
   // stores the result for the later passes; the cursor of tile k starts at tile_start[k] plus
   // this workgroup's offset within the tile
@@ -653,6 +664,12 @@ struct TileBox { int x0, y0, wx, wy; };
 // threads of a tile workgroup (density map, field gather, adjoint): eight wavefronts, so that the
 // gathers of a tile's entries have more loads in flight than the LDS-bound occupancy allows
 constexpr int kTileThreads = 512;
+// The density pass takes wide workgroups where there are no more tiles than this, one per compute
+// unit: its time is then the fullest tile's, entry after entry (64 tiles of 5500 entries 33 -> 25 us, 256
+// tiles of 200k cells 25 -> 20).  With more tiles narrow ones share the units better (768: 16 us
+// against 20; 1024 beside the wirelength sweep: 36 against 126).  The gathers are split further and
+// gain nothing.
+constexpr int kWideTiles = 256, kWideThreads = 1024;
 
 __device__ __forceinline__ TileBox tile_box(const Geom& g, const TileGeom& t, int tile) {
   TileBox b;
@@ -816,10 +833,15 @@ __device__ __forceinline__ void write_tile(const Geom& g, const TileGeom& t, con
 // 64 tiles have three chunks each.)
 // (eight wavefronts per SIMD: the scalar registers its heavy-tile path needs would otherwise cost
 // one; the excess goes to vector-register lanes)
-__device__ __forceinline__ void density_of_tiles(Geom g, TileGeom t, const float4* __restrict__ entries, Chunks ch, unsigned long long* __restrict__ sums, const float* __restrict__ fixed_map, const float4* __restrict__ lrec, int nlarge, float target, int fillers, float* __restrict__ rho, double* __restrict__ part, int stride) {
+template <int TT>
+__device__ __forceinline__ void density_of_tiles(Geom g, TileGeom t, const float4* __restrict__ entries, Chunks ch,
+                                                 unsigned long long* __restrict__ sums,
+                                                 const float* __restrict__ fixed_map, const float4* __restrict__ lrec,
+                                                 int nlarge, float target, int fillers, float* __restrict__ rho,
+                                                 double* __restrict__ part, int stride) {
   extern __shared__ unsigned long long S64[];
-  __shared__ int hits[kTileThreads];
-  __shared__ int wave_cnt[kTileThreads / kWave];
+  __shared__ int hits[TT];
+  __shared__ int wave_cnt[TT / kWave];
   __shared__ int last_chunk;
   const int tsz = t.T * t.T * g.nz;
   const float inv_vol = 1.f / g.vol_bin;
@@ -978,10 +1000,10 @@ struct DensityArgs {
   double* part;
   int stride;
 };
-template <int B>
-__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_density_tiles(Many<DensityArgs, B> m) {
+template <int B, int TT>
+__global__ __launch_bounds__(TT) __attribute__((amdgpu_waves_per_eu(8))) void k_density_tiles(Many<DensityArgs, B> m) {
   const DensityArgs& a = m.mine();
-  density_of_tiles(a.g, a.t, a.entries, a.ch, a.sums, a.fixed_map, a.lrec, a.nlarge, a.target, a.fillers, a.rho, a.part, a.stride);
+  density_of_tiles<TT>(a.g, a.t, a.entries, a.ch, a.sums, a.fixed_map, a.lrec, a.nlarge, a.target, a.fillers, a.rho, a.part, a.stride);
 }
 
 // fixed map: one workgroup per fixed instance, global atomics (built once)
@@ -1076,7 +1098,11 @@ __global__ __launch_bounds__(256) void k_red_final(const double* __restrict__ pa
 // sign (E - O), with E at column x and O at column hx + x of the stored map.
 struct FoldX { int on, hx; float sx, sy, sz; };
 
-__device__ __forceinline__ void gather_of_tiles(Geom g, TileGeom t, const float4* __restrict__ entries, Chunks ch, const float* __restrict__ mx, const float* __restrict__ my, const float* __restrict__ mz, FoldX fx, float4* __restrict__ out, const float4* __restrict__ lrec, int nlarge, float4* __restrict__ lpart) {
+__device__ __forceinline__ void gather_of_tiles(Geom g, TileGeom t, const float4* __restrict__ entries, Chunks ch,
+                                                const float* __restrict__ mx, const float* __restrict__ my,
+                                                const float* __restrict__ mz, FoldX fx, float4* __restrict__ out,
+                                                const float4* __restrict__ lrec, int nlarge,
+                                                float4* __restrict__ lpart) {
   extern __shared__ __align__(16) float S[];
   __shared__ int hits[kTileThreads];
   __shared__ int wave_cnt[kTileThreads / kWave];
@@ -1235,7 +1261,9 @@ __global__ __launch_bounds__(kTileThreads) void k_gather_tiles(Many<GatherArgs, 
 }
 
 // per large instance (one wavefront each): sum the partials of the tiles its record overlaps
-__device__ __forceinline__ void large_gather_finish(Geom g, TileGeom t, const int32_t* __restrict__ large, int nlarge, const float4* __restrict__ lrec, const float4* __restrict__ lpart, float scale, float* __restrict__ grad, int accumulate) {
+__device__ __forceinline__ void large_gather_finish(Geom g, TileGeom t, const int32_t* __restrict__ large, int nlarge,
+                                                    const float4* __restrict__ lrec, const float4* __restrict__ lpart,
+                                                    float scale, float* __restrict__ grad, int accumulate) {
   const int j = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   const int lane = threadIdx.x & (kWave - 1);
   if (j >= nlarge) return;
@@ -1720,13 +1748,19 @@ int density_tiles_many(place3d_ctx* const* c, const float* const* xyz, float* co
     const int fillers = most_of(nb, [&](int i) { return c[i]->n_fillers > 0 ? 1 : 0; });
     const int extra = most_of(nb, [&](int i) { return c[i]->max_extra[kSplitDensity]; });
     auto inst = [&](int i) { return (c[i]->prob.options & PLACE3D_OPT_MACRO_INSTANCE) != 0; };
-    launch_many<DensityArgs>(k_density_tiles<1>, k_density_tiles<kMaxMany>, nb, ntiles + extra, kTileThreads,
-                             (2 + 2 * fillers) * tile_lds(c[0], 1), s, [&](int i) {
+    auto args = [&](int i) {
       place3d_ctx* q = c[i];
       return DensityArgs{q->g, q->tg, q->bk_entries, chunks_of(q, kSplitDensity), q->chunk_sums,
                          q->n_fixed > 0 ? q->fixed_map : nullptr, q->large_rec, inst(i) ? 0 : q->n_large,
                          (float)q->prob.target_density, q->n_fillers > 0 ? 1 : 0, rho[i], q->part, q->part_stride};
-    });
+    };
+    const size_t lds = (2 + 2 * fillers) * tile_lds(c[0], 1);
+    if (ntiles * nb <= kWideTiles)
+      launch_many<DensityArgs>(k_density_tiles<1, kWideThreads>, k_density_tiles<kMaxMany, kWideThreads>, nb,
+                               ntiles + extra, kWideThreads, lds, s, args);
+    else
+      launch_many<DensityArgs>(k_density_tiles<1, kTileThreads>, k_density_tiles<kMaxMany, kTileThreads>, nb,
+                               ntiles + extra, kTileThreads, lds, s, args);
     P3D_LAUNCH(c[0], "k_density_tiles");
     for (int i = 0; i < nb; ++i) {
       place3d_ctx* q = c[i];

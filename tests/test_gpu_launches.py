@@ -1,5 +1,6 @@
 """The sizes at which passes change how they share their launches: the scatter that adds up the tiles'
-counts itself against the scan pass (32768 counts, 4096 tiles), and the move that sums the step's norms
+counts itself against the scan pass (32768 counts, 4096 tiles), the wide density workgroups (256 tiles)
+and the move that sums the step's norms
 itself against a reduction (512 partials, 131072 instances; multi-die 2048 and 524288 nodes).
 
 Density maps against the oracle with the parity tests' bar (rel L2 <= 1e-6).  A step's size against
@@ -23,7 +24,8 @@ def sized_case(n_inst, nx, ny, die):
 
 
 @pytest.mark.parametrize("n_inst,nx,ny", [(32 * 2048, 1024, 1024), (32 * 2048 + 1, 1024, 1024),     # 32 and 33 x 1024
-                                          (2048, 2048, 2048), (2048, 2049, 2048), (5000, 40, 1000)])
+                                          (2048, 2048, 2048), (2048, 2049, 2048), (5000, 40, 1000),
+                                          (9000, 512, 512), (9000, 513, 512)])
 def test_counts_added_by_either_pass(n_inst, nx, ny):
     need_gpu()
     log(f"[launches] {n_inst} instances on {nx} x {ny}")
