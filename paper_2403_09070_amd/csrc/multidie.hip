@@ -92,21 +92,32 @@ __global__ void k_md_pack(int n, const float* __restrict__ xy, const uint8_t* __
   d[j] = x; d[m + j] = y; d[2 * m + j] = zmid;
 }
 
-// The layers' density gradients: g (every node's, or the large nodes' where cs holds the cells'
-// shares).
+// The layers' density gradients: g (every node's, or the large nodes' where cs.entry holds the cells'
+// shares).  Layer L's arrays lie d*[L] elements after layer 0's (all are in the one workspace): the
+// nodes of a wavefront are of all layers, and pointers chosen lane by lane from a table of them would
+// be read from a copy of the table in scratch memory.
 struct LayerGrads {
-  const float* g[3];
+  const float* g;
+  CellShares cs;
+  long long dg[3], dcls[3], dpacked[3], dentry[3];
   int n[3];
-  CellShares cs[3];
 };
 
-__device__ __forceinline__ void den_grad(const LayerGrads& lg, const uint8_t* __restrict__ layer,
-                                         const int32_t* __restrict__ local, int i, float& gx, float& gy) {
-  const int L = layer[i], j = local[i];
-  const float* g = L == 0 ? lg.g[0] : (L == 1 ? lg.g[1] : lg.g[2]);
-  const int m = L == 0 ? lg.n[0] : (L == 1 ? lg.n[1] : lg.n[2]);
-  const CellShares cs = L == 0 ? lg.cs[0] : (L == 1 ? lg.cs[1] : lg.cs[2]);
-  if (cs.entry) {
+// one of three uniform values, chosen per lane
+template <class T>
+__device__ __forceinline__ T pick(int L, T a, T b, T c) {
+  asm("" : "+s"(a), "+s"(b), "+s"(c));
+  return L == 0 ? a : (L == 1 ? b : c);
+}
+
+// of node j of layer L
+__device__ __forceinline__ void den_grad(const LayerGrads& lg, int L, int j, float& gx, float& gy) {
+  const float* g = lg.g + pick(L, lg.dg[0], lg.dg[1], lg.dg[2]);
+  const int m = pick(L, lg.n[0], lg.n[1], lg.n[2]);
+  if (lg.cs.entry) {
+    const CellShares cs{lg.cs.cls + pick(L, lg.dcls[0], lg.dcls[1], lg.dcls[2]),
+                        lg.cs.cell_entry + pick(L, lg.dpacked[0], lg.dpacked[1], lg.dpacked[2]),
+                        lg.cs.entry + pick(L, lg.dentry[0], lg.dentry[1], lg.dentry[2]), lg.cs.scale};
     float d[3];
     density_grad_of(cs, g, m, j, cs.cls[j], cs.cell_entry[j], d);
     gx = d[0];
@@ -126,7 +137,7 @@ __global__ void k_md_parts(int n, const uint8_t* __restrict__ layer, const int32
   gw[i] = g_wl[i];
   gw[n + i] = g_wl[n + i];
   float x, y;
-  den_grad(lg, layer, local, i, x, y);
+  den_grad(lg, layer[i], local[i], x, y);
   gd[i] = x;
   gd[n + i] = y;
 }
@@ -180,7 +191,7 @@ __global__ void k_md_l1(int n, const uint8_t* __restrict__ kind, const uint8_t* 
   if (i < n && !(kind[i] & PLACE3D_KIND_FIXED)) {
     const int L = layer[i];
     float x, y;
-    den_grad(lg, layer, local, i, x, y);
+    den_grad(lg, layer[i], local[i], x, y);
     const double w = fabs((double)g_wl[i]) + fabs((double)g_wl[n + i]), d = fabs((double)x) + fabs((double)y);
 #pragma unroll
     for (int q = 0; q < 3; ++q) {      // selects, not a runtime index into the register array
@@ -203,21 +214,35 @@ __global__ void k_md_combine(int n, const float* __restrict__ size, const uint8_
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (mode == 1 && i == 0) *a_copy = sc[PLACE3D_MS_A];
   double acc[2] = {0.0, 0.0};
+  const double l0 = sc[PLACE3D_MS_LAMBDA], l1 = sc[PLACE3D_MS_LAMBDA + 1], l2 = sc[PLACE3D_MS_LAMBDA + 2];
   if (i < n) {
+    // the node's operands are all loaded before any is used, then its layer's class and tile range,
+    // then its cell's shares (300k nodes 11 us; 31 with layer tables read from scratch memory)
     const uint8_t k = kind[i];
+    const int L = layer[i], j = local[i];
+    const float w = size[i], h = size[n + i], np = npins[i];
+    float wv[2], vv[2], vp[2] = {0.f, 0.f}, go[2] = {0.f, 0.f};
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      wv[a] = g_wl[a * n + i];
+      vv[a] = v[a * n + i];
+      if (mode == 1) {
+        vp[a] = v_prev[a * n + i];
+        go[a] = gout[a * n + i];
+      }
+    }
+    float d[2];
+    den_grad(lg, L, j, d[0], d[1]);
     float gv[2] = {0.f, 0.f};
     if (!(k & PLACE3D_KIND_FIXED)) {
-      const int L = layer[i];
-      const double lam = sc[PLACE3D_MS_LAMBDA + L];
-      const double lq = lam * (double)size[i] * (double)size[n + i];
-      const double H = (k & PLACE3D_KIND_MACRO) ? fmax(1.0, (double)npins[i] + lq) : fmax(1.0, lq);
-      float d[2];
-      den_grad(lg, layer, local, i, d[0], d[1]);
-      for (int a = 0; a < 2; ++a) gv[a] = (float)(((double)g_wl[a * n + i] + lam * (double)d[a]) / H);
+      const double lam = L == 0 ? l0 : (L == 1 ? l1 : l2);
+      const double lq = lam * (double)w * (double)h;
+      const double H = (k & PLACE3D_KIND_MACRO) ? fmax(1.0, (double)np + lq) : fmax(1.0, lq);
+      for (int a = 0; a < 2; ++a) gv[a] = (float)(((double)wv[a] + lam * (double)d[a]) / H);
       if (mode == 1) {
         for (int a = 0; a < 2; ++a) {
-          const double dv = (double)v[a * n + i] - (double)v_prev[a * n + i];
-          const double dg = (double)gv[a] - (double)gout[a * n + i];
+          const double dv = (double)vv[a] - (double)vp[a];
+          const double dg = (double)gv[a] - (double)go[a];
           acc[0] += dv * dv;
           acc[1] += dg * dg;
         }
@@ -463,11 +488,16 @@ int md_layout(place3d_md2d_ctx* c, const place3d_md2d_problem& p, char* base, si
 
 LayerGrads layer_grads(const place3d_md2d_ctx* c, bool shares = false) {
   LayerGrads lg = {};
+  const place3d_ctx* l0 = c->lay[0];
+  lg.g = c->g_l[0];
+  if (shares) lg.cs = CellShares{l0->cls, l0->cell_entry, l0->entry_out, l0->cell_scale};   // one scale for all
   for (int L = 0; L < 3; ++L) {
-    lg.g[L] = c->g_l[L];
-    lg.n[L] = c->n_of[L];
     const place3d_ctx* lc = c->lay[L];
-    if (shares) lg.cs[L] = CellShares{lc->cls, lc->cell_entry, lc->entry_out, lc->cell_scale};
+    lg.n[L] = c->n_of[L];
+    lg.dg[L] = c->g_l[L] - c->g_l[0];
+    lg.dcls[L] = lc->cls - l0->cls;
+    lg.dpacked[L] = lc->cell_entry - l0->cell_entry;
+    lg.dentry[L] = lc->entry_out - l0->entry_out;
   }
   return lg;
 }
