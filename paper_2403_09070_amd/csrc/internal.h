@@ -289,6 +289,13 @@ __device__ __forceinline__ void row_sums(const double* const (&row)[NQ], int npa
   for (int q = 0; q < NQ; ++q) out[q] = sh[q][0];
 }
 
+// Pins from which an evaluation runs its wirelength sweep on a side stream beside the density chain.
+// The four event operations cost the host 45 to 60 us a call (2k instances: issued in 43 us on one
+// stream, 88 on two), the overlap saves less the smaller the sweep is: step of 2k instances, 8k pins,
+// 65 us on one stream, 72 to 88 on two; 60k instances, 235k pins, 98 and 94 to 98; 100k, 392k pins, 108
+// and 103; 200k, 760k pins, 134 and 121; 1.2M, 4.5M pins, 361 and 346.
+constexpr int kForkPins = 1 << 18;
+
 // Partials up to which the move sums a step's norms itself, every workgroup the same two rows, instead
 // of reading what a reduction launched before it left: it saves a launch (2k instances 88 -> 84 us a
 // step, the host's time) and costs a round of loads per 1024 partials (200k instances, 785 partials:

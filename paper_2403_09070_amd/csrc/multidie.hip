@@ -529,8 +529,8 @@ LayerRed layer_red(const place3d_md2d_ctx* c) {
 // in_combine: the cells' density-gradient shares and the overflow partials are left to the step's
 // combine and move.
 // The partial nets' wirelength and the layers' density chains share nothing but the packed positions:
-// the wirelength runs on its sub-context's side stream (default priority) meanwhile, and s waits for
-// it before anything reads its results.  The three layers, each too small to fill the chip, share
+// a large wirelength sweep runs on its sub-context's side stream (default priority) meanwhile, and s
+// waits for it before anything reads its results.  The three layers, each too small to fill the chip, share
 // their launches: 300k nodes on 512 x 512 181 us a step, against 199 to 253 with a stream for each
 // (as its streams share the hardware queues; the host then issues 30 launches and 10 event
 // operations in 160 to 230 us, here 14 and 4 in 85 to 105), 8k nodes on 64 x 64 78 against 160.
@@ -540,11 +540,14 @@ int md_evaluate(place3d_md2d_ctx* c, const float* xy, hipStream_t s, double* en 
   hipLaunchKernelGGL(k_md_pack, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, xy, p.layer, c->node_local, c->zmid,
                      c->wl->xyzp, c->xyz_l[0], c->xyz_l[1], c->xyz_l[2], c->n_of[0], c->n_of[1], c->n_of[2]);
   MD_HIP(c, hipGetLastError());
-  MD_HIP(c, hipEventRecord(c->ev_fork, s));
-  hipStream_t ws = c->wl->side;
-  MD_HIP(c, hipStreamWaitEvent(ws, c->ev_fork, 0));
+  const bool fork = p.n_pins > kForkPins;
+  hipStream_t ws = fork ? c->wl->side : s;
+  if (fork) {
+    MD_HIP(c, hipEventRecord(c->ev_fork, s));
+    MD_HIP(c, hipStreamWaitEvent(ws, c->ev_fork, 0));
+  }
   MD_SUB(c, c->wl, wirelength_eval(c->wl, nullptr, c->g_wl, 0, c->wl->red, nullptr, ws, true, nullptr, false, false));
-  MD_HIP(c, hipEventRecord(c->ev_done[0], ws));
+  if (fork) MD_HIP(c, hipEventRecord(c->ev_done[0], ws));
   const float *xyz[3], *cex[3], *cey[3], *cez[3];
   const float* crho[3];
   float *rho[3], *phi[3], *ex[3], *ey[3], *ez[3], *g[3];
@@ -580,7 +583,7 @@ int md_evaluate(place3d_md2d_ctx* c, const float* xy, hipStream_t s, double* en 
   }
   // grad = (4/d_z) grad_3: the layer's 2D field-gather gradient
   MD_SUB(c, c->lay[0], gather_bucketed_many(c->lay, xyz, cex, cey, cez, -4.f / c->dz, g, 0, 3, s, !in_combine, false));
-  MD_HIP(c, hipStreamWaitEvent(s, c->ev_done[0], 0));
+  if (fork) MD_HIP(c, hipStreamWaitEvent(s, c->ev_done[0], 0));
   return PLACE3D_OK;
 }
 
