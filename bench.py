@@ -6,9 +6,9 @@ Workload: the 1.2M-cell synthetic netlist (150 macros, 1.3M nets, ~4.5M pins, gr
   mixed  -- the precision form (PLACE3D_BF16X3): compensated exponential sums, same field-gather
             gradient
   autograd (optional, --forms) -- the precision form with the exact-adjoint density gradient
-The solve of a grid with power-of-two planar sides runs by float32 fast transforms in the plain and
-mixed forms; on other grids the plain form contracts in float32 and mixed in split bf16 (hi/lo,
-three products, float32 accumulation), as autograd does on every grid.
+The solve of a grid with power-of-two planar sides runs by float32 fast transforms in the plain form
+and, up to 2^20 instances, in mixed; otherwise the plain form contracts in float32 and mixed in split
+bf16 (hi/lo, three products, float32 accumulation), as autograd always does.
 A step is one full GP iteration (place3d_step): density map, spectral solve, density gradient,
 bistratal WA wirelength with the FDA z-gradient, preconditioned Nesterov move.  `value` is the
 mixed form's iterations/s over exactly --steps timed steps after --warmup warm-up and
@@ -68,10 +68,11 @@ def gemm_flops_per_step(nx, ny, nz, dgrad_field, bf16x3):
     return total * (3.0 if bf16x3 else 1.0)
 
 
-def fast_solve(nx, ny, nz, dgrad_field):
-    """Whether the library solves this grid by fast transforms (float32 in both precisions)."""
+def fast_solve(case, bf16x3, dgrad_field):
+    """Whether the library's steps solve this case by fast transforms (float32 in both precisions)."""
     side = lambda n: 64 <= n <= 2048 and n & (n - 1) == 0  # noqa: E731
-    return dgrad_field and side(nx) and side(ny) and nz in (2, 4)
+    large_split = bf16x3 and case.n_inst > 1 << 20
+    return dgrad_field and side(case.nx) and side(case.ny) and case.nz in (2, 4) and not large_split
 
 
 def fft_bytes_per_step(bins):
@@ -647,7 +648,7 @@ def main():
         prof = head["prof"]
         ps = args.profile_steps
         field_form = head_name != "autograd"
-        fast = fast_solve(case.nx, case.ny, case.nz, field_form)
+        fast = fast_solve(case, bf16x3, field_form)
         cands = {
             "gemm": ("hbm", fft_bytes_per_step(bins) / 1e9, HBM_PEAK_GBS, "GB/s") if fast else (
                 "mfma", gemm_flops_per_step(case.nx, case.ny, case.nz, field_form, bf16x3) / 1e12,
@@ -682,7 +683,7 @@ def main():
         "repeats": args.repeats, "readback_every": args.readback_every,
         "runs_iters_per_s": [round(v, 1) for v in head["runs"]],
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "bf16x3/f32" if bf16x3 and not fast_solve(case.nx, case.ny, case.nz, head_name != "autograd")
+        "dtype": "bf16x3/f32" if bf16x3 and not fast_solve(case, bf16x3, head_name != "autograd")
         else "f32", "data": "synthetic",
         "config": {"workload": f"{args.config}: {n - case.meta['n_macros']} cells + {case.meta['n_macros']} macros, "
                                f"{m} nets, {P} pins, grid {case.nx}x{case.ny}x{case.nz}, seed {args.seed}",

@@ -106,6 +106,14 @@ bool fft_grid(const place3d_problem& p) {
   return side(p.nx) && side(p.ny) && (p.nz == 2 || p.nz == 4) && p.dgrad == PLACE3D_DGRAD_FIELD;
 }
 
+// Steps of large split-bf16 problems keep the contractions too, for the same reason: an instance
+// that the first steps leave within a few float32 units of the mid-plane takes the other die's
+// sizes and offsets when the solve rounds otherwise, and the split contractions' rounding (3.4e-6 of
+// the gradient) moves enough positions that one of 1.2M instances did so in 4 of 16 starts, against
+// none of up to 640k instances in 45 (float32: 1 of 14, none of 20).  They pay
+// for it: a step of 1.2M instances on 1024 x 1024 x 4 takes 455 us, 350 with the transforms.
+bool split_steps(const place3d_problem& p) { return p.precision == PLACE3D_BF16X3 && p.n_inst > (1 << 20); }
+
 int parts_bound(const place3d_problem& p, const p3d::TileGeom& t) {
   int b = std::max(p.n_nets / 4 + 16, p.n_inst / 256 + p.n_pins / 128 + 8);
   b = std::max(b, t.ntiles);
@@ -158,9 +166,9 @@ size_t layout(place3d_ctx* c, const place3d_problem& p, char* base) {
     auto& q = c->fft;
     q.tx = w.take<float2>(p3d::kFftTable * nx); q.wx = w.take<float2>(nx / 2 + 1);
     q.ty = w.take<float2>(p3d::kFftTable * ny); q.wy = w.take<float2>(ny / 2 + 1);
-  } else {
-    layout_dense(c, p, w);
   }
+  c->step_dense = c->fft.on && split_steps(p);
+  if (!c->fft.on || c->step_dense) layout_dense(c, p, w);
   c->rho = w.take<float>(map); c->phi = w.take<float>(map);
   c->ex = w.take<float>(map); c->ey = w.take<float>(map); c->ez = w.take<float>(map);
   c->fixed_map = w.take<float>(map);

@@ -133,6 +133,7 @@ struct place3d_ctx {
   p3d::DctBases dct;
   p3d::SplitChain sc;
   p3d::FftChain fft;
+  bool step_dense = false;             // steps keep the dense contractions beside the fast transforms
   float *map_t = nullptr, *map_a = nullptr, *map_vg = nullptr, *map_vh = nullptr;
   float *map_pc = nullptr, *map_ps = nullptr, *map_qc = nullptr;
   // step scratch maps (rho, phi, ex, ey, ez)
@@ -357,7 +358,7 @@ int build_dct_bases(place3d_ctx* c, hipStream_t s);
 // [0, nx/2) and [nx/2, nx)) for a consumer that unfolds them on load; ctx->field_xfold says
 // whether that happened
 int spectral_field(place3d_ctx* c, const float* rho, float* phi, float* ex, float* ey, float* ez,
-                   double* energy, hipStream_t s, bool x_folded_out = false);
+                   double* energy, hipStream_t s, bool x_folded_out = false, bool in_step = false);
 // the split chain's bases (at creation) and its contractions; outputs in natural x order
 int build_split_chain(place3d_ctx* c, hipStream_t s);
 int field_split(place3d_ctx* c, const float* rho, float* phi, float* ex, float* ey, float* ez, hipStream_t s);

@@ -743,7 +743,9 @@ int build_dct_bases(place3d_ctx* c, hipStream_t s) {
   c->dct.fold = (g.nx % 2 == 0 && g.ny % 2 == 0) ? 1 : 0;
   hipLaunchKernelGGL(k_basis_z, dim3(1), dim3(kMaxNz * kMaxNz), 0, s, g.nz, dz, c->dct.zmat);
   P3D_LAUNCH(c, "k_basis_z");
-  if (c->fft.on) return build_fft(c, s);
+  if (c->fft.on)
+    if (int rc = build_fft(c, s)) return rc;
+  if (c->fft.on && !c->step_dense) return PLACE3D_OK;
   hipLaunchKernelGGL(k_basis_x, dim3(blocks_for((long long)g.nx * g.nx, 256)), dim3(256), 0, s, g.nx, c->dct.fold,
                      p.die_x, c->dct.Fx, c->dct.Gx, c->dct.Hx);
   P3D_LAUNCH(c, "k_basis_x");
@@ -769,7 +771,7 @@ int build_dct_bases(place3d_ctx* c, hipStream_t s) {
 }
 
 int spectral_field(place3d_ctx* c, const float* rho, float* phi, float* ex, float* ey, float* ez,
-                   double* energy, hipStream_t s, bool x_folded_out) {
+                   double* energy, hipStream_t s, bool x_folded_out, bool in_step) {
   const Geom& g = c->g;
   const DctBases& d = c->dct;
   const int nx = g.nx, ny = g.ny, nz = g.nz;
@@ -790,7 +792,7 @@ int spectral_field(place3d_ctx* c, const float* rho, float* phi, float* ex, floa
   if (ez) xo[nxo++] = {c->map_ps, Gx, ez, 1.f};
   if (phi) xo[nxo++] = {c->map_pc, Gx, phi, 1.f};
 
-  if (c->fft.on) {
+  if (c->fft.on && !(in_step && c->step_dense)) {
     c->field_xfold = 0;
     if ((rc = field_fft(c, rho, phi, ex, ey, ez, s))) return rc;
   } else if (d.fold) {

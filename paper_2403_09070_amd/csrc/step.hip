@@ -345,11 +345,12 @@ int eval_parts(place3d_ctx* c, const float* xyz, float* gw, float* gd, double* r
   if (c->prob.dgrad == PLACE3D_DGRAD_FIELD) {
     // the float32 form's field stays x-folded for the gather, which unfolds it while staging its
     // tiles (the split-bf16 chain returns it unfolded)
-    if ((rc = spectral_field(c, c->rho, nullptr, c->ex, c->ey, c->ez, nullptr, s, large_in_tiles(c)))) return rc;
+    if ((rc = spectral_field(c, c->rho, nullptr, c->ex, c->ey, c->ez, nullptr, s, large_in_tiles(c), true)))
+      return rc;
     if ((rc = gather_bucketed(c, xyz, c->ex, c->ey, c->ez, -1.f, gd, 0, s, !in_combine, c->field_xfold != 0)))
       return rc;
   } else {
-    if ((rc = spectral_field(c, c->rho, c->phi, nullptr, nullptr, nullptr, red + R_ENERGY, s))) return rc;
+    if ((rc = spectral_field(c, c->rho, c->phi, nullptr, nullptr, nullptr, red + R_ENERGY, s, false, true))) return rc;
     if ((rc = adjoint_bucketed(c, xyz, c->phi, c->g.vol_bin, gd, 0, s, !in_combine))) return rc;
   }
   if (fork) P3D_HIP(c, hipStreamWaitEvent(s, c->ev_join, 0));

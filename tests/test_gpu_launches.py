@@ -73,3 +73,35 @@ def test_multi_die_step_size_from_either_reduction(n):
     prob.step(st)
     want = float(torch.sqrt(((v - vp) ** 2).sum() / ((st.g_prev.double() - g) ** 2).sum()))
     assert abs(st.read()["step"] - want) <= 1e-9 * want
+
+
+@pytest.mark.parametrize("n_inst", [1 << 20, (1 << 20) + 1])
+def test_steps_of_large_split_problems_solve_by_contractions(n_inst):
+    """Up to 2^20 instances a split-bf16 step takes the float32 transforms (its gradient within 1e-6 of
+    the plain form's: the same field, compensated wirelength sums), from there on the split
+    contractions, whose field differs by their rounding (some 4e-6); both meet the bar of 1e-4, and
+    the field call takes the transforms either way."""
+    need_gpu()
+    log(f"[launches] split step of {n_inst} instances")
+    case = sized_case(n_inst, 64, 64, 2400.0)
+    assert case.n_inst == n_inst
+    g, f = [], []
+    for precision in (place3d.FP32, place3d.BF16X3):
+        prob = gpu_problem(case, precision=precision)
+        st = prob.new_state()
+        x = prob.xyz(case.xyz0)
+        for t in (st.u, st.v):
+            t.copy_(x)
+        st.v_prev.copy_(x + 0.01)
+        st.g_prev.zero_()
+        st.scalars.zero_()
+        st.scalars[place3d.S["a"]] = 1.0
+        st.scalars[place3d.S["lam"]] = 1.0
+        prob.step(st)
+        g.append(st.g_prev.double())
+        rho = prob.density(case.xyz0)
+        f.append(prob.field(rho, want=("ex", "ez")))
+    err = float((g[0] - g[1]).norm() / g[0].norm())
+    log(f"[launches] {n_inst}: gradient of the split form {err:.2e} from the plain one")
+    assert err <= 1e-4 and (err <= 1e-6) == (n_inst <= 1 << 20)
+    assert all(torch.equal(f[0][k], f[1][k]) for k in ("ex", "ez"))
