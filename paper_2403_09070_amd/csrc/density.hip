@@ -1690,26 +1690,21 @@ int most_of(int nb, Get get) {
   return m;
 }
 
-int bucket_cells(place3d_ctx* c, const float* xyz, hipStream_t s, int part) {
-  return bucket_cells_many(&c, &xyz, 1, s, part);
-}
+int bucket_cells(place3d_ctx* c, const float* xyz, hipStream_t s) { return bucket_cells_many(&c, &xyz, 1, s); }
 
-int bucket_cells_many(place3d_ctx* const* c, const float* const* xyz, int nb, hipStream_t s, int part) {
+int bucket_cells_many(place3d_ctx* const* c, const float* const* xyz, int nb, hipStream_t s) {
   const int ntiles = c[0]->tg.ntiles;
   ProfScope prof_(c[0], PLACE3D_STAGE_BUCKET, s);
   const size_t hist = sizeof(int) * ntiles;
-  if (part != 2) {
-    const int blocks = most_of(nb, [&](int i) {
-      return c[i]->tg.nblk + (c[i]->n_large + kBucketThreads - 1) / kBucketThreads;
-    });
-    launch_many<CountArgs>(k_bucket_count<1>, k_bucket_count<kMaxMany>, nb, blocks, kBucketThreads, hist, s, [&](int i) {
-      place3d_ctx* q = c[i];
-      return CountArgs{q->g, q->tg, xyz[i], q->prob.size, q->prob.kind, q->cls, q->bk_counts, q->cell_entry, q->xyzp,
-                       q->large_list, q->n_large, q->large_rec};
-    });
-    P3D_LAUNCH(c[0], "k_bucket_count");
-  }
-  if (part == 1) return PLACE3D_OK;
+  const int blocks = most_of(nb, [&](int i) {
+    return c[i]->tg.nblk + (c[i]->n_large + kBucketThreads - 1) / kBucketThreads;
+  });
+  launch_many<CountArgs>(k_bucket_count<1>, k_bucket_count<kMaxMany>, nb, blocks, kBucketThreads, hist, s, [&](int i) {
+    place3d_ctx* q = c[i];
+    return CountArgs{q->g, q->tg, xyz[i], q->prob.size, q->prob.kind, q->cls, q->bk_counts, q->cell_entry, q->xyzp,
+                     q->large_list, q->n_large, q->large_rec};
+  });
+  P3D_LAUNCH(c[0], "k_bucket_count");
   // Up to this many counts every scatter workgroup adds them up itself: 25k of them (200k instances on
   // 256 tiles) cost it 3 us, the scan pass 5 and a launch (step 130 -> 126 us; multi-die 300k nodes
   // 197 -> 181; even at 40k).

@@ -387,7 +387,7 @@ struct Many {
   A v[B];
   __device__ __forceinline__ const A& mine() const { return v[B == 1 ? 0 : blockIdx.y]; }
 };
-int bucket_cells_many(place3d_ctx* const* c, const float* const* xyz, int nb, hipStream_t s, int part = 0);
+int bucket_cells_many(place3d_ctx* const* c, const float* const* xyz, int nb, hipStream_t s);
 int density_tiles_many(place3d_ctx* const* c, const float* const* xyz, float* const* rho, double* const* red, int nb,
                        hipStream_t s, bool reduce);
 int gather_bucketed_many(place3d_ctx* const* c, const float* const* xyz, const float* const* ex, const float* const* ey,
@@ -395,7 +395,7 @@ int gather_bucketed_many(place3d_ctx* const* c, const float* const* xyz, const f
                          bool cells, bool xfold);
 int field_fft_many(place3d_ctx* const* c, const float* const* rho, float* const* phi, float* const* ex, float* const* ey,
                    float* const* ez, int nb, hipStream_t s);
-int bucket_cells(place3d_ctx* c, const float* xyz, hipStream_t s, int part = 0);
+int bucket_cells(place3d_ctx* c, const float* xyz, hipStream_t s);
 // reduce: finish the overflow reduction here (else the caller reduces the R_EXCESS slots later)
 int density_tiles(place3d_ctx* c, const float* xyz, float* rho, double* red, hipStream_t s, bool reduce = true);
 int gather_bucketed(place3d_ctx* c, const float* xyz, const float* ex, const float* ey, const float* ez, float scale,

@@ -323,24 +323,19 @@ int eval_parts(place3d_ctx* c, const float* xyz, float* gw, float* gd, double* r
   int rc;
   // every reduction slot read after an evaluation is written by it (the energy slot, read only
   // for the scalars, stays as gp_init zeroed it in the field-gather form)
-  if ((rc = bucket_cells(c, xyz, s, 1))) return rc;  // the count pass packs xyz for the wirelength sweep
+  if ((rc = bucket_cells(c, xyz, s))) return rc;     // also packs xyz for the wirelength sweep
   // fork: a large wirelength sweep (its own reduction slots, pin and instance scratch) runs on the
-  // side stream while the bucketing, density, spectral and gather chain runs on s; joined below.
-  // With the fast transforms and the float32 contractions the sweep forks after the scatter pass,
-  // which then runs alone (1.2M-cell float32 step 346 us against 357 us with the fork after the
-  // count pass and 361 us with everything on one stream; the 200k-cell mixed one 121, 123 and 134 us);
-  // with the split contractions it forks right after the count pass, so that it is mostly done
-  // before they start.
+  // side stream while the density, spectral and gather chain runs on s; joined below.  It forks after
+  // the scatter pass, which then runs alone (1.2M-cell float32 step 346 us against 357 us with the
+  // fork after the count pass and 361 us with everything on one stream; mixed, with the split
+  // contractions, 433, 456 and 462; 640k mixed on 374 x 382 256 and 271 with the fork after the count).
   const bool fork = c->prob.n_pins > kForkPins;
-  const bool fork_after_scatter = !fork || !c->sc.on;
-  if (fork_after_scatter && (rc = bucket_cells(c, xyz, s, 2))) return rc;
   if (fork) {
     P3D_HIP(c, hipEventRecord(c->ev_fork, s));
     P3D_HIP(c, hipStreamWaitEvent(c->side, c->ev_fork, 0));
   }
   if ((rc = wirelength_eval(c, xyz, gw, 0, red, nullptr, fork ? c->side : s, true, nullptr, true, !in_combine))) return rc;
   if (fork) P3D_HIP(c, hipEventRecord(c->ev_join, c->side));
-  if (!fork_after_scatter && (rc = bucket_cells(c, xyz, s, 2))) return rc;
   if ((rc = density_tiles(c, xyz, c->rho, red, s, !in_combine))) return rc;
   if (c->prob.dgrad == PLACE3D_DGRAD_FIELD) {
     // the float32 form's field stays x-folded for the gather, which unfolds it while staging its
