@@ -94,8 +94,8 @@ p3d::TileGeom tile_geom(const place3d_problem& p) {
 // and 70 KiB of LDS), and the two layer counts whose mixing a lane holds in registers.  They are
 // faster over the whole range in both precisions (Ex, Ey and Ez of a map, against the float32
 // contractions): 64 x 64 x 2 20 us against 42, 128 x 128 x 4 20 against 61, 512 x 512 x 4 26 against
-// 172, 1024 x 1024 x 4 53 against 418 (split bf16 154), 2048 x 2048 x 4 297 against 2569 (split bf16,
-// all four maps: 373 against 974).
+// 172, 1024 x 1024 x 4 53 against 418 (split bf16 154), 2048 x 2048 x 4 284 against 2569 (split bf16,
+// all four maps: 305 against 970).
 // The exact-adjoint form keeps the contractions: its gradient jumps where a cell's edge crosses a
 // bin face, so that after one step even the transforms' smaller rounding moves a few cells' whole
 // gradient (320k instances on 256 x 256 x 4: 6.5e-4 of the gradient's norm after two steps, where

@@ -513,30 +513,32 @@ __global__ __launch_bounds__((y_threads<N, NZ>()), 2) void k_fft_y(FftYArgs g, F
 struct FftXJob { const float* v; const float* zm; int sine; float* out; };
 struct FftXArgs { int ny; float px; int vec; FftXJob job[4 * kMaxMany]; };
 
-// z mixing and x inverse of four rows y of a map (blockIdx.y), one group of lanes each, two layers
+// z mixing and x inverse of a few rows y of a map (blockIdx.y), one group of lanes each, two layers
 // per FFT.  The rows' coefficients are read as the y pass wrote them, one run of 128 bytes (NZ = 4)
-// for a pair of frequencies of the four rows, and turned to rows in LDS, two z frequencies at a time.
-constexpr int kIxRows = 4;
-template <int N> constexpr int ix_threads() { return kIxRows * lanes_of<N>(); }
+// for a pair of frequencies of four rows, and turned to rows in LDS, two z frequencies at a time.
+// Two rows where four would leave one workgroup to a compute unit's registers (2048 x 2048 x 4, all
+// four maps: 180 -> 153 us) or few to the chip (512 x 512 x 4, E: 9.3 -> 8.5); at 1024 four are as good.
+template <int N> constexpr int ix_rows() { return N == 512 || N == 2048 ? 2 : 4; }
+template <int N> constexpr int ix_threads() { return ix_rows<N>() * lanes_of<N>(); }
 
 template <int N, int NZ>
 __global__ __launch_bounds__(ix_threads<N>(), (N == 2048 ? 2 : 3)) void k_fft_ix(FftXArgs g, FftTabs tb) {
-  constexpr int E = Plan<N>::E, T = lanes_of<N>(), NP = pairs_of<N>(), H = NZ / 2;
-  constexpr int S = N + 16, kBuf = 2 * kIxRows * buf_of<N>(), kStage = 2 * kIxRows * S;     // floats
+  constexpr int E = Plan<N>::E, T = lanes_of<N>(), NP = pairs_of<N>(), H = NZ / 2, RW = ix_rows<N>();
+  constexpr int S = N + 16, kBuf = 2 * RW * buf_of<N>(), kStage = 2 * RW * S;     // floats
   __shared__ __attribute__((aligned(16))) float L[kBuf > kStage ? kBuf : kStage];
   const FftXJob J = g.job[blockIdx.y];
   const int tid = threadIdx.x, t = tid & (T - 1), f = tid / T, ny = g.ny;
-  const int y0 = xcd_swizzle((int)blockIdx.x, (int)gridDim.x) * kIxRows, y = y0 + f;
+  const int y0 = xcd_swizzle((int)blockIdx.x, (int)gridDim.x) * RW, y = y0 + f;
   const Lane<N> ln(t);
   cf* buf = reinterpret_cast<cf*>(L) + f * buf_of<N>();
   f32x4 in[E / 2][H];
   {
-    const float* at = J.v + (size_t)(y0 + (tid & 3)) * (2 * NZ);
+    const float* at = J.v + (size_t)(y0 + (tid & (RW - 1))) * (2 * NZ);
 #pragma unroll
     for (int e = 0; e < E / 2; ++e)
 #pragma unroll
       for (int h = 0; h < H; ++h)
-        in[e][h] = *reinterpret_cast<const f32x4*>(at + (size_t)((tid >> 2) + T * e) * ny * (2 * NZ) + 4 * h);
+        in[e][h] = *reinterpret_cast<const f32x4*>(at + (size_t)((tid / RW) + T * e) * ny * (2 * NZ) + 4 * h);
   }
   // (c_k, c_m) of every pair and layer, and c_0
   cf c[NZ][NP];
@@ -544,16 +546,16 @@ __global__ __launch_bounds__(ix_threads<N>(), (N == 2048 ? 2 : 3)) void k_fft_ix
 #pragma unroll
   for (int h = 0; h < H; ++h) {
     if (h > 0) __syncthreads();
-    float* at = L + (tid & 3) * S + 2 * (tid >> 2);
+    float* at = L + (tid & (RW - 1)) * S + 2 * (tid / RW);
 #pragma unroll
     for (int e = 0; e < E / 2; ++e) {
       *reinterpret_cast<f32x2*>(at + 2 * T * e) = (f32x2){in[e][h][0], in[e][h][1]};
-      *reinterpret_cast<f32x2*>(at + kIxRows * S + 2 * T * e) = (f32x2){in[e][h][2], in[e][h][3]};
+      *reinterpret_cast<f32x2*>(at + RW * S + 2 * T * e) = (f32x2){in[e][h][2], in[e][h][3]};
     }
     __syncthreads();
 #pragma unroll
     for (int l = 2 * h; l < 2 * h + 2; ++l) {
-      const float* row = L + ((l & 1) * kIxRows + f) * S;
+      const float* row = L + ((l & 1) * RW + f) * S;
       const float v0 = row[0];
 #pragma unroll
       for (int z = 0; z < NZ; ++z) c0[z] = l == 0 ? J.zm[z] * v0 : fmaf(J.zm[l * kMaxNz + z], v0, c0[z]);
@@ -728,7 +730,7 @@ int field_fft_many(place3d_ctx* const* c, const float* const* rho, float* const*
   xa.vec = (at & 15) == 0;
   with_side(nx, [&](auto side) {
     constexpr int N = decltype(side)::value;
-    const dim3 grid(ny / kIxRows, nj);
+    const dim3 grid(ny / ix_rows<N>(), nj);
     if (nz == 2) hipLaunchKernelGGL((k_fft_ix<N, 2>), grid, dim3(ix_threads<N>()), 0, s, xa, tb);
     else hipLaunchKernelGGL((k_fft_ix<N, 4>), grid, dim3(ix_threads<N>()), 0, s, xa, tb);
   });
