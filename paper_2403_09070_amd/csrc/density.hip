@@ -443,8 +443,8 @@ __global__ __launch_bounds__(kScanTiles * kScanParts) void k_bucket_scan_cols(in
 }
 
 // A chunk plan of the current buckets, made by one workgroup of the scatter pass (every thread
-// takes the tiles [k0, k1) of the tile scan): a tile of more entries than `most` is heavy; its
-// chunks after the first are numbered after the tiles, in tile order.  Layout of plan: [0] extra
+// takes the tiles [k0, k1) of the tile scan): a tile of more entries than the split's bounds is
+// heavy; its chunks after the first are numbered after the tiles, in tile order.  Layout of plan: [0] extra
 // chunks, [1] most, [2 + k] first extra chunk of tile k (-1 for a tile of one chunk), [2 + ntiles
 // + e] tile of extra chunk e, [2 + ntiles + max_extra + e] its index within the tile.  most is the
 // split's bound for the entries at hand, which keeps the extra chunks below max_extra: a tile of v
@@ -453,11 +453,11 @@ __device__ void chunk_plan(const int32_t* totals, int entries, SplitBound sb, in
                            int max_extra, int32_t* __restrict__ plan) {
   __shared__ int wx[kBucketThreads / kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int most = max(sb.min, (entries + sb.count - 1) / sb.count);
+  const int most = max(sb.min, (entries + sb.count - 1) / sb.count), bound = max(most, sb.from);
   int ox = 0;
   for (int k = k0; k < k1; ++k) {
     const int v = totals[k];
-    if (v > most) ox += (v - 1) / most;
+    if (v > bound) ox += (v - 1) / most;
   }
   int ix = ox;                          // inclusive scan within the wavefront
   for (int o = 1; o < kWave; o <<= 1) {
@@ -471,7 +471,7 @@ __device__ void chunk_plan(const int32_t* totals, int entries, SplitBound sb, in
   int32_t* extra = plan + 2 + ntiles;
   for (int k = k0; k < k1; ++k) {
     const int v = totals[k];
-    if (v > most) {
+    if (v > bound) {
       const int nx = (v - 1) / most;
       for (int j = 0; j < nx; ++j) {
         extra[ex + j] = k;
@@ -741,7 +741,7 @@ struct Chunks {
   const int32_t* __restrict__ tile_start;   // [ntiles + 1] entry ranges of the tiles
   int32_t* plan;                            // the context's chunk plan (written by chunk_plan;
                                             // its layout is in the accessors below)
-  int ntiles, max_extra;
+  int ntiles, max_extra, from;
   __device__ __forceinline__ int n_extra() const { return plan[0]; }
   __device__ __forceinline__ int most() const { return plan[1]; }
   __device__ __forceinline__ int first_extra(int tile) const { return plan[2 + tile]; }
@@ -774,7 +774,7 @@ __device__ __forceinline__ ChunkRef chunk_ref(const Chunks& ch, const TileGeom& 
   ck.first = ts;
   ck.last = te;
   const int v = te - ts, most = __builtin_amdgcn_readfirstlane(ch.most());
-  if (v > most) {           // equal chunks, none above most
+  if (v > most && v > ch.from) {      // equal chunks, none above most
     ck.nchunks = (v - 1) / most + 1;
     const int per = (v + ck.nchunks - 1) / ck.nchunks;
     ck.first = min(ts + kc * per, te);
@@ -1616,7 +1616,7 @@ __global__ void k_cells_combine(int n, const uint8_t* __restrict__ cls, const in
 size_t tile_lds(const place3d_ctx* c, int maps) { return sizeof(float) * (size_t)maps * c->tg.T * c->tg.T * c->g.nz; }
 
 Chunks chunks_of(const place3d_ctx* c, SplitKind k) {
-  return Chunks{c->bk_tile_start, c->bk_plan[k], c->tg.ntiles, c->max_extra[k]};
+  return Chunks{c->bk_tile_start, c->bk_plan[k], c->tg.ntiles, c->max_extra[k], kSplit[k].from};
 }
 
 }  // namespace

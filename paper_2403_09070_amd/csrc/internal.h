@@ -21,17 +21,18 @@ constexpr int kNumGroups = 7;           // nets by lane group: 1, 2, 4, ..., 64 
 constexpr int kNumClasses = kNumGroups + 1;   // the groups, then two-pin nets (one lane each)
 constexpr int kChunkGroup = 16;         // chunks of a tile whose density sums one workgroup adds
 
-// Splits of heavy tiles: a tile is split where it holds more (cell, tile) entries than
-// max(min, entries / count), which leaves at most count chunks beside the tiles' first ones.  The
-// gathers' chunks are independent, so that they are split as far as a workgroup's staging of the
-// maps allows (min of 16384, 2048, 1024: adjoint of 320k cells on 64 tiles 62, 34, 23 us; gather of
-// 200k cells on 256 tiles 28.6, 19.8, 16.1; 1.2M cells on four tiles with count of 256, 512, 1024: 72,
-// 51, 46).  The density chunks' sums have to meet, 0.1 us of fence each beside their bytes: 320k
-// cells on 64 tiles 33 us whole, 36 in two, 54 in six chunks; 1.2M cells on four tiles 165 us
-// in 80 chunks, 94 in 256, 102 in 512.
+// Splits of heavy tiles: a tile of more (cell, tile) entries than `from` and than most = max(min,
+// entries / count) is split into chunks of at most `most`, which leaves at most count chunks beside
+// the tiles' first ones.  The gathers' chunks are independent, so that they are split as far as a
+// workgroup's staging of the maps allows (min of 16384, 2048, 1024: adjoint of 320k cells on 64 tiles
+// 62, 34, 23 us; gather of 200k cells on 256 tiles 28.6, 19.8, 16.1; 1.2M cells on four tiles with
+// count of 256, 512, 1024: 72, 51, 46).  The density chunks' sums have to meet, 0.1 us of fence each
+// beside their bytes: tiles that would make two chunks are faster whole (64 of 5500 entries 25 us,
+// in two 27, in four 30), full ones in many (1.2M cells on four tiles: 165 us in 80 chunks, 86 in 160,
+// 72 in 256, 83 in 512).
 enum SplitKind { kSplitDensity = 0, kSplitGather = 1, kSplits = 2 };
-struct SplitBound { int min, count; };
-constexpr SplitBound kSplit[kSplits] = {{8192, 256}, {1024, 1024}};
+struct SplitBound { int from, min, count; };
+constexpr SplitBound kSplit[kSplits] = {{8192, 4096, 256}, {1024, 1024, 1024}};
 
 // Reduction slots (float64, device) inside the workspace.
 enum RedSlot {

@@ -20,8 +20,8 @@ from paper_2403_09070_amd import place3d, synth
 
 pytestmark = pytest.mark.gpu
 
-DENSITY, GATHER, GROUP = 8192, 1024, 16     # entries a chunk may hold; chunks one workgroup adds up
-COUNTS = [GATHER, GATHER + 1, DENSITY, DENSITY + 1, GROUP * DENSITY, GROUP * DENSITY + 1, 34 * DENSITY + 7]
+DENSITY, CHUNK, GATHER, GROUP = 8192, 4096, 1024, 16   # entries a tile, a chunk may hold; chunks one workgroup adds up
+COUNTS = [GATHER, GATHER + 1, DENSITY, DENSITY + 1, GROUP * CHUNK, GROUP * CHUNK + 1, 68 * CHUNK + 7]
 
 
 def one_tile_case(cells):
