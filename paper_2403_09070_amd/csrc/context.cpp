@@ -114,6 +114,24 @@ bool fft_grid(const place3d_problem& p) {
 // for it: a step of 1.2M instances on 1024 x 1024 x 4 takes 455 us, 350 with the transforms.
 bool split_steps(const place3d_problem& p) { return p.precision == PLACE3D_BF16X3 && p.n_inst > (1 << 20); }
 
+// sides and layers that the split-bf16 chain takes
+bool split_chain(const place3d_problem& p) { return p.nx % 2 == 0 && p.ny % 2 == 0 && (p.nz == 2 || p.nz == 4); }
+
+// Whether the dense contractions of a BF16X3 problem run in split bf16: where that is faster than
+// float32.  Its launches convert and write three operands for every one they read, so that grids of
+// up to 786432 bins are faster in float32 (Ex, Ey and Ez, split against float32: 66 x 70 x 2 52 us and
+// 33, 260 x 260 x 4 79 and 59, 420 x 380 x 4 89 and 80, 520 x 520 x 2 103 and 83; then 700 x 700 x 2 106 and
+// 131, 520 x 520 x 4 101 and 124, 1000 x 900 x 4 175 and 360, 512 x 512 x 6 94 and 133), and outside the
+// chain it loads element by element unless the sides are multiples of 64 (398 x 354 x 6 177 and 98,
+// 999 x 1001 x 4 1050 and 640).  Grids of up to 4096 bins are launches either way (34 x 38 x 2 35 and 34)
+// and keep it, as do large problems with their steps.
+bool split_solve(const place3d_problem& p) {
+  if (p.precision != PLACE3D_BF16X3) return false;
+  const long long bins = (long long)p.nx * p.ny * p.nz;
+  if (split_steps(p) || bins <= 4096) return true;
+  return bins > 786432 && (split_chain(p) || (p.nx % 64 == 0 && p.ny % 64 == 0));
+}
+
 int parts_bound(const place3d_problem& p, const p3d::TileGeom& t) {
   int b = std::max(p.n_nets / 4 + 16, p.n_inst / 256 + p.n_pins / 128 + 8);
   b = std::max(b, t.ntiles);
@@ -131,7 +149,7 @@ void layout_dense(place3d_ctx* c, const place3d_problem& p, Carver& w) {
   for (uint16_t** q : {&d.FyT_h, &d.FyT_l, &d.Gy_h, &d.Gy_l, &d.Hy_h, &d.Hy_l}) *q = w.take<uint16_t>(ny * ny);
   {
     auto& q = c->sc;
-    q.on = p.precision == PLACE3D_BF16X3 && nx % 2 == 0 && ny % 2 == 0 && (nz == 2 || nz == 4);
+    q.on = c->split && split_chain(p);
     if (q.on) {
       const size_t hx = nx / 2, hy = ny / 2, rx = (hx + 31) / 32 * 32, ry = (hy + 31) / 32 * 32;
       q.hx = (int)hx; q.hy = (int)hy; q.rx = (int)rx; q.ry = (int)ry;
@@ -167,6 +185,7 @@ size_t layout(place3d_ctx* c, const place3d_problem& p, char* base) {
     q.tx = w.take<float2>(p3d::kFftTable * nx); q.wx = w.take<float2>(nx / 2 + 1);
     q.ty = w.take<float2>(p3d::kFftTable * ny); q.wy = w.take<float2>(ny / 2 + 1);
   }
+  c->split = split_solve(p);
   c->step_dense = c->fft.on && split_steps(p);
   if (!c->fft.on || c->step_dense) layout_dense(c, p, w);
   c->rho = w.take<float>(map); c->phi = w.take<float>(map);

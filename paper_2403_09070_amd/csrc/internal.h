@@ -134,6 +134,7 @@ struct place3d_ctx {
   p3d::DctBases dct;
   p3d::SplitChain sc;
   p3d::FftChain fft;
+  bool split = false;                  // dense contractions in split bf16
   bool step_dense = false;             // steps keep the dense contractions beside the fast transforms
   float *map_t = nullptr, *map_a = nullptr, *map_vg = nullptr, *map_vh = nullptr;
   float *map_pc = nullptr, *map_ps = nullptr, *map_qc = nullptr;

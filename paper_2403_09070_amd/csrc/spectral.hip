@@ -696,7 +696,7 @@ int gemm(place3d_ctx* c, int M, int N, int K, int nbatch, bool left_basis, int l
   };
   if (tiles_of(64, 64) > 0x7fffffffLL) return set_err(c, PLACE3D_ERR_SIZE, "contraction grid too large");
   ProfScope prof_(c, PLACE3D_STAGE_GEMM, s);
-  if (c->prob.precision == PLACE3D_BF16X3) {
+  if (c->split) {
     // 64-row blocks when 128-row ones would leave the chip with fewer than two per compute unit
     const bool half = tiles_of(BM, BN) < 512 && M > 64;
     const dim3 grid_s((unsigned)tiles_of(half ? 64 : BM, BN));
