@@ -99,8 +99,8 @@ p3d::TileGeom tile_geom(const place3d_problem& p) {
 // The exact-adjoint form keeps the contractions: its gradient jumps where a cell's edge crosses a
 // bin face, so that after one step even the transforms' smaller rounding moves a few cells' whole
 // gradient (320k instances on 256 x 256 x 4: 6.5e-4 of the gradient's norm after two steps, where
-// the field form differs by 4e-6), and its iterates are kept as they are (386 us a step; 291 with
-// the transforms).
+// the field form differs by 4e-6), and its iterates are kept as they are: the four contractions
+// take 36 of such a step's 175 us.
 bool fft_grid(const place3d_problem& p) {
   auto side = [](int n) { return n >= 64 && n <= 2048 && (n & (n - 1)) == 0; };
   return side(p.nx) && side(p.ny) && (p.nz == 2 || p.nz == 4) && p.dgrad == PLACE3D_DGRAD_FIELD;
@@ -111,7 +111,7 @@ bool fft_grid(const place3d_problem& p) {
 // sizes and offsets when the solve rounds otherwise, and the split contractions' rounding (3.4e-6 of
 // the gradient) moves enough positions that one of 1.2M instances did so in 4 of 16 starts, against
 // none of up to 640k instances in 45 (float32: 1 of 14, none of 20).  They pay
-// for it: a step of 1.2M instances on 1024 x 1024 x 4 takes 455 us, 350 with the transforms.
+// for it: a step of 1.2M instances on 1024 x 1024 x 4 takes 433 us, 350 with the transforms.
 bool split_steps(const place3d_problem& p) { return p.precision == PLACE3D_BF16X3 && p.n_inst > (1 << 20); }
 
 // sides and layers that the split-bf16 chain takes
