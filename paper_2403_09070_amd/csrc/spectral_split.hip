@@ -37,7 +37,8 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 
-constexpr int kTile = 128;          // output tile is 128 x 128, four 64 x 64 wavefront tiles
+constexpr int kTile = 128;          // output tile is 128 x 128, eight 64 x 32 wavefront tiles
+constexpr int kThreads = 512;
 constexpr int kStep = 32;           // k per stage
 
 enum Kind { XF = 0, YF = 1, YI = 2, XI = 3 };
@@ -162,15 +163,19 @@ __device__ __forceinline__ int xfreq(int pos, int h) { return pos < h ? 2 * pos 
 
 // ------------------------------------------------------------------ contraction
 
-// kStages: LDS ring depth (32 KiB per stage)
+// kStages: LDS ring depth (32 KiB per stage).  A workgroup's loop waits in turn for its loads, its
+// fragment reads and its matrix instructions; with one wavefront per SIMD (four of 64 x 64) nothing
+// ran beside a wait.  Eight of 64 x 32 give each SIMD two, at 96 KiB of fragment reads a stage instead
+// of 64: at 1024 x 1024 x 4 the four launches went from 25, 27, 39 and 55 us to 25, 24, 34 and 51
+// (the same sums), a step of 1.2M instances from 434 to 421.
 template <int KIND, int NZ, int kStages>
-__global__ __launch_bounds__(256) void k_sgemm(SArgs g) {
+__global__ __launch_bounds__(kThreads) void k_sgemm(SArgs g) {
   constexpr bool DUAL = KIND == YI || KIND == XI;
   // stage s: [0] A hi, [1] A lo, [2] B hi, [3] B lo, each 128 rows of 32 bfloat16 (four 16-byte
   // units); unit u of row r sits at position u ^ ((r >> 1) & 3), so that the MFMA fragment reads
   // (8 consecutive rows, one unit) touch distinct banks
   __shared__ __attribute__((aligned(16))) unsigned short L[kStages][4][kTile][kStep];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wm = w >> 1, wn = w & 1;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wm = w >> 2, wc = (w & 3) * 32;
   int tm, tn, jb;
   {
     const int x = xcd_swizzle((int)blockIdx.x, (int)gridDim.x);
@@ -183,61 +188,51 @@ __global__ __launch_bounds__(256) void k_sgemm(SArgs g) {
   const SJob J = g.job[jb];
   const int KT = g.ksteps;
 
-  // each wavefront streams rows [32 w, 32 w + 32) of the four arrays, 16 rows (1 KiB) per
-  // instruction: lane i fills row 32 w + 16 j + i / 4 at position i % 4
-  const int lr = w * 32 + (lane >> 2);
-  const int unit = (lane & 3) ^ ((lr >> 1) & 3);   // the same for row lr + 16
+  // each wavefront streams rows [16 w, 16 w + 16) of the four arrays, 1 KiB per instruction: lane i
+  // fills row 16 w + i / 4 at position i % 4
+  const int lr = w * 16 + (lane >> 2);
+  const int unit = (lane & 3) ^ ((lr >> 1) & 3);
   const size_t sa = (size_t)g.ra * kStep, sb = (size_t)g.rb * kStep;   // one k block of A, of B
-  const size_t oa0 = (J.koa / kStep) * sa + (size_t)a_row<KIND, NZ>(g, tm, lr) * kStep + 8 * unit;
-  const size_t oa1 = (J.koa / kStep) * sa + (size_t)a_row<KIND, NZ>(g, tm, lr + 16) * kStep + 8 * unit;
-  const size_t ob0 = (J.kob / kStep) * sb + (size_t)b_row<KIND, NZ>(g, tn, lr) * kStep + 8 * unit;
-  const size_t ob1 = (J.kob / kStep) * sb + (size_t)b_row<KIND, NZ>(g, tn, lr + 16) * kStep + 8 * unit;
+  const size_t oa = (J.koa / kStep) * sa + (size_t)a_row<KIND, NZ>(g, tm, lr) * kStep + 8 * unit;
+  const size_t ob = (J.kob / kStep) * sb + (size_t)b_row<KIND, NZ>(g, tn, lr) * kStep + 8 * unit;
   auto issue = [&](int kt) {
     const int st = kt % kStages;
     const size_t ka = kt * sa, kb = kt * sb;
-    unsigned short* d = &L[st][0][w * 32][0];   // [0] A hi; the arrays are kTile * kStep apart
+    unsigned short* d = &L[st][0][w * 16][0];   // [0] A hi; the arrays are kTile * kStep apart
     constexpr int ARR = kTile * kStep;
-    lds_load16(J.ah + oa0 + ka, d);
-    lds_load16(J.ah + oa1 + ka, d + 16 * kStep);
-    lds_load16(J.al + oa0 + ka, d + ARR);
-    lds_load16(J.al + oa1 + ka, d + ARR + 16 * kStep);
-    lds_load16(J.bh + ob0 + kb, d + 2 * ARR);
-    lds_load16(J.bh + ob1 + kb, d + 2 * ARR + 16 * kStep);
-    lds_load16(J.bl + ob0 + kb, d + 3 * ARR);
-    lds_load16(J.bl + ob1 + kb, d + 3 * ARR + 16 * kStep);
+    lds_load16(J.ah + oa + ka, d);
+    lds_load16(J.al + oa + ka, d + ARR);
+    lds_load16(J.bh + ob + kb, d + 2 * ARR);
+    lds_load16(J.bl + ob + kb, d + 3 * ARR);
   };
-  constexpr int kLoadsPerStage = 8;
+  constexpr int kLoadsPerStage = 4;
 
-  f32x16 acc[2][2][2];
+  f32x16 acc[2][2];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) acc[h][a][b] = (f32x16)(0.f);
+    for (int a = 0; a < 2; ++a) acc[h][a] = (f32x16)(0.f);
 
-  auto mma = [&](int st, f32x16 (&C)[2][2]) {
+  auto mma = [&](int st, f32x16 (&C)[2]) {
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
       const int u = 2 * kk + (lane >> 5);
-      bf16x8 ah[2], al[2], bh[2], bl[2];
+      bf16x8 ah[2], al[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        const int ar = wm * 64 + t * 32 + (lane & 31), br = wn * 64 + t * 32 + (lane & 31);
-        const int pa = 8 * (u ^ ((ar >> 1) & 3)), pb = 8 * (u ^ ((br >> 1) & 3));
+        const int ar = wm * 64 + t * 32 + (lane & 31), pa = 8 * (u ^ ((ar >> 1) & 3));
         ah[t] = *reinterpret_cast<const bf16x8*>(&L[st][0][ar][pa]);
         al[t] = *reinterpret_cast<const bf16x8*>(&L[st][1][ar][pa]);
-        bh[t] = *reinterpret_cast<const bf16x8*>(&L[st][2][br][pb]);
-        bl[t] = *reinterpret_cast<const bf16x8*>(&L[st][3][br][pb]);
       }
+      const int br = wc + (lane & 31), pb = 8 * (u ^ ((br >> 1) & 3));
+      const bf16x8 bh = *reinterpret_cast<const bf16x8*>(&L[st][2][br][pb]);
+      const bf16x8 bl = *reinterpret_cast<const bf16x8*>(&L[st][3][br][pb]);
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          C[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh[b], C[a][b], 0, 0, 0);
-          C[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl[b], C[a][b], 0, 0, 0);
-          C[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh[b], C[a][b], 0, 0, 0);
-        }
+      for (int a = 0; a < 2; ++a) {
+        C[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh, C[a], 0, 0, 0);
+        C[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl, C[a], 0, 0, 0);
+        C[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh, C[a], 0, 0, 0);
+      }
     }
   };
   // Stage kt is waited for by count: the loads of the kStages - 2 later stages may still be in
@@ -282,33 +277,30 @@ __global__ __launch_bounds__(256) void k_sgemm(SArgs g) {
     uint16_t* oh = upper ? J.oh1 : J.oh0;
     uint16_t* ol = upper ? J.ol1 : J.ol0;
     const int yk = yp0 + 32 * wm;   // first y' of the k block (ry and yk are multiples of 32)
+    const int n = tn * kTile + wc + (lane & 31);
+    u32x4 hv[4], lv[4];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int n = tn * kTile + wn * 64 + b * 32 + (lane & 31);
-      u32x4 hv[4], lv[4];
+    for (int a = 0; a < 2; ++a) {
+      float v[16];
 #pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        float v[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float own = acc[0][a][b][r], oth = other_half(own, upper);
-          const float sv = upper ? oth - own : own + oth;
-          v[r] = yk + 16 * a + r < g.hy ? sv : 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const u32x2 t_ = split2(v[2 * e], v[2 * e + 1]);
-          hv[2 * a + e / 4][e % 4] = t_[0];
-          lv[2 * a + e / 4][e % 4] = t_[1];
-        }
+      for (int r = 0; r < 16; ++r) {
+        const float own = acc[0][a][r], oth = other_half(own, upper);
+        const float sv = upper ? oth - own : own + oth;
+        v[r] = yk + 16 * a + r < g.hy ? sv : 0.f;
       }
-      if (n < g.hx && yk < g.ry) {
-        const size_t o = ((size_t)(yk / kStep) * g.ro + (size_t)(z * g.nx + J.sel * g.hx + n)) * kStep;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          *reinterpret_cast<u32x4*>(oh + o + 8 * q) = hv[q];
-          *reinterpret_cast<u32x4*>(ol + o + 8 * q) = lv[q];
-        }
+      for (int e = 0; e < 8; ++e) {
+        const u32x2 t_ = split2(v[2 * e], v[2 * e + 1]);
+        hv[2 * a + e / 4][e % 4] = t_[0];
+        lv[2 * a + e / 4][e % 4] = t_[1];
+      }
+    }
+    if (n < g.hx && yk < g.ry) {
+      const size_t o = ((size_t)(yk / kStep) * g.ro + (size_t)(z * g.nx + J.sel * g.hx + n)) * kStep;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        *reinterpret_cast<u32x4*>(oh + o + 8 * q) = hv[q];
+        *reinterpret_cast<u32x4*>(ol + o + 8 * q) = lv[q];
       }
     }
   } else if constexpr (KIND == YF) {
@@ -319,45 +311,43 @@ __global__ __launch_bounds__(256) void k_sgemm(SArgs g) {
 #pragma unroll
     for (int z = 0; z < NZ; ++z) fz[z] = g.zmat[z * kMaxNz + lz];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a) {
+      const int c = wc + (lane & 31);
+      const int kx = tn * (kTile / NZ) + c / NZ;
+      const int j = xfreq(kx, g.hx);
+      float o[16];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int c = wn * 64 + b * 32 + (lane & 31);
-        const int kx = tn * (kTile / NZ) + c / NZ;
-        const int j = xfreq(kx, g.hx);
-        float o[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float v = acc[0][a][b][r];
-          float s = fz[0] * group_lane<NZ, 0>(v);
-          if constexpr (NZ > 1) s += fz[1] * group_lane<NZ, 1>(v);
-          if constexpr (NZ > 2) {
-            s += fz[2] * group_lane<NZ, 2>(v);
-            s += fz[3] * group_lane<NZ, 3>(v);
-          }
-          o[r] = s;
+      for (int r = 0; r < 16; ++r) {
+        const float v = acc[0][a][r];
+        float s = fz[0] * group_lane<NZ, 0>(v);
+        if constexpr (NZ > 1) s += fz[1] * group_lane<NZ, 1>(v);
+        if constexpr (NZ > 2) {
+          s += fz[2] * group_lane<NZ, 2>(v);
+          s += fz[3] * group_lane<NZ, 3>(v);
         }
-        if (kx < g.nx) {
+        o[r] = s;
+      }
+      if (kx < g.nx) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int ky0 = tm * kTile + wm * 64 + a * 32 + 8 * q + 4 * (lane >> 5);
-            if (ky0 >= g.ry) continue;
-            float v4[4];
+        for (int q = 0; q < 4; ++q) {
+          const int ky0 = tm * kTile + wm * 64 + a * 32 + 8 * q + 4 * (lane >> 5);
+          if (ky0 >= g.ry) continue;
+          float v4[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int ky = ky0 + e;
-              v4[e] = ky < g.hy ? o[4 * q + e] * inv_w2(g, j, 2 * ky + J.sel, lz) : 0.f;
-            }
-            u32x2 hh, ll;
-            { const u32x2 t_ = split2(v4[0], v4[1]); hh[0] = t_[0]; ll[0] = t_[1]; }
-            { const u32x2 t_ = split2(v4[2], v4[3]); hh[1] = t_[0]; ll[1] = t_[1]; }
-            const int kcol = J.sel * g.ry + ky0;
-            const size_t off = ((size_t)(kcol / kStep) * g.ro + (size_t)(kx * NZ + lz)) * kStep + kcol % kStep;
-            *reinterpret_cast<u32x2*>(J.oh0 + off) = hh;
-            *reinterpret_cast<u32x2*>(J.ol0 + off) = ll;
+          for (int e = 0; e < 4; ++e) {
+            const int ky = ky0 + e;
+            v4[e] = ky < g.hy ? o[4 * q + e] * inv_w2(g, j, 2 * ky + J.sel, lz) : 0.f;
           }
+          u32x2 hh, ll;
+          { const u32x2 t_ = split2(v4[0], v4[1]); hh[0] = t_[0]; ll[0] = t_[1]; }
+          { const u32x2 t_ = split2(v4[2], v4[3]); hh[1] = t_[0]; ll[1] = t_[1]; }
+          const int kcol = J.sel * g.ry + ky0;
+          const size_t off = ((size_t)(kcol / kStep) * g.ro + (size_t)(kx * NZ + lz)) * kStep + kcol % kStep;
+          *reinterpret_cast<u32x2*>(J.oh0 + off) = hh;
+          *reinterpret_cast<u32x2*>(J.ol0 + off) = ll;
         }
       }
+    }
   } else if constexpr (KIND == YI) {
     // rows: register quad q -> layer q % NZ and x bits (q / NZ) << 3, register r % 4 and lane
     // half -> x bits 0-2; column = y'.  V(y') = E + O, V(ny-1-y') = E - O (cosine, sel 0) or
@@ -374,31 +364,29 @@ __global__ __launch_bounds__(256) void k_sgemm(SArgs g) {
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < 2; ++a) {
+        const int yl = wc + (lane & 31);
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const int yl = wn * 64 + b * 32 + (lane & 31);
+        for (int gq = 0; gq < 4 / NZ; ++gq) {
+          const int kxl = (wm * 2 + a) * (32 / NZ) + (gq << 3) + ((lane >> 5) << 2);
 #pragma unroll
-          for (int gq = 0; gq < 4 / NZ; ++gq) {
-            const int kxl = (wm * 2 + a) * (32 / NZ) + (gq << 3) + ((lane >> 5) << 2);
+          for (int l = 0; l < NZ; ++l) {
+            float o[4];
 #pragma unroll
-            for (int l = 0; l < NZ; ++l) {
-              float o[4];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const float E = acc[0][a][b][4 * (gq * NZ + l) + e], O = acc[1][a][b][4 * (gq * NZ + l) + e];
-                o[e] = side == 0 ? E + O : (cosine ? E - O : O - E);
-              }
-              const u32x2 t0 = split2(o[0], o[1]), t1 = split2(o[2], o[3]);
-              const int at = (l * kTile + yl) * SR + kxl;
-              *reinterpret_cast<u32x2*>(S + at) = (u32x2){t0[0], t1[0]};
-              *reinterpret_cast<u32x2*>(S + PL + at) = (u32x2){t0[1], t1[1]};
+            for (int e = 0; e < 4; ++e) {
+              const float E = acc[0][a][4 * (gq * NZ + l) + e], O = acc[1][a][4 * (gq * NZ + l) + e];
+              o[e] = side == 0 ? E + O : (cosine ? E - O : O - E);
             }
+            const u32x2 t0 = split2(o[0], o[1]), t1 = split2(o[2], o[3]);
+            const int at = (l * kTile + yl) * SR + kxl;
+            *reinterpret_cast<u32x2*>(S + at) = (u32x2){t0[0], t1[0]};
+            *reinterpret_cast<u32x2*>(S + PL + at) = (u32x2){t0[1], t1[1]};
           }
         }
+      }
       __syncthreads();
       // copy out: consecutive threads take consecutive 16-byte chunks of consecutive rows
-      for (int idx = tid; idx < 2 * NZ * kTile * CH; idx += 256) {
+      for (int idx = tid; idx < 2 * NZ * kTile * CH; idx += kThreads) {
         const int hl = idx / (NZ * kTile * CH), rem = idx % (NZ * kTile * CH);
         const int c = rem % CH, rl = rem / CH, l = rl / kTile, yl = rl % kTile;
         const int yp = tn * kTile + yl;
@@ -429,38 +417,36 @@ __global__ __launch_bounds__(256) void k_sgemm(SArgs g) {
     // sg Z^T (E - O) at the mirror nx-1-x', Z = Gz or Hz
     const float* Z = g.zmat + (J.sel ? 2 : 1) * kMaxNz * kMaxNz;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a) {
+      const int xp = tn * kTile + wc + (lane & 31);
+      if (xp >= g.hx) continue;
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int xp = tn * kTile + wn * 64 + b * 32 + (lane & 31);
-        if (xp >= g.hx) continue;
+      for (int gq = 0; gq < 4 / NZ; ++gq)
 #pragma unroll
-        for (int gq = 0; gq < 4 / NZ; ++gq)
+        for (int e = 0; e < 4; ++e) {
+          const int y = tm * (kTile / NZ) + (wm * 2 + a) * (32 / NZ) + (gq << 3) + ((lane >> 5) << 2) + e;
+          if (y >= g.ny) continue;
+          float u[NZ], v[NZ];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int y = tm * (kTile / NZ) + (wm * 2 + a) * (32 / NZ) + (gq << 3) + ((lane >> 5) << 2) + e;
-            if (y >= g.ny) continue;
-            float u[NZ], v[NZ];
+          for (int l = 0; l < NZ; ++l) {
+            const float E = acc[0][a][4 * (gq * NZ + l) + e], O = acc[1][a][4 * (gq * NZ + l) + e];
+            u[l] = E + O;
+            v[l] = E - O;
+          }
+#pragma unroll
+          for (int z = 0; z < NZ; ++z) {
+            float pu = 0.f, pv = 0.f;
 #pragma unroll
             for (int l = 0; l < NZ; ++l) {
-              const float E = acc[0][a][b][4 * (gq * NZ + l) + e], O = acc[1][a][b][4 * (gq * NZ + l) + e];
-              u[l] = E + O;
-              v[l] = E - O;
+              pu += Z[l * kMaxNz + z] * u[l];
+              pv += Z[l * kMaxNz + z] * v[l];
             }
-#pragma unroll
-            for (int z = 0; z < NZ; ++z) {
-              float pu = 0.f, pv = 0.f;
-#pragma unroll
-              for (int l = 0; l < NZ; ++l) {
-                pu += Z[l * kMaxNz + z] * u[l];
-                pv += Z[l * kMaxNz + z] * v[l];
-              }
-              float* row = J.of + (size_t)(z * g.ny + y) * g.nx;
-              row[xp] = pu;
-              row[g.nx - 1 - xp] = J.sg * pv;
-            }
+            float* row = J.of + (size_t)(z * g.ny + y) * g.nx;
+            row[xp] = pu;
+            row[g.nx - 1 - xp] = J.sg * pv;
           }
-      }
+        }
+    }
   }
 }
 
@@ -538,10 +524,11 @@ int launch(place3d_ctx* c, SArgs& a, int njobs, hipStream_t s, int& made) {
   if (tiles > 0x7fffffffLL) return set_err(c, PLACE3D_ERR_SIZE, "contraction grid too large");
   for (int i = njobs; i < kMaxJobs; ++i) a.job[i] = a.job[0];
   ++made;
-  const dim3 grid((unsigned)tiles), block(256);
-  // three stages for the launches of one workgroup per compute unit, two for the x inverse,
-  // whose 768 workgroups then run two per compute unit
-  constexpr int ST = KIND == XI ? 2 : 3;
+  // four stages for the launches of one workgroup per compute unit (three: 422 us a step of 1.2M
+  // instances against 421), two for the x inverse, whose 768 workgroups then run two per compute unit
+  // (three stages and one: 61 us against 51)
+  constexpr int ST = KIND == XI ? 2 : 4;
+  const dim3 grid((unsigned)tiles), block(kThreads);
   if (a.nz == 2) hipLaunchKernelGGL((k_sgemm<KIND, 2, ST>), grid, block, 0, s, a);
   else hipLaunchKernelGGL((k_sgemm<KIND, 4, ST>), grid, block, 0, s, a);
   P3D_LAUNCH(c, "k_sgemm");
