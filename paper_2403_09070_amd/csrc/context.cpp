@@ -111,7 +111,7 @@ bool fft_grid(const place3d_problem& p) {
 // sizes and offsets when the solve rounds otherwise, and the split contractions' rounding (3.4e-6 of
 // the gradient) moves enough positions that one of 1.2M instances did so in 4 of 16 starts, against
 // none of up to 640k instances in 45 (float32: 1 of 14, none of 20).  They pay
-// for it: a step of 1.2M instances on 1024 x 1024 x 4 takes 433 us, 350 with the transforms.
+// for it: a step of 1.2M instances on 1024 x 1024 x 4 takes 421 us, 350 with the transforms.
 bool split_steps(const place3d_problem& p) { return p.precision == PLACE3D_BF16X3 && p.n_inst > (1 << 20); }
 
 // sides and layers that the split-bf16 chain takes
@@ -119,12 +119,13 @@ bool split_chain(const place3d_problem& p) { return p.nx % 2 == 0 && p.ny % 2 ==
 
 // Whether the dense contractions of a BF16X3 problem run in split bf16: where that is faster than
 // float32.  Its launches convert and write three operands for every one they read, so that grids of
-// up to 786432 bins are faster in float32 (Ex, Ey and Ez, split against float32: 66 x 70 x 2 52 us and
-// 33, 260 x 260 x 4 79 and 59, 420 x 380 x 4 89 and 80, 520 x 520 x 2 103 and 83; then 700 x 700 x 2 106 and
-// 131, 520 x 520 x 4 101 and 124, 1000 x 900 x 4 175 and 360, 512 x 512 x 6 94 and 133), and outside the
-// chain it loads element by element unless the sides are multiples of 64 (398 x 354 x 6 177 and 98,
-// 999 x 1001 x 4 1050 and 640).  Grids of up to 4096 bins are launches either way (34 x 38 x 2 35 and 34)
-// and keep it, as do large problems with their steps.
+// up to 786432 bins are faster in float32, or level (Ex, Ey and Ez, split against float32: 66 x 70 x 2
+// 37 us and 32, 260 x 260 x 4 62 and 56, 420 x 380 x 4 71 and 77, 520 x 520 x 2 78 and 81; phi alone 37
+// and 30, 61 and 47, 69 and 58, 77 and 65; then 700 x 700 x 2 88 and 131, 520 x 520 x 4 83 and 124,
+// 1000 x 900 x 4 170 and 360, 512 x 512 x 6 94 and 133), and outside the chain it loads element by
+// element unless the sides are multiples of 64 (398 x 354 x 6 177 and 98, 999 x 1001 x 4 1050 and 640).
+// Grids of up to 4096 bins are launches either way (32 x 32 x 4 29, 34 x 38 x 2 34 in float32) and keep
+// it, as do large problems with their steps.
 bool split_solve(const place3d_problem& p) {
   if (p.precision != PLACE3D_BF16X3) return false;
   const long long bins = (long long)p.nx * p.ny * p.nz;

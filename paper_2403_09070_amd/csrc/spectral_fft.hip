@@ -31,7 +31,7 @@
 // 2.4 and 3.8 TB/s against 5.1 for a copy); their vector instructions alone take about 3, 10 and 9 us,
 // and two or three wavefronts per SIMD, the registers' and the grid's limit, leave the LDS and load
 // latencies of their one or two rounds in sight.  The four dense split contractions and the fold
-// they replace took 154 us, the float32 ones with their z passes 418 us.
+// they replace take 143 us, the float32 ones with their z passes 418 us.
 #include <cmath>
 
 #include "internal.h"
