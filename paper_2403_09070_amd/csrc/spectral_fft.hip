@@ -260,10 +260,15 @@ __device__ __forceinline__ cf series(bool sine, float wk, float wm, float ck, fl
 
 struct FftTabs { const cf *tx, *wx, *ty, *wy; };   // the stages' twiddles and w_k, k <= N / 2, per axis
 
-// groups per workgroup: 16 rows y per workgroup where the grid then still fills the chip, so that
-// the transposed rows are written in runs of 64 bytes
-template <int N> constexpr int x_groups() { return N == 512 || N == 2048 ? 4 : 8; }
-template <int N> constexpr int x_threads() { return x_groups<N>() * lanes_of<N>(); }
+// Groups of lanes per workgroup of the x pass.  Sixteen rows y (eight groups) write the transposed
+// rows in runs of 64 bytes and pay where the grid fills the chip several times over, eight rows split
+// small grids better; at sides of 512 and up the line is kWideRows rows of all maps (eight rows and
+// sixteen, Ex, Ey and Ez: 2048 x 2048 x 4 278 and 262 us, 1024 x 2048 x 4 112.5 and 110.4,
+// 512 x 2048 x 4 62.1 and 61.6; 2048 x 1024 x 4 115.4 and 116.5, 1024 x 1024 x 4 56.2 and 56.7, 2048 x 512 x 4
+// 65.7 and 70.0, 2048 x 64 x 2 22.6 and 28.2).  Shorter sides have groups of 16
+// or 32 lanes and keep eight.
+constexpr int kWideRows = 8192;
+template <int N, int G> constexpr int x_threads() { return G * lanes_of<N>(); }
 
 // A reference value of a layer, the mean of 64 of its bins spread over it (one per lane, the same in
 // every wavefront).  The transforms take the map less its layers' references, which only the (0, 0)
@@ -281,11 +286,11 @@ struct FftMapIn { const float* p[kMaxMany]; };
 struct FftMapOut { float* p[kMaxMany]; };
 
 // x forward: rows (z, y), two per FFT, to t[x frequency][z][y], with the x normalisation
-template <int N>
-__global__ __launch_bounds__(x_threads<N>()) void k_fft_x(FftMapIn maps, int ny, int nz, FftTabs tb, FftMapOut outs) {
+template <int N, int G>
+__global__ __launch_bounds__((x_threads<N, G>())) void k_fft_x(FftMapIn maps, int ny, int nz, FftTabs tb, FftMapOut outs) {
   const float* __restrict__ rho = maps.p[blockIdx.y];
   float* __restrict__ out = outs.p[blockIdx.y];
-  constexpr int E = Plan<N>::E, T = lanes_of<N>(), G = x_groups<N>(), RW = 2 * G;
+  constexpr int E = Plan<N>::E, T = lanes_of<N>(), RW = 2 * G;
   constexpr int kBuf = G * buf_of<N>() * 2, kTileF = N * (RW + 1);      // floats
   __shared__ __attribute__((aligned(16))) float L[kBuf > kTileF ? kBuf : kTileF];
   const int t = threadIdx.x & (T - 1), f = threadIdx.x / T;
@@ -338,7 +343,7 @@ __global__ __launch_bounds__(x_threads<N>()) void k_fft_x(FftMapIn maps, int ny,
   __syncthreads();
   // four consecutive y of one frequency per thread
   constexpr int Q = RW / 4;
-  for (int i = threadIdx.x; i < N * Q; i += x_threads<N>()) {
+  for (int i = threadIdx.x; i < N * Q; i += x_threads<N, G>()) {
     const int k = i / Q, q = i % Q;
     const float* s = L + k * (RW + 1) + 4 * q;
     *reinterpret_cast<float4*>(out + ((size_t)k * nz + z) * ny + y0 + 4 * q) = make_float4(s[0], s[1], s[2], s[3]);
@@ -701,8 +706,15 @@ int field_fft_many(place3d_ctx* const* c, const float* const* rho, float* const*
   }
   with_side(nx, [&](auto side) {
     constexpr int N = decltype(side)::value;
-    hipLaunchKernelGGL((k_fft_x<N>), dim3(nz * ny / (2 * x_groups<N>()), nb), dim3(x_threads<N>()), 0, s, in, ny, nz, tb,
-                       t_out);
+    auto go = [&](auto groups) {
+      constexpr int G = decltype(groups)::value;
+      hipLaunchKernelGGL((k_fft_x<N, G>), dim3(nz * ny / (2 * G), nb), dim3(x_threads<N, G>()), 0, s, in, ny, nz, tb,
+                         t_out);
+    };
+    if constexpr (N >= 512) {
+      if (nb * nz * ny < kWideRows) return go(std::integral_constant<int, 4>{});
+    }
+    go(std::integral_constant<int, 8>{});
   });
   P3D_LAUNCH(c[0], "k_fft_x");
   if (!need_g && !need_h) return PLACE3D_OK;

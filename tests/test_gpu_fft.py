@@ -54,6 +54,12 @@ def test_every_length_matches_the_oracle(nx, ny, nz, precision):
         assert all(torch.equal(part[k], out[k]) for k in want), want
 
 
+@pytest.mark.parametrize("nx,ny,nz", [(512, 2048, 4), (1024, 2048, 4)])
+def test_sixteen_rows_a_workgroup_match_the_oracle(nx, ny, nz):
+    """Maps of 8192 rows and more, where the x pass takes sixteen rows a workgroup at every side."""
+    test_every_length_matches_the_oracle(nx, ny, nz, 0)
+
+
 @pytest.mark.parametrize("nx,ny,nz", [(64, 64, 4), (1024, 128, 2)])
 def test_unaligned_maps_give_the_same_values(nx, ny, nz):
     """The map and the outputs at 4-byte aligned addresses (a slice of a larger array)."""
