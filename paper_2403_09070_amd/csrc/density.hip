@@ -940,11 +940,14 @@ __device__ __forceinline__ void density_of_tiles(Geom g, TileGeom t, const float
       auto sums_of = [&](int q) { return sums + (size_t)(q == 0 ? ch.max_extra + e0 : e0 + q - 1) * 2 * tsz; };
       // stores the LDS sums as those of chunk q (past the cache, so that the fence finds little to
       // write back) and counts them: true for the last of `of` workgroups to do so, which then sees
-      // the others' sums.  One thread fences for the workgroup.
+      // the others' sums.  Every wavefront waits for its own stores before the barrier, which waits
+      // for none; the one thread that then fences and counts would otherwise wait for those of its
+      // wavefront alone.
       auto hand_in = [&](int q, int32_t* count, int of) {
         unsigned long long* to = sums_of(q);
         for (int k = threadIdx.x; k < used; k += blockDim.x)
           __hip_atomic_store(to + k, S64[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (threadIdx.x == 0) {
           __threadfence();
