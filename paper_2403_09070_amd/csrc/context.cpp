@@ -185,6 +185,7 @@ size_t layout(place3d_ctx* c, const place3d_problem& p, char* base) {
     auto& q = c->fft;
     q.tx = w.take<float2>(p3d::kFftTable * nx); q.wx = w.take<float2>(nx / 2 + 1);
     q.ty = w.take<float2>(p3d::kFftTable * ny); q.wy = w.take<float2>(ny / 2 + 1);
+    q.mean = w.take<float>(nz * ny / 2);
   }
   c->split = split_solve(p);
   c->step_dense = c->fft.on && split_steps(p);

@@ -99,12 +99,13 @@ struct SplitChain {
 };
 
 // Fast transforms of the solve (fft_grid in context.cpp): tables per axis, the stages'
-// twiddles (at most kFftTable N entries) and e^{-i pi k / 2N} (k <= N / 2).  The dense bases and
-// the split chain are then not built.
+// twiddles (at most kFftTable N entries) and e^{-i pi k / 2N} (k <= N / 2), and the means of the rows in
+// hand ([nz][ny / 2], a call's scratch).  The dense bases and the split chain are then not built.
 constexpr int kFftTable = 2;
 struct FftChain {
   int on = 0;
   float2 *tx = nullptr, *wx = nullptr, *ty = nullptr, *wy = nullptr;
+  float* mean = nullptr;
 };
 
 }  // namespace p3d

@@ -270,24 +270,33 @@ struct FftTabs { const cf *tx, *wx, *ty, *wy; };   // the stages' twiddles and w
 constexpr int kWideRows = 8192;
 template <int N, int G> constexpr int x_threads() { return G * lanes_of<N>(); }
 
-// A reference value of a layer, the mean of 64 of its bins spread over it (one per lane, the same in
-// every wavefront).  The transforms take the map less its layers' references, which only the (0, 0)
-// modes see again: the rounding of a transform is relative to what it sums, and an even density is
-// mostly its mean, which the potential leaves out.
-__device__ __forceinline__ float layer_ref(const float* __restrict__ plane, int nx, int ny) {
-  const int lane = threadIdx.x & (kWave - 1);
-  float v = plane[(size_t)(lane * (ny / 64) + ny / 128) * nx + ((lane * 37) & 63) * (nx / 64) + nx / 128];
-  for (int m = kWave / 2; m > 0; m >>= 1) v += __shfl_xor(v, m);
-  return v * (1.f / 64.f);
+// The sum of v over a group's lanes, the same in all of them.  at: two floats of LDS for a group of two
+// wavefronts (N = 2048), which every group of the workgroup then reaches alike.
+template <int N>
+__device__ __forceinline__ float group_sum(float v, int t, float* at) {
+  constexpr int T = lanes_of<N>();
+  for (int m = (T < kWave ? T : kWave) / 2; m > 0; m >>= 1) v += __shfl_xor(v, m);
+  if constexpr (T > kWave) {
+    if (t % kWave == 0) at[t / kWave] = v;
+    __syncthreads();
+    v = at[0] + at[1];
+  }
+  return v;
 }
 
 // the maps of a launch (of one problem, or of the layers of a multi-die one)
 struct FftMapIn { const float* p[kMaxMany]; };
 struct FftMapOut { float* p[kMaxMany]; };
 
-// x forward: rows (z, y), two per FFT, to t[x frequency][z][y], with the x normalisation
+// x forward: rows (z, y), two per FFT, to t[x frequency][z][y], with the x normalisation.
+// The rows are transformed less the mean of the two, which goes to mean[z][y / 2] and which only the y
+// transform of x frequency 0 sees again: the rounding of a transform is relative to what it sums, and an
+// even density is mostly its mean, which the potential leaves out.  (A mean never makes what is
+// summed larger, whatever the rows hold.  One value a layer, the mean of 64 of its bins, did where one of
+// them held a peak: a bin of 1e4 over a density of 0.85 on 1024 x 1024 x 2, phi's error 4.1e-5, 2.3e-7 so.)
 template <int N, int G>
-__global__ __launch_bounds__((x_threads<N, G>())) void k_fft_x(FftMapIn maps, int ny, int nz, FftTabs tb, FftMapOut outs) {
+__global__ __launch_bounds__((x_threads<N, G>())) void k_fft_x(FftMapIn maps, int ny, int nz, FftTabs tb, FftMapOut outs,
+                                                              FftMapOut means) {
   const float* __restrict__ rho = maps.p[blockIdx.y];
   float* __restrict__ out = outs.p[blockIdx.y];
   constexpr int E = Plan<N>::E, T = lanes_of<N>(), RW = 2 * G;
@@ -306,9 +315,13 @@ __global__ __launch_bounds__((x_threads<N, G>())) void k_fft_x(FftMapIn maps, in
       const int i = ln.sample(s);
       x[s] = {a[i], b[i]};
     }
-    const float ref = layer_ref(rho + (size_t)z * ny * N, N, ny);
+    float sum = 0.f;
 #pragma unroll
-    for (int s = 0; s < E; ++s) x[s] = {x[s].x - ref, x[s].y - ref};
+    for (int s = 0; s < E; ++s) sum += x[s].x + x[s].y;
+    const float mean = group_sum<N>(sum, t, reinterpret_cast<float*>(buf)) * (0.5f / N);
+#pragma unroll
+    for (int s = 0; s < E; ++s) x[s] = {x[s].x - mean, x[s].y - mean};
+    if (t == 0) means.p[blockIdx.y][row0 / 2 + f] = mean;
   }
   fft<N>(x, ln, buf, tb.tx);
   const PairW<N> pw(tb.wx, t);
@@ -351,8 +364,7 @@ __global__ __launch_bounds__((x_threads<N, G>())) void k_fft_x(FftMapIn maps, in
 }
 
 struct FftYArgs {
-  int nx;
-  FftMapIn rho;                  // the map, for its layers' references
+  FftMapIn mean;                 // [nz][N / 2] what the x pass took off the rows
   float px2, py, py2, pz2;       // (pi / length)^2, pi / d_y
   const float* zmat;
   FftMapIn t;                    // [nx][nz][N]
@@ -392,7 +404,30 @@ __global__ __launch_bounds__((y_threads<N, NZ>()), 2) void k_fft_y(FftYArgs g, F
       const int n = ln.sample(s);
       x[s] = {r0[n], r1[n]};
     }
+    // x frequency 0 gets the rows' means back, less the layer's, which goes to frequency (0, 0)
+    float ref0 = 0.f, ref1 = 0.f;
+    if (kx2 == pr) {                                     // its workgroup
+      const float* m0 = g.mean.p[blockIdx.y] + (size_t)(2 * r) * (N / 2);
+      float a[E], b[E];
+#pragma unroll
+      for (int s = 0; s < E; ++s) {
+        const int n = ln.sample(s) / 2;
+        a[s] = m0[n];
+        b[s] = m0[N / 2 + n];
+        ref0 += a[s];
+        ref1 += b[s];
+      }
+      ref0 = group_sum<N>(ref0, t, reinterpret_cast<float*>(buf)) * (1.f / N);
+      ref1 = group_sum<N>(ref1, t, reinterpret_cast<float*>(buf) + 2) * (1.f / N);
+      if (kx == 0) {
+#pragma unroll
+        for (int s = 0; s < E; ++s) x[s] = {x[s].x + (a[s] - ref0), x[s].y + (b[s] - ref1)};
+      } else {
+        ref0 = ref1 = 0.f;
+      }
+    }
     fft<N>(x, ln, buf, tb.ty);
+    if (t == 0) x[0] = {x[0].x + (float)N * ref0, x[0].y + (float)N * ref1};
     put<N>(x, ln, buf);
   }
   __syncthreads();
@@ -427,12 +462,7 @@ __global__ __launch_bounds__((y_threads<N, NZ>()), 2) void k_fft_y(FftYArgs g, F
       for (int l = 0; l < NZ; ++l)
         b[j][l] = {fmaf(f1[l], vb.x, fmaf(f0[l], va.x, b[j][l].x)), fmaf(f1[l], vb.y, fmaf(f0[l], va.y, b[j][l].y))};
     }
-    cf z0 = zb[0];
-    if (kx2 == pr) {                                     // the workgroup of x frequency 0
-      const float* plane = g.rho.p[blockIdx.y] + (size_t)(2 * p) * g.nx * N;
-      const float c0 = layer_ref(plane, g.nx, N), c1 = layer_ref(plane + (size_t)g.nx * N, g.nx, N);
-      if (kx == 0) z0 = {z0.x + (float)N * c0, z0.y + (float)N * c1};
-    }
+    const cf z0 = zb[0];
 #pragma unroll
     for (int l = 0; l < NZ; ++l) b0[l] = fmaf(f1[l], z0.y, fmaf(f0[l], z0.x, b0[l]));
   }
@@ -696,11 +726,12 @@ int field_fft_many(place3d_ctx* const* c, const float* const* rho, float* const*
   prof_.launches = 3;
   // every context asks for the same outputs
   const bool need_g = phi[0] || ex[0] || ez[0], need_h = ey[0] != nullptr;
-  FftMapIn in{}, t_in{};
-  FftMapOut t_out{}, vg{}, vh{};
+  FftMapIn in{}, t_in{}, mean_in{};
+  FftMapOut t_out{}, mean_out{}, vg{}, vh{};
   for (int i = 0; i < nb; ++i) {
     in.p[i] = rho[i];
     t_in.p[i] = t_out.p[i] = c[i]->map_t;
+    mean_in.p[i] = mean_out.p[i] = c[i]->fft.mean;
     vg.p[i] = need_g ? c[i]->map_vg : nullptr;
     vh.p[i] = need_h ? c[i]->map_vh : nullptr;
   }
@@ -709,7 +740,7 @@ int field_fft_many(place3d_ctx* const* c, const float* const* rho, float* const*
     auto go = [&](auto groups) {
       constexpr int G = decltype(groups)::value;
       hipLaunchKernelGGL((k_fft_x<N, G>), dim3(nz * ny / (2 * G), nb), dim3(x_threads<N, G>()), 0, s, in, ny, nz, tb,
-                         t_out);
+                         t_out, mean_out);
     };
     if constexpr (N >= 512) {
       if (nb * nz * ny < kWideRows) return go(std::integral_constant<int, 4>{});
@@ -718,7 +749,7 @@ int field_fft_many(place3d_ctx* const* c, const float* const* rho, float* const*
   });
   P3D_LAUNCH(c[0], "k_fft_x");
   if (!need_g && !need_h) return PLACE3D_OK;
-  const FftYArgs ya{nx, in, (float)(px * px), (float)py, (float)(py * py), (float)(pz * pz), c[0]->dct.zmat, t_in, vg, vh};
+  const FftYArgs ya{mean_in, (float)(px * px), (float)py, (float)(py * py), (float)(pz * pz), c[0]->dct.zmat, t_in, vg, vh};
   with_side(ny, [&](auto side) {
     constexpr int N = decltype(side)::value;
     const int pairs = nx / 2;
