@@ -3,7 +3,7 @@
 // Sec. IV-B: incremental evaluation from first and second extremes).
 //
 // Work split: a net of degree d is taken by a group of G = 1, 2, 4, ..., 64 lanes, the smallest
-// with d <= kPinsPerLane * G (64 lanes for larger nets, whose lanes then loop); most nets have
+// with d <= kPinsPerLane * G (64 lanes for larger nets, wl_wide); most nets have
 // few pins and are taken by a single lane.  Lane l of a group holds pins l, l + G, ... in
 // registers and the group takes one axis after the other, x, y, z: first and second largest and
 // smallest pin coordinate per die set (in z the extremes of the whole net); max-shifted
@@ -16,7 +16,7 @@
 // result in a line of its own: 360 MB in 71 us, 5 TB/s); with it the latency of the loads, three
 // deep (net, owner, coordinates), against the wavefronts that the registers allow.  So all loads of
 // a lane's pins are issued before any is used, and the axes follow one another, one axis's extremes,
-// sums and coefficients live at a time (125 registers, four wavefronts a SIMD, against 155 and three
+// sums and coefficients live at a time (126 registers, four wavefronts a SIMD, against 155 and three
 // with all axes at once; 1.2M instances, 4.5M pins: 85 us in float32 sums and 93 in compensated ones,
 // against 110 and 119).  Masking a lane's absent pins instead of branching round them makes 17 %
 // fewer instructions but holds 143 registers: no faster.
@@ -215,10 +215,10 @@ __device__ __forceinline__ void sums_add(Sums4<C>& s, bool in, float du, float d
   s.tm.add_small(in ? dl * em : 0.f);
 }
 
-// one pin's terms along one axis: u its coordinate, (M, m) the extremes of its own set
+// one pin's terms along one axis: u its coordinate, relative to the extremes of its own set
 template <bool C>
-__device__ __forceinline__ void sums_axis(AxisSums<C>& S, bool top, float u, float M, float m, float ig) {
-  const float du = u - M, dl = u - m;
+__device__ __forceinline__ void sums_axis(AxisSums<C>& S, bool top, float u, const SetExt& e, float ig) {
+  const float du = u - (top ? e.t.max1 : e.b.max1), dl = u - (top ? e.t.min1 : e.b.min1);
   const float ep = __expf(du * ig), em = __expf(-dl * ig);
   sums_add(S.t, top, du, dl, ep, em);
   sums_add(S.b, !top, du, dl, ep, em);
@@ -391,44 +391,167 @@ __device__ __forceinline__ double wave_sum(float v) {
 // extent, whole-net extent.
 struct AxisOut { float W, We, span; };
 
+// One planar axis of a net from its two sets' extremes and sums, and the exact extent with a pin (u on
+// its own die, f on the other) moved to the other die less the extent as it is
+struct Axis {
+  SetExt e;
+  AxisCoef c;
+  float We;
+  template <bool C>
+  __device__ __forceinline__ void finish(const AxisSums<C>& S, Counts n, float ig) {
+    c = axis_coef(e.t, val(S.t), n.t, e.b, val(S.b), n.b, ig);
+    We = w_exact(e.t.max1, e.t.min1, n.t, e.b.max1, e.b.min1, n.b);
+  }
+  __device__ __forceinline__ float flip(Counts n, bool top, float u, float f) const {
+    return w_flip(ext_sel(top, e.t, e.b), top ? n.t : n.b, ext_sel(top, e.b, e.t), top ? n.b : n.t, u, f) - We;
+  }
+  __device__ __forceinline__ AxisOut out() const {
+    return {c.W, We, fmaxf(e.t.max1, e.b.max1) - fminf(e.t.min1, e.b.min1)};
+  }
+};
+
 // One planar axis of a net: u[j] the lane's pins on their own die, replaced by their gradients;
-// f[j] on the other die, replaced by the exact extent with the pin moved there less the extent as
-// it is.  tail(fn) calls fn(k, u, f, top) for the lane's pins past the registers, put(k, g, dw)
-// takes their results.
-template <int G, bool kGrad, bool C, class Tail, class Put>
+// f[j] on the other die, replaced by Axis::flip.
+template <int G, bool kGrad, bool C>
 __device__ __forceinline__ AxisOut wl_axis(int d, int lg, float (&u)[kPinsPerLane], float (&f)[kPinsPerLane],
-                                           const bool (&top)[kPinsPerLane], Counts n, float ig, float big, Tail tail,
-                                           Put put) {
-  SetExt e = {ext_empty(), ext_empty()};
+                                           const bool (&top)[kPinsPerLane], Counts n, float ig, float big) {
+  Axis a = {{ext_empty(), ext_empty()}};
 #pragma unroll
   for (int j = 0; j < kPinsPerLane; ++j)
-    if (lg + G * j < d) ext_add(e, top[j], u[j]);
-  tail([&](int, float tu, float, bool tt) { ext_add(e, tt, tu); });
-  group_merge<G>(e);
+    if (lg + G * j < d) ext_add(a.e, top[j], u[j]);
+  group_merge<G>(a.e);
   AxisSums<C> S = {sums_start<C>(big), sums_start<C>(big)};
 #pragma unroll
   for (int j = 0; j < kPinsPerLane; ++j)
-    if (lg + G * j < d) sums_axis(S, top[j], u[j], top[j] ? e.t.max1 : e.b.max1, top[j] ? e.t.min1 : e.b.min1, ig);
-  tail([&](int, float tu, float, bool tt) {
-    sums_axis(S, tt, tu, tt ? e.t.max1 : e.b.max1, tt ? e.t.min1 : e.b.min1, ig);
-  });
+    if (lg + G * j < d) sums_axis(S, top[j], u[j], a.e, ig);
   sums_settle(S.t, big); sums_settle(S.b, big);
   group_merge<G>(S);
-  const AxisCoef c = axis_coef(e.t, val(S.t), n.t, e.b, val(S.b), n.b, ig);
-  const float We = w_exact(e.t.max1, e.t.min1, n.t, e.b.max1, e.b.min1, n.b);
+  a.finish(S, n, ig);
   if constexpr (kGrad) {
-    auto flip = [&](bool tt, float tu, float tf) {
-      return w_flip(ext_sel(tt, e.t, e.b), tt ? n.t : n.b, ext_sel(tt, e.b, e.t), tt ? n.b : n.t, tu, tf) - We;
-    };
 #pragma unroll
     for (int j = 0; j < kPinsPerLane; ++j)
       if (lg + G * j < d) {
-        f[j] = flip(top[j], u[j], f[j]);
-        u[j] = axis_grad(c, top[j], u[j], ig);
+        f[j] = a.flip(n, top[j], u[j], f[j]);
+        u[j] = axis_grad(a.c, top[j], u[j], ig);
       }
-    tail([&](int k, float tu, float tf, bool tt) { put(k, axis_grad(c, tt, tu, ig), flip(tt, tu, tf)); });
   }
-  return {c.W, We, fmaxf(e.t.max1, e.b.max1) - fminf(e.t.min1, e.b.min1)};
+  return a.out();
+}
+
+template <bool C>
+__device__ __forceinline__ ZCoef z_coef(const Sums4<C>& S, Range rz) {
+  const Sums4v sz = val(S);
+  ZCoef c = {rz.max, rz.min, rcp(sz.sp), 0.f, rcp(sz.sm), 0.f};
+  c.Az_p = sz.tp * c.az_p;
+  c.Az_m = sz.tm * c.az_m;
+  return c;
+}
+
+__device__ __forceinline__ void pin_range(Counts& n, Range& rz, float z, bool top) {
+  n.t += top ? 1 : 0;
+  n.b += top ? 0 : 1;
+  rz.max = fmaxf(rz.max, z);
+  rz.min = fminf(rz.min, z);
+}
+
+// net totals, from the group's first lane
+__device__ __forceinline__ NetTotals net_totals(int lg, const AxisOut& ax, const AxisOut& ay, Counts n, const ZCoef& c,
+                                                float alpha) {
+  NetTotals t = {0.f, 0.f, 0.f, 0.f, 0.f};
+  if (lg == 0) {
+    t.wa_bi = ax.W + ay.W;
+    t.wa_z = alpha * ((c.zmax - c.zmin) + (c.Az_p - c.Az_m));
+    t.hpwl = ax.We + ay.We;
+    t.hpwl3d = ax.span + ay.span + alpha * (c.zmax - c.zmin);
+    t.ncut = (n.t > 0 && n.b > 0) ? 1.f : 0.f;
+  }
+  return t;
+}
+
+// A net of more pins than a wavefront's lanes hold (64 kPinsPerLane), d of them from slot s: a lane holds its
+// first kPinsPerLane pins' coordinates, the others are read by each pass, W a lane at a time with all
+// their loads in flight: extremes of every axis, sums of x and z, sums of y (one planar axis's
+// compensated sums live at a time), results (of all pins, read again).  One wavefront's chain of loads
+// bounds it, three deep a round, and the sweep of a netlist that has one such net: 30000 pins 521 us, with
+// passes axis by axis, which read the pins past the registers nine times, 1495; 4000 nets of 400 pins,
+// totals alone 33 us and 41.
+template <bool kGrad, bool C>
+__device__ __forceinline__ NetTotals wl_wide(int s, int d, int lane, float half_dz, float four_over_dz, float ig, float big,
+                                             float alpha, const float4* __restrict__ xyzp,
+                                             const int32_t* __restrict__ pin_node, const float4* __restrict__ off,
+                                             const int32_t* __restrict__ slot_pos, float4* __restrict__ pin_out) {
+  constexpr int W = kGrad ? 3 : 1;      // as many as cost the kernel no wavefront (128 registers, four; 86, five)
+  const float4 q0 = at(xyzp, at(pin_node, s));
+  auto read = [&](int from, auto fn) {
+    int k = from + lane;
+    for (; k - lane + kWave * W <= s + d; k += kWave * W) {
+      int node[W];
+      float4 o[W], q[W];
+#pragma unroll
+      for (int j = 0; j < W; ++j) {
+        node[j] = at(pin_node, k + kWave * j);
+        o[j] = at(off, k + kWave * j);
+      }
+#pragma unroll
+      for (int j = 0; j < W; ++j) q[j] = at(xyzp, node[j]);
+#pragma unroll
+      for (int j = 0; j < W; ++j) fn(k + kWave * j, pin_rel(q[j], o[j], half_dz, q0.x, q0.y));
+    }
+    for (; k < s + d; k += kWave) fn(k, load_pin(xyzp, pin_node, off, k, half_dz, q0.x, q0.y));
+  };
+  float ux[kPinsPerLane], uy[kPinsPerLane], uz[kPinsPerLane];
+  bool top[kPinsPerLane];
+#pragma unroll
+  for (int j = 0; j < kPinsPerLane; ++j) {
+    const PinRel p = load_pin(xyzp, pin_node, off, s + kWave * j + lane, half_dz, q0.x, q0.y);
+    ux[j] = p.ux; uy[j] = p.uy; uz[j] = p.z; top[j] = p.top;
+  }
+  auto pins = [&](auto fn) {
+#pragma unroll
+    for (int j = 0; j < kPinsPerLane; ++j) fn(ux[j], uy[j], uz[j], top[j]);
+    read(s + kWave * kPinsPerLane, [&](int, const PinRel& p) { fn(p.ux, p.uy, p.z, p.top); });
+  };
+  Counts n = {0, 0};
+  Range rz = {kNegInf, kPosInf};
+  Axis x = {{ext_empty(), ext_empty()}}, y = x;
+  pins([&](float px, float py, float pz, bool pt) {
+    pin_range(n, rz, pz, pt);
+    ext_add(x.e, pt, px);
+    ext_add(y.e, pt, py);
+  });
+  group_merge<kWave>(n);
+  group_merge<kWave>(rz);
+  group_merge<kWave>(x.e);
+  group_merge<kWave>(y.e);
+  Sums4<C> sz = sums_start<C>(big);
+  {
+    AxisSums<C> S = {sums_start<C>(big), sums_start<C>(big)};
+    pins([&](float px, float, float pz, bool pt) {
+      sums_axis(S, pt, px, x.e, ig);
+      sums_z(sz, rz.max, rz.min, pz, ig);
+    });
+    sums_settle(S.t, big); sums_settle(S.b, big);
+    sums_settle(sz, big);
+    group_merge<kWave>(S);
+    group_merge<kWave>(sz);
+    x.finish(S, n, ig);
+  }
+  const ZCoef c = z_coef(sz, rz);
+  {
+    AxisSums<C> S = {sums_start<C>(big), sums_start<C>(big)};
+    pins([&](float, float py, float, bool pt) { sums_axis(S, pt, py, y.e, ig); });
+    sums_settle(S.t, big); sums_settle(S.b, big);
+    group_merge<kWave>(S);
+    y.finish(S, n, ig);
+  }
+  if constexpr (kGrad) {
+    read(s, [&](int k, const PinRel& p) {
+      const float dw = x.flip(n, p.top, p.ux, p.fx) + y.flip(n, p.top, p.uy, p.fy);
+      at(pin_out, at(slot_pos, k)) = make_float4(axis_grad(x.c, p.top, p.ux, ig), axis_grad(y.c, p.top, p.uy, ig),
+                                                 z_grad(c, p.z, ig, alpha), four_over_dz * (p.top ? -dw : dw));
+    });
+  }
+  return net_totals(lane, x.out(), y.out(), n, c, alpha);
 }
 
 // one net per group of G lanes; lane lg of the group holds pins lg + G j.  kGrad: also write the
@@ -441,6 +564,9 @@ __device__ __forceinline__ NetTotals wl_group(int net, int lg, float half_dz, fl
                                               const int32_t* __restrict__ pin_node, const float4* __restrict__ off,
                                               const int32_t* __restrict__ slot_pos, float4* __restrict__ pin_out) {
   const int s = at(s_net_start, net), d = at(s_net_start, net + 1) - s;
+  if constexpr (G == kWave)
+    if (d > G * kPinsPerLane)
+      return wl_wide<kGrad, C>(s, d, lg, half_dz, four_over_dz, ig, big, alpha, xyzp, pin_node, off, slot_pos, pin_out);
   float ux[kPinsPerLane], uy[kPinsPerLane], fx[kPinsPerLane], fy[kPinsPerLane], z[kPinsPerLane], xa, ya;
   bool top[kPinsPerLane];
   int pos[kPinsPerLane];
@@ -469,54 +595,20 @@ __device__ __forceinline__ NetTotals wl_group(int net, int lg, float half_dz, fl
     for (int j = 0; j < kPinsPerLane; ++j) {
       const PinRel p = pin_rel(q[j], o[j], half_dz, xa, ya);
       ux[j] = p.ux; uy[j] = p.uy; fx[j] = p.fx; fy[j] = p.fy; z[j] = p.z; top[j] = p.top;
-      if (lg + G * j < d) {
-        n.t += p.top ? 1 : 0;
-        n.b += p.top ? 0 : 1;
-        rz.max = fmaxf(rz.max, p.z);
-        rz.min = fminf(rz.min, p.z);
-      }
+      if (lg + G * j < d) pin_range(n, rz, p.z, p.top);
     }
   }
-  // pins past the registers (nets of more than 64 kPinsPerLane pins) are read again by each pass
-  auto tail = [&](auto fn) {
-    if constexpr (G == kWave)
-      for (int k = lg + G * kPinsPerLane; k < d; k += G) fn(k, load_pin(xyzp, pin_node, off, s + k, half_dz, xa, ya));
-  };
-  tail([&](int, const PinRel& p) {
-    n.t += p.top ? 1 : 0;
-    n.b += p.top ? 0 : 1;
-    rz.max = fmaxf(rz.max, p.z);
-    rz.min = fminf(rz.min, p.z);
-  });
   group_merge<G>(n);
   group_merge<G>(rz);
-  const AxisOut ax = wl_axis<G, kGrad, C>(
-      d, lg, ux, fx, top, n, ig, big,
-      [&](auto fn) { tail([&](int k, const PinRel& p) { fn(k, p.ux, p.fx, p.top); }); },
-      [&](int k, float g, float dw) {
-        float4& r = at(pin_out, at(slot_pos, s + k));
-        r.x = g;
-        r.w = dw;
-      });
-  const AxisOut ay = wl_axis<G, kGrad, C>(
-      d, lg, uy, fy, top, n, ig, big,
-      [&](auto fn) { tail([&](int k, const PinRel& p) { fn(k, p.uy, p.fy, p.top); }); },
-      [&](int k, float g, float dw) {
-        float4& r = at(pin_out, at(slot_pos, s + k));
-        r.y = g;
-        r.w += dw;
-      });
+  const AxisOut ax = wl_axis<G, kGrad, C>(d, lg, ux, fx, top, n, ig, big);
+  const AxisOut ay = wl_axis<G, kGrad, C>(d, lg, uy, fy, top, n, ig, big);
   Sums4<C> S = sums_start<C>(big);
 #pragma unroll
   for (int j = 0; j < kPinsPerLane; ++j)
     if (lg + G * j < d) sums_z(S, rz.max, rz.min, z[j], ig);
-  tail([&](int, const PinRel& p) { sums_z(S, rz.max, rz.min, p.z, ig); });
   sums_settle(S, big);
   group_merge<G>(S);
-  const Sums4v sz = val(S);
-  ZCoef c = {rz.max, rz.min, rcp(sz.sp), 0.f, rcp(sz.sm), 0.f};
-  c.Az_p = sz.tp * c.az_p;
-  c.Az_m = sz.tm * c.az_m;
+  const ZCoef c = z_coef(S, rz);
   if constexpr (kGrad) {
     // the FDA difference: (4/d_z) (W with the owner on top - W with it on the bottom)
 #pragma unroll
@@ -525,24 +617,8 @@ __device__ __forceinline__ NetTotals wl_group(int net, int lg, float half_dz, fl
         const float dw = fx[j] + fy[j];
         at(pin_out, pos[j]) = make_float4(ux[j], uy[j], z_grad(c, z[j], ig, alpha), four_over_dz * (top[j] ? -dw : dw));
       }
-    tail([&](int k, const PinRel& p) {
-      float4& r = at(pin_out, at(slot_pos, s + k));
-      const float dw = r.w;
-      r.z = z_grad(c, p.z, ig, alpha);
-      r.w = four_over_dz * (p.top ? -dw : dw);
-    });
   }
-
-  // ---- net totals, from the group's first lane
-  NetTotals t = {0.f, 0.f, 0.f, 0.f, 0.f};
-  if (lg == 0) {
-    t.wa_bi = ax.W + ay.W;
-    t.wa_z = alpha * ((rz.max - rz.min) + (c.Az_p - c.Az_m));
-    t.hpwl = ax.We + ay.We;
-    t.hpwl3d = ax.span + ay.span + alpha * (rz.max - rz.min);
-    t.ncut = (n.t > 0 && n.b > 0) ? 1.f : 0.f;
-  }
-  return t;
+  return net_totals(lg, ax, ay, n, c, alpha);
 }
 
 // tanh(x/2) for x >= 0: below x = 1/2 its Taylor series to the y^9 term (y = x/2; the first term
