@@ -741,7 +741,10 @@ struct Chunks {
   const int32_t* __restrict__ tile_start;   // [ntiles + 1] entry ranges of the tiles
   int32_t* plan;                            // the context's chunk plan (written by chunk_plan;
                                             // its layout is in the accessors below)
-  int ntiles, max_extra, from;
+  int ntiles, max_extra;
+  int from;                                 // tiles of up to this many entries stay whole (at least the plan's)
+  int round;                                // if the mean tile's chunks make more workgroups than this (0: any
+                                            // number will do), tiles of up to twice the mean stay whole too
   __device__ __forceinline__ int n_extra() const { return plan[0]; }
   __device__ __forceinline__ int most() const { return plan[1]; }
   __device__ __forceinline__ int first_extra(int tile) const { return plan[2 + tile]; }
@@ -774,7 +777,13 @@ __device__ __forceinline__ ChunkRef chunk_ref(const Chunks& ch, const TileGeom& 
   ck.first = ts;
   ck.last = te;
   const int v = te - ts, most = __builtin_amdgcn_readfirstlane(ch.most());
-  if (v > most && v > ch.from) {      // equal chunks, none above most
+  bool split = v > most && v > ch.from;
+  if (split && ch.round > 0) {
+    const int total = __builtin_amdgcn_readfirstlane(ch.tile_start[t.ntiles]);
+    const int chunks = (total - 1) / (most * t.ntiles) + 1;
+    split = chunks * t.ntiles <= ch.round || (long long)v * t.ntiles > 2ll * total;
+  }
+  if (split) {                        // equal chunks, none above most
     ck.nchunks = (v - 1) / most + 1;
     const int per = (v + ck.nchunks - 1) / ck.nchunks;
     ck.first = min(ts + kc * per, te);
@@ -1116,6 +1125,7 @@ __device__ __forceinline__ void gather_of_tiles(Geom g, TileGeom t, const float4
   if (qc >= t.ntiles && qc >= t.ntiles + __builtin_amdgcn_readfirstlane(ch.n_extra())) return;
   {
     const ChunkRef ck = chunk_ref(ch, t, qc);
+    if (ck.kc > 0 && ck.nchunks == 1) return;       // of a tile that the plan splits and this launch does not
     const int tile = ck.tile;
     const TileBox tb = tile_box(g, t, tile);
     EntryStream<2> es(entries, ck.first + (int)threadIdx.x, ck.last, (int)blockDim.x);
@@ -1619,7 +1629,21 @@ __global__ void k_cells_combine(int n, const uint8_t* __restrict__ cls, const in
 size_t tile_lds(const place3d_ctx* c, int maps) { return sizeof(float) * (size_t)maps * c->tg.T * c->tg.T * c->g.nz; }
 
 Chunks chunks_of(const place3d_ctx* c, SplitKind k) {
-  return Chunks{c->bk_tile_start, c->bk_plan[k], c->tg.ntiles, c->max_extra[k], kSplit[k].from};
+  return Chunks{c->bk_tile_start, c->bk_plan[k], c->tg.ntiles, c->max_extra[k], kSplit[k].from, 0};
+}
+
+// The field gather stages three maps a workgroup, so that a compute unit holds three of them, the chip 768.
+// Chunks of uniform tiles that go past that make a second, mostly empty round (1000 cells a tile on 484
+// tiles 32 us, whole 28; on 676 42 and 35; 2200 a tile on 361 41.6 and 38.3, on 729 65 and 56; 900k cells on
+// 1024 x 512 x 4 47 and 43), unless the tiles alone leave much of the chip idle (2700 a tile on 289 38
+// and 41).  There only tiles of twice the mean are split, and past one round of tiles those of more than 1536
+// entries (1000 cells a tile on 900 tiles 50 and 44; 2M cells among large instances on 1024 93, whole 96).
+constexpr int kGatherFew = 320, kGatherRound = 768, kGatherWhole = 1536;
+Chunks gather_chunks(const place3d_ctx* c) {
+  Chunks ch = chunks_of(c, kSplitGather);
+  if (ch.ntiles >= kGatherRound) ch.from = kGatherWhole;
+  else if (ch.ntiles >= kGatherFew) ch.round = kGatherRound;
+  return ch;
 }
 
 }  // namespace
@@ -1800,7 +1824,7 @@ int gather_bucketed_many(place3d_ctx* const* c, const float* const* xyz, const f
   launch_many<GatherArgs>(k_gather_tiles<1>, k_gather_tiles<kMaxMany>, nb, ntiles + extra, kTileThreads,
                           tile_lds(c[0], 3), s, [&](int i) {
     place3d_ctx* q = c[i];
-    return GatherArgs{q->g, q->tg, q->bk_entries, chunks_of(q, kSplitGather), ex[i], ey[i], ez[i], fx, q->entry_out,
+    return GatherArgs{q->g, q->tg, q->bk_entries, gather_chunks(q), ex[i], ey[i], ez[i], fx, q->entry_out,
                       q->large_rec, q->n_large, large_in_tiles(q) && q->n_large > 0 ? q->lpart : nullptr};
   });
   P3D_LAUNCH(c[0], "k_gather_tiles");

@@ -26,7 +26,8 @@ constexpr int kChunkGroup = 16;         // chunks of a tile whose density sums o
 // the tiles' first ones.  The gathers' chunks are independent, so that they are split as far as a
 // workgroup's staging of the maps allows (min of 16384, 2048, 1024: adjoint of 320k cells on 64 tiles
 // 62, 34, 23 us; gather of 200k cells on 256 tiles 28.6, 19.8, 16.1; 1.2M cells on four tiles with
-// count of 256, 512, 1024: 72, 51, 46).  The density chunks' sums have to meet, 0.1 us of fence each
+// count of 256, 512, 1024: 72, 51, 46); the field gather takes a tile's chunks as one again where that
+// costs it more than it gives (gather_chunks).  The density chunks' sums have to meet, 0.1 us of fence each
 // beside their bytes: tiles that would make two chunks are faster whole (64 of 5500 entries 25 us,
 // in two 27, in four 30), full ones in many (1.2M cells on four tiles: 165 us in 80 chunks, 86 in 160,
 // 72 in 256, 83 in 512).
