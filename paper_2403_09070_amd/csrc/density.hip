@@ -442,16 +442,19 @@ __global__ __launch_bounds__(kScanTiles * kScanParts) void k_bucket_scan_cols(in
   }
 }
 
-// A chunk plan of the current buckets, made by one workgroup of the scatter pass (every thread
+// A chunk plan of the current buckets, made by a workgroup of the scatter pass (every thread
 // takes the tiles [k0, k1) of the tile scan): a tile of more entries than the split's bounds is
 // heavy; its chunks after the first are numbered after the tiles, in tile order.  Layout of plan: [0] extra
 // chunks, [1] most, [2 + k] first extra chunk of tile k (-1 for a tile of one chunk), [2 + ntiles
 // + e] tile of extra chunk e, [2 + ntiles + max_extra + e] its index within the tile.  most is the
 // split's bound for the entries at hand, which keeps the extra chunks below max_extra: a tile of v
 // entries has floor((v - 1) / most) of them.
-__device__ void chunk_plan(const int32_t* totals, int entries, SplitBound sb, int k0, int k1, int ntiles,
-                           int max_extra, int32_t* __restrict__ plan) {
+// first: LDS for the tiles' first extra chunks, by which every thread finds the tiles of some (one thread
+// writing all of its tile's takes as long as the rest of the launch where 1.2M cells meet in four tiles).
+__device__ void chunk_plan(const int32_t* totals, int entries, SplitBound sb, int k0, int k1, int ntiles, int max_extra,
+                           int* first, int32_t* __restrict__ plan) {
   __shared__ int wx[kBucketThreads / kWave];
+  __shared__ int extras;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int most = max(sb.min, (entries + sb.count - 1) / sb.count), bound = max(most, sb.from);
   int ox = 0;
@@ -468,23 +471,25 @@ __device__ void chunk_plan(const int32_t* totals, int entries, SplitBound sb, in
   __syncthreads();
   int ex = ix - ox;                     // exclusive prefix of this thread's tiles
   for (int w = 0; w < wave; ++w) ex += wx[w];
-  int32_t* extra = plan + 2 + ntiles;
   for (int k = k0; k < k1; ++k) {
-    const int v = totals[k];
-    if (v > bound) {
-      const int nx = (v - 1) / most;
-      for (int j = 0; j < nx; ++j) {
-        extra[ex + j] = k;
-        extra[max_extra + ex + j] = j + 1;
-      }
-      plan[2 + k] = ex;
-      ex += nx;
-    } else {
-      plan[2 + k] = -1;
-    }
+    const int v = totals[k], nx = v > bound ? (v - 1) / most : 0;
+    first[k] = ex;
+    plan[2 + k] = nx > 0 ? ex : -1;
+    ex += nx;
   }
   // the last thread's tile range ends at the last tile: its running count is the total
-  if (threadIdx.x == blockDim.x - 1) { plan[0] = ex; plan[1] = most; }
+  if (threadIdx.x == blockDim.x - 1) { plan[0] = extras = ex; plan[1] = most; }
+  __syncthreads();
+  int32_t* extra = plan + 2 + ntiles;
+  for (int e = threadIdx.x; e < extras; e += blockDim.x) {
+    int lo = 0, hi = ntiles - 1;        // the last tile whose first extra chunk is at most e
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (first[mid] <= e) lo = mid; else hi = mid - 1;
+    }
+    extra[e] = lo;
+    extra[max_extra + e] = e - first[lo] + 1;
+  }
 }
 
 // kScan: the workgroup also adds up its column offsets and the tile totals from all blocks' counts,
@@ -500,7 +505,11 @@ __device__ __forceinline__ void bucket_scatter(Geom g, TileGeom t, const float* 
   // every workgroup scans the tile totals itself (exclusive prefix = tile_start) and workgroup 0
   // stores the result for the later passes; the cursor of tile k starts at tile_start[k] plus
   // this workgroup's offset within the tile
-  if ((int)blockIdx.x >= t.nblk) return;      // a launch over several contexts takes the most blocks of any
+  if ((int)blockIdx.x > t.nblk) return;       // a launch over several contexts takes the most blocks of any
+  // the workgroup past the last one with cells makes the two chunk plans: in workgroups 0 and 1, beside
+  // cells, they were the longest of the launch (bucketing of 2k instances 15.2 us, 13.6 so; 900k 37.8 and
+  // 36.9; 2M 67.9 and 66.0)
+  const bool plans = (int)blockIdx.x == t.nblk;
   extern __shared__ int cursor[];
   __shared__ int wsum[kBucketThreads / kWave];
   __shared__ int total;
@@ -555,17 +564,17 @@ __device__ __forceinline__ void bucket_scatter(Geom g, TileGeom t, const float* 
   for (int k = k0; k < k1; ++k) {
     const int v = kScan ? totals[k] : cursor[k];
     if (blockIdx.x == 0) tile_start[k] = run;
-    cursor[k] = run + (kScan ? cursor[k] : counts[(size_t)blockIdx.x * t.ntiles + k]);
+    cursor[k] = run + (kScan ? cursor[k] : plans ? 0 : counts[(size_t)blockIdx.x * t.ntiles + k]);
     run += v;
   }
   if (blockIdx.x == 0 && k0 < k1 && k1 == t.ntiles) tile_start[t.ntiles] = run;
   if (threadIdx.x == blockDim.x - 1) total = run;     // its tile range ends at the last tile
   __syncthreads();
-  // the two chunk plans, by workgroups 0 and 1 where there are two
-  if (blockIdx.x == 0) chunk_plan(totals, total, kSplit[kSplitDensity], k0, k1, t.ntiles, max_extra_d, plan_d);
-  if ((int)blockIdx.x == min(1, t.nblk - 1)) {
-    __syncthreads();            // a single workgroup makes both: the wavefront sums are free again
-    chunk_plan(totals, total, kSplit[kSplitGather], k0, k1, t.ntiles, max_extra_g, plan_g);
+  if (plans) {
+    chunk_plan(totals, total, kSplit[kSplitDensity], k0, k1, t.ntiles, max_extra_d, cursor, plan_d);
+    __syncthreads();            // the plan's LDS is free again
+    chunk_plan(totals, total, kSplit[kSplitGather], k0, k1, t.ntiles, max_extra_g, cursor, plan_g);
+    return;
   }
   const int n = g.n;
   const int base = blockIdx.x * t.cpb;
@@ -1749,10 +1758,10 @@ int bucket_cells_many(place3d_ctx* const* c, const float* const* xyz, int nb, hi
                        q->bk_plan[kSplitDensity], q->max_extra[kSplitGather], q->bk_plan[kSplitGather]};
   };
   if (own_scan)
-    launch_many<ScatterArgs>(k_bucket_scatter<true, 1>, k_bucket_scatter<true, kMaxMany>, nb, nblk, kBucketThreads,
+    launch_many<ScatterArgs>(k_bucket_scatter<true, 1>, k_bucket_scatter<true, kMaxMany>, nb, nblk + 1, kBucketThreads,
                              2 * hist, s, args);
   else
-    launch_many<ScatterArgs>(k_bucket_scatter<false, 1>, k_bucket_scatter<false, kMaxMany>, nb, nblk, kBucketThreads, hist,
+    launch_many<ScatterArgs>(k_bucket_scatter<false, 1>, k_bucket_scatter<false, kMaxMany>, nb, nblk + 1, kBucketThreads, hist,
                              s, args);
   P3D_LAUNCH(c[0], "k_bucket_scatter");
   return PLACE3D_OK;
