@@ -167,7 +167,8 @@ void layout_dense(place3d_ctx* c, const place3d_problem& p, Carver& w) {
   c->map_pc = w.take<float>(map); c->map_ps = w.take<float>(map); c->map_qc = w.take<float>(map);
 }
 
-size_t layout(place3d_ctx* c, const place3d_problem& p, char* base) {
+// steps: place3d_step will be called on the context
+size_t layout(place3d_ctx* c, const place3d_problem& p, bool steps, char* base) {
   Carver w{base};
   c->tg = tile_geom(p);
   c->part_stride = parts_bound(p, c->tg);
@@ -188,7 +189,7 @@ size_t layout(place3d_ctx* c, const place3d_problem& p, char* base) {
     q.mean = w.take<float>(nz * ny / 2);
   }
   c->split = split_solve(p);
-  c->step_dense = c->fft.on && split_steps(p);
+  c->step_dense = c->fft.on && split_steps(p) && steps;
   if (!c->fft.on || c->step_dense) layout_dense(c, p, w);
   c->rho = w.take<float>(map); c->phi = w.take<float>(map);
   c->ex = w.take<float>(map); c->ey = w.take<float>(map); c->ez = w.take<float>(map);
@@ -470,17 +471,29 @@ const char* place3d_last_error(const place3d_ctx* ctx) {
 }
 
 int32_t place3d_workspace_size(const place3d_problem* prob, size_t* bytes) {
+  return p3d::workspace_size(prob, true, bytes);
+}
+
+int32_t place3d_create(const place3d_problem* prob, void* d_workspace, size_t bytes, void* stream,
+                       place3d_ctx** out) {
+  return p3d::create(prob, true, d_workspace, bytes, stream, out);
+}
+
+}  // extern "C"
+
+namespace p3d {
+
+int workspace_size(const place3d_problem* prob, bool steps, size_t* bytes) {
   std::string why;
   int rc = check_problem(prob, why);
   if (rc != PLACE3D_OK) { g_create_err = why; return rc; }
   if (!bytes) { g_create_err = "bytes is NULL"; return PLACE3D_ERR_ARG; }
   place3d_ctx tmp;
-  *bytes = layout(&tmp, *prob, nullptr);
+  *bytes = layout(&tmp, *prob, steps, nullptr);
   return PLACE3D_OK;
 }
 
-int32_t place3d_create(const place3d_problem* prob, void* d_workspace, size_t bytes, void* stream,
-                       place3d_ctx** out) {
+int create(const place3d_problem* prob, bool steps, void* d_workspace, size_t bytes, void* stream, place3d_ctx** out) {
   std::string why;
   int rc = check_problem(prob, why);
   if (rc != PLACE3D_OK) { g_create_err = why; return rc; }
@@ -490,7 +503,7 @@ int32_t place3d_create(const place3d_problem* prob, void* d_workspace, size_t by
   place3d_ctx* c = new (std::nothrow) place3d_ctx();
   if (!c) { g_create_err = "out of host memory"; return PLACE3D_ERR_ARG; }
   c->prob = *prob;
-  size_t need = layout(c, *prob, reinterpret_cast<char*>(d_workspace));
+  size_t need = layout(c, *prob, steps, reinterpret_cast<char*>(d_workspace));
   if (bytes < need) {
     g_create_err = "workspace too small: need " + std::to_string(need) + " bytes";
     delete c;
@@ -535,6 +548,10 @@ int32_t place3d_create(const place3d_problem* prob, void* d_workspace, size_t by
   *out = c;
   return PLACE3D_OK;
 }
+
+}  // namespace p3d
+
+extern "C" {
 
 int32_t place3d_destroy(place3d_ctx* ctx) {
   delete ctx;

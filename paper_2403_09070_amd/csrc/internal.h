@@ -353,6 +353,11 @@ __device__ __forceinline__ void density_grad_of(const CellShares& cs, const floa
   d[0] = sx; d[1] = sy; d[2] = sz;
 }
 
+// place3d_workspace_size and place3d_create; steps: place3d_step and place3d_gp_init will be called on
+// the context (a multi-die problem's contexts take neither, and hold nothing for them)
+int workspace_size(const place3d_problem* prob, bool steps, size_t* bytes);
+int create(const place3d_problem* prob, bool steps, void* d_workspace, size_t bytes, void* stream, place3d_ctx** out);
+
 // ---- launchers implemented in the .hip sources (all enqueue only) ----
 int launch_zero_f64(place3d_ctx* c, double* p, int n, hipStream_t s);
 int launch_fill_f32(place3d_ctx* c, float* p, long long n, float v, hipStream_t s);

@@ -458,7 +458,7 @@ int md_layout(place3d_md2d_ctx* c, const place3d_md2d_problem& p, char* base, si
   for (int k = 0; k < 4; ++k) {
     fake_arrays(sub[k]);
     size_t b = 0;
-    const int rc = place3d_workspace_size(&sub[k], &b);
+    const int rc = workspace_size(&sub[k], false, &b);
     if (rc != PLACE3D_OK) { why = std::string("sub-problem: ") + place3d_last_error(nullptr); return rc; }
     c->sub_bytes[k] = b;
     c->sub_ws[k] = w.take<char>(b);
@@ -714,12 +714,12 @@ int32_t place3d_md2d_create(const place3d_md2d_problem* prob, void* d_workspace,
   place3d_problem q = wl_problem(p);
   q.size = c->wl_size; q.kind = c->wl_kind; q.net_start = p.net_start; q.pin2node = p.pin2node;
   q.pin_off = c->wl_off; q.fixed_xyz = c->wl_fixed;
-  rc = place3d_create(&q, c->sub_ws[0], c->sub_bytes[0], stream, &c->wl);
+  rc = create(&q, false, c->sub_ws[0], c->sub_bytes[0], stream, &c->wl);
   if (rc != PLACE3D_OK) return fail(rc, std::string("wirelength context: ") + place3d_last_error(nullptr));
   for (int L = 0; L < 3; ++L) {
     place3d_problem r = layer_problem(p, cnt[L]);
     r.size = c->l_size[L]; r.kind = c->l_kind[L]; r.net_start = c->l_start[L]; r.fixed_xyz = c->l_fixed[L];
-    rc = place3d_create(&r, c->sub_ws[1 + L], c->sub_bytes[1 + L], stream, &c->lay[L]);
+    rc = create(&r, false, c->sub_ws[1 + L], c->sub_bytes[1 + L], stream, &c->lay[L]);
     if (rc != PLACE3D_OK) return fail(rc, "layer " + std::to_string(L) + " context: " + place3d_last_error(nullptr));
     // E_z of a z-uniform map is zero: the gather reads it from a zero map
     const long long map = (long long)p.nx * p.ny * 2;
