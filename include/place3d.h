@@ -80,8 +80,9 @@ typedef enum place3d_status {
  * planar sides are powers of two in [64, 2048] with nz of 2 or 4 are solved by float32 fast
  * transforms in both precisions (problems with PLACE3D_DGRAD_FIELD); on every other grid, with
  * PLACE3D_DGRAD_ADJOINT, and in the steps of BF16X3 problems of more than 2^20 instances, the
- * precision picks the dense contractions; BF16X3 takes float32 ones too where they are faster (4097
- * to 786432 bins; odd sides or other layer counts with a side that is no multiple of 64).
+ * precision picks the dense contractions; BF16X3 takes float32 ones too, more exact and mostly faster,
+ * on grids of 4097 to 786432 bins and on odd sides or other layer counts with a side that is no
+ * multiple of 64.
  * BF16X3 also compensates the exponential sums, on every grid. */
 enum { PLACE3D_FP32 = 0,        /* float32 operands on float32 MFMA                          */
        PLACE3D_BF16X3 = 1 };    /* split hi/lo bfloat16 operands, three products, f32 accum  */

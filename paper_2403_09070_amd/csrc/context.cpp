@@ -90,8 +90,8 @@ p3d::TileGeom tile_geom(const place3d_problem& p) {
 }
 
 // Grids the fast transforms take: sides that are powers of two from 64 (below, a dense contraction
-// is as short as a launch) to 2048 (a workgroup's NZ groups of N / 16 lanes then reach 512 threads
-// and 70 KiB of LDS), and the two layer counts whose mixing a lane holds in registers.  They are
+// is as short as a launch) to 2048 (where a workgroup of the x pass reaches 1024 threads and 136 of the
+// 160 KiB of LDS), and the two layer counts whose mixing a lane holds in registers.  They are
 // faster over the whole range in both precisions (Ex, Ey and Ez of a map, against the float32
 // contractions): 64 x 64 x 2 20 us against 42, 128 x 128 x 4 20 against 61, 512 x 512 x 4 26 against
 // 172, 1024 x 1024 x 4 53 against 418 (split bf16 154), 2048 x 2048 x 4 284 against 2569 (split bf16,
@@ -106,26 +106,29 @@ bool fft_grid(const place3d_problem& p) {
   return side(p.nx) && side(p.ny) && (p.nz == 2 || p.nz == 4) && p.dgrad == PLACE3D_DGRAD_FIELD;
 }
 
-// Steps of large split-bf16 problems keep the contractions too, for the same reason: an instance
-// that the first steps leave within a few float32 units of the mid-plane takes the other die's
-// sizes and offsets when the solve rounds otherwise, and the split contractions' rounding (3.4e-6 of
-// the gradient) moves enough positions that one of 1.2M instances did so in 4 of 16 starts, against
-// none of up to 640k instances in 45 (float32: 1 of 14, none of 20).  They pay
-// for it: a step of 1.2M instances on 1024 x 1024 x 4 takes 421 us, 350 with the transforms.
+// Steps of large split-bf16 problems keep the contractions too, so that their iterates stay those of the
+// contractions: an instance that the first steps leave within a few float32 units of the mid-plane takes the
+// other die's sizes and offsets when the solve rounds otherwise.  Between the two solves one of 1.2M
+// instances did so in 4 of 16 starts, none of up to 640k in 45; the number grows with the instances,
+// and the line lies between the sizes tried.  It is the form's own rounding that shows so, not an error of the
+// transforms: float32 problems of 1.2M, which take them, have the same event in 1 of 14 starts, and the
+// contractions are the less exact (3.4e-6 of the gradient against 3.5e-7) and the slower (a step of 1.2M
+// instances on 1024 x 1024 x 4 418 us, 350 with the transforms).
 bool split_steps(const place3d_problem& p) { return p.precision == PLACE3D_BF16X3 && p.n_inst > (1 << 20); }
 
 // sides and layers that the split-bf16 chain takes
 bool split_chain(const place3d_problem& p) { return p.nx % 2 == 0 && p.ny % 2 == 0 && (p.nz == 2 || p.nz == 4); }
 
-// Whether the dense contractions of a BF16X3 problem run in split bf16: where that is faster than
-// float32.  Its launches convert and write three operands for every one they read, so that grids of
-// up to 786432 bins are faster in float32, or level (Ex, Ey and Ez, split against float32: 66 x 70 x 2
-// 37 us and 32, 260 x 260 x 4 62 and 56, 420 x 380 x 4 71 and 77, 520 x 520 x 2 78 and 81; phi alone 37
-// and 30, 61 and 47, 69 and 58, 77 and 65; then 700 x 700 x 2 88 and 131, 520 x 520 x 4 83 and 124,
-// 1000 x 900 x 4 170 and 360, 512 x 512 x 6 94 and 133), and outside the chain it loads element by
-// element unless the sides are multiples of 64 (398 x 354 x 6 177 and 98, 999 x 1001 x 4 1050 and 640).
-// Grids of up to 4096 bins are launches either way (32 x 32 x 4 29, 34 x 38 x 2 34 in float32) and keep
-// it, as do large problems with their steps.
+// Whether the dense contractions of a BF16X3 problem run in split bf16.  Its launches convert and write
+// three operands for every one they read, so that on grids of up to 786432 bins float32, ten times as
+// exact, is faster, or for the field up to a tenth slower (Ex, Ey and Ez, split against float32: 66 x 70 x 2
+// 37 us and 32, 260 x 260 x 4 62 and 56, 420 x 380 x 4 71 and 77, 520 x 520 x 2 78 and 81, 640 x 600 x 2 90
+// and 95, 256 x 384 x 8 76 and 81, 512 x 256 x 6 75 and 82; phi alone, in the order of the first four, 37 and
+// 30, 61 and 47, 69 and 58, 77 and 65).  Past that it is far slower (700 x 700 x 2 88 and 131, 520 x 520 x 4
+// 83 and 124, 1000 x 900 x 4 170 and 360, 512 x 512 x 6 94 and 133).  Outside the chain the split loads
+// element by element unless the sides are multiples of 64 (398 x 354 x 6 177 and 98, 999 x 1001 x 4 1050 and
+// 640).  Grids of up to 4096 bins are launches either way (32 x 32 x 4 29, 34 x 38 x 2 34 in float32) and keep
+// the split, as do large problems with their steps.
 bool split_solve(const place3d_problem& p) {
   if (p.precision != PLACE3D_BF16X3) return false;
   const long long bins = (long long)p.nx * p.ny * p.nz;

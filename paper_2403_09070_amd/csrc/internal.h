@@ -101,7 +101,8 @@ struct SplitChain {
 
 // Fast transforms of the solve (fft_grid in context.cpp): tables per axis, the stages'
 // twiddles (at most kFftTable N entries) and e^{-i pi k / 2N} (k <= N / 2), and the means of the rows in
-// hand ([nz][ny / 2], a call's scratch).  The dense bases and the split chain are then not built.
+// hand ([nz][ny / 2], a call's scratch).  The dense bases and the split chain are then built only where a
+// step takes them (step_dense).
 constexpr int kFftTable = 2;
 struct FftChain {
   int on = 0;
@@ -387,7 +388,6 @@ int reduce_final2(place3d_ctx* c, const double* part, int stride, int slot0, int
                   double* out1, hipStream_t s);
 
 int build_fixed_map(place3d_ctx* c, hipStream_t s);
-// part 0: the whole bucketing; 1: only the count pass (which also packs xyzp); 2: the rest
 // The same launch over up to kMaxMany contexts (blockIdx.y picks one), for the layers of a multi-die
 // problem: their grids and options are the same, their instances are not.
 constexpr int kMaxMany = 3;
